@@ -34,16 +34,20 @@ steps, roofline, CPU oracle baseline and error against the oracle):
       single-right-hand-side FP64 CG (W = 1), tol 1e-10.
 
 value = RHS * site * CG-iteration / s over the K timed steps (iterations
-counted per right-hand side up to its own convergence).  Block widths and
+counted per right-hand side up to its own convergence, as the library counts
+them: iterations of CG on A.  Every extent here is even, so the solves run on
+the even-odd reduced system, one step of which advances the Krylov space of A
+by two degrees and counts as two iterations).  Block widths and
 stencil launches come from the library's autotuner (rhs_block = 0; the
 batch's width from its traffic model), timed in the untimed warm-up.  roofline: the
 stencil kernel (the dominant kernel), its launches timed with HIP events on
 the stream they run on, inside the timed region, against the algorithmic
 bytes the library reports for them.  cg_bandwidth: the whole CG at the
-algorithmic bytes of an iteration, 6V + 4L/W per right-hand side and site
-(x, r, p read and written once, the four links per site shared by W lanes;
-V, L the bytes of a site vector and of a link), and beside it the bytes this
-schedule moves (schedule_bytes).  cpu_baseline: the FP64 oracle (OpenMP, one
+algorithmic bytes of an iteration, half of an even-odd step: (3V + 4L/W) / 2
+per right-hand side and site (x, r, p read and written once on half the
+sites, the four links per site shared by W lanes; V, L the bytes of a site
+vector and of a link), and beside it the bytes this schedule moves
+(schedule_bytes).  cpu_baseline: the FP64 oracle (OpenMP, one
 right-hand side per host thread) on a bounded sample of the same right-hand
 sides, at the workload's tolerance; the same solutions give error_vs_oracle,
 the largest |t_j - t_j(oracle)| over max |t_j(oracle)| of the per-right-hand-
@@ -144,16 +148,19 @@ def roofline(stats, tag, kernel):
 
 def cg_bandwidth(site_iters, elapsed, inner, W, nc=3):
     """Whole-CG bandwidth.  site_iters = sum over right-hand sides of CG
-    iterations x sites.  Algorithmic bytes per RHS*site*iteration: 6V + 4L/W.
-    This schedule: the stencil reads p (and, BF16, r) and writes q; the
-    update reads r, p, q and writes r, p, and with FP64 storage reads and
-    writes x too (mixed precision: every other iteration); the eight hop
-    links of a site are read once per W lanes: FP64 9V, FP32 8V, BF16 9V,
-    each + 8L/W."""
+    iterations x sites, an even-odd step counted as two iterations.
+    Algorithmic bytes per RHS*site*iteration: a step reads and writes x, r, p
+    once on half the sites and each link once, (3V + 4L/W) / 2.  This
+    schedule, per step and half-lattice vector: the odd-half stencil reads
+    p_e and writes p_o, the even-half one reads p_o, p_e (and, BF16, r) and
+    writes q; the update reads r, p, q and writes r, p, and with FP64 storage
+    reads and writes x too (mixed precision: every other step); the eight hop
+    links of a site are read once per W lanes: FP64 12, FP32 11, BF16 12
+    quarter passes of V an iteration, each + 4L/W."""
     c = CB[inner]
     V, L = nc * c, nc * nc * c
-    alg = 6 * V + 4 * L / W
-    sched = {"f64": 9, "f32": 8, "bf16": 9}[inner] * V + 8 * L / W
+    alg = 1.5 * V + 2 * L / W
+    sched = {"f64": 12, "f32": 11, "bf16": 12}[inner] * V / 4 + 4 * L / W
     a = site_iters * alg / elapsed / 1e9
     return {"alg_bytes_per_rhs_site_iter": alg, "alg_bytes": site_iters * alg, "achieved": a, "unit": "GB/s",
             "frac": a / HBM_PEAK_GBS, "schedule_bytes_per_rhs_site_iter": sched,
@@ -338,7 +345,7 @@ def run_gauge16(a, torch, dp, workloads, steps, warmup, cpu, plain):
                                  "per step), Z2 complex noise, tol 1e-8",
                      "rhs_per_step": sum(s["nrhs"] for s in stats) // steps, "rhs_block": W, "inner": inner,
                      "colours": [int(v) for v in ncols], "coloring_seconds": t_color}
-    out["roofline"] = roofline(stats, f"gauge16_{inner}_w{W}", "k_stencil (q = A p, p^H q, |q|^2)")
+    out["roofline"] = roofline(stats, f"gauge16_{inner}_w{W}", "k_stencil (the two half stencils of a step)")
     out["cg_bandwidth"] = cg_bandwidth(rhs_iters * N, elapsed, inner, W)
     out["stats"] = stats
     return out
@@ -359,11 +366,8 @@ def run_uneven(a, torch, dp, workloads, steps, warmup, cpu, plain):
         cols.append((torch.from_numpy(np.ascontiguousarray(col)).cuda(), m, col))
         ops.append(c.operator(w.dims, w.nc, w.m2, torch.from_numpy(U).cuda()))
     t_color = time.time() - t0
-    # reliable-update drop: swept on this batch (BF16, W = 32, paired x
-    # updates, ms per step): 0.0002 / 0.0005 / 0.001 / 0.002 / 0.003 /
-    # 0.005 -> 102.1 / 96.8 / 93.3 / 89.7 / 91.1 / 92.4 (1.76 / 1.59 / 1.48 /
-    # 1.44 / 1.45 / 1.48 M iterations)
-    delta = 0.002 if a.delta is None else a.delta
+    # reliable-update drop: the library's own choice for BF16
+    delta = 0.0 if a.delta is None else a.delta
     opts = c.opts(tol=inst[0].tol, inner=inner, rhs_block=W_req, reliable_delta=delta, use_graph=a.graph or 0)
 
     def specs(sample):
@@ -415,7 +419,7 @@ def run_uneven(a, torch, dp, workloads, steps, warmup, cpu, plain):
                                  "Z2 complex sample per instance per step, tol 1e-8",
                      "rhs_per_step": sum(s["nrhs"] for s in stats) // steps, "rhs_block": W, "inner": inner,
                      "reliable_delta": delta, "sites": sum(w.volume for w in inst), "coloring_seconds": t_color}
-    out["roofline"] = roofline(stats, f"batch64_{inner}_w{W}", "k_b_stencil (q = A p and its dot products)")
+    out["roofline"] = roofline(stats, f"batch64_{inner}_w{W}", "k_b_stencil (the two half stencils of a step)")
     out["cg_bandwidth"] = cg_bandwidth(site_iters, elapsed, inner, W)
     out["stats"] = stats
     return out
@@ -465,7 +469,7 @@ def run_gauge32(a, torch, dp, workloads, steps, warmup, cpu, plain):
                                  f"({m * nc} forward + {m * nc} adjoint RHS), Z2 complex noise, tol 1e-10",
                      "rhs_per_step": sum(s["nrhs"] for s in stats) // steps, "rhs_block": W, "inner": inner,
                      "coloring_seconds": t_color}
-    out["roofline"] = roofline(stats, f"gauge32_{inner}_w{W}", "k_stencil (q = A p, p^H q, |q|^2)")
+    out["roofline"] = roofline(stats, f"gauge32_{inner}_w{W}", "k_stencil (the two half stencils of a step)")
     out["cg_bandwidth"] = cg_bandwidth(rhs_iters * N, elapsed, inner, W)
     out["stats"] = stats
     return out

@@ -178,7 +178,11 @@ typedef struct {
 typedef struct {
     double tol;             /* stop when |b - A x| / |b| <= tol (FP64 true residual
                                for mixed precision; recursive residual for F64) */
-    int32_t max_iter;       /* iteration limit per right-hand side (0: 100000) */
+    int32_t max_iter;       /* iteration limit per right-hand side (0: 100000) of CG on A;
+                               where every extent is even (and m2 > -8) the solves run on
+                               the even-odd reduced system, one step of which advances
+                               the Krylov space of A by two degrees and counts as two
+                               iterations here and in dp_solve_stats */
     int32_t inner;          /* DP_PREC_*: storage of the inner CG vectors and links;
                                F32 and BF16 accumulate in FP32 and are refined by
                                FP64 reliable updates */
@@ -194,8 +198,8 @@ typedef struct {
     double reliable_delta;  /* mixed precision: replace the residual by the FP64
                                true residual once it dropped by this factor; a lane
                                that reaches it waits for that update before it moves
-                               on (0: 0.002 for BF16, 1e-3 for F32).  BF16 storage
-                               resolves about 3 digits: smaller values cost extra
+                               on (0: 1e-3 for F32; for BF16 0.002, and 0.01 on the
+                               even-odd reduced system).  BF16 storage resolves about 3 digits: smaller values cost extra
                                iterations, larger ones extra FP64 updates */
     int32_t use_graph;      /* 1: replay the iteration loop from a captured hipGraph */
     int32_t profile;        /* 1: time stencil kernel launches with HIP events (single
@@ -205,7 +209,8 @@ typedef struct {
 
 typedef struct {
     int64_t nrhs;            /* right-hand sides solved */
-    int64_t rhs_iters;       /* sum over right-hand sides of CG iterations to convergence */
+    int64_t rhs_iters;       /* sum over right-hand sides of CG iterations to convergence
+                                (a step of the even-odd reduced system counts as two) */
     int32_t max_iters;       /* largest iteration count of one right-hand side */
     int32_t nconverged;      /* right-hand sides that met tol */
     int32_t nbreakdown;      /* right-hand sides that broke down */
@@ -218,6 +223,9 @@ typedef struct {
                                 launch 2*W*V + 4*L (read p and write q for the W right-hand
                                 sides, read each of the 4 links once), V = bytes of one site
                                 vector, L = bytes of one link matrix (0 without links).
+                                Even-odd: two launches per step, per site of a half
+                                2*W*V + 8*L (p_e read, p_o written) and 3*W*V + 8*L
+                                (p_o and p_e read, q_e written).
                                 A multi-instance launch (solve_batch / trace_estimate with
                                 ninst > 1) covers every instance: its totals are reported
                                 in the stats of instance 0 only */

@@ -41,7 +41,7 @@ dp_status solve_cfg(dp_ctx *ctx, const dp_solve_opts *o, SolveCfg &c) {
     c.tol = o->tol;
     c.max_iter = o->max_iter > 0 ? o->max_iter : 100000;
     c.inner = o->inner;
-    c.delta = o->reliable_delta > 0 ? o->reliable_delta : default_reliable_delta(c.inner);
+    c.delta = o->reliable_delta > 0 ? o->reliable_delta : 0.0;
     c.profile = o->profile;
     c.use_graph = o->use_graph;
     c.ru_gap = default_ru_gap(c.inner);
@@ -332,6 +332,7 @@ dp_status dp_solve_batch(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, con
                 return DP_EINVAL;
             }
             DP_TRY(batch_inst(ctx, ops[i], in[i]));
+            in[i].index = i;
             in[i].nrhs = nrhs[i];
             in[i].babi = (const double *)b[i];
             in[i].xabi = (double *)x[i];
@@ -571,6 +572,7 @@ dp_status dp_trace_estimate(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, 
                 return DP_EINVAL;
             }
             DP_TRY(batch_inst(ctx, ops[i], in[i]));
+            in[i].index = i;
             const int ndil = ps[i].dilute ? ps[i].nc : 1;
             in[i].nrhs = (long long)ps[i].nsamples * ps[i].ncolors * ndil;
             in[i].ps = ps[i];
@@ -793,7 +795,7 @@ dp_status dp_apply(dp_ctx *ctx, const dp_operator *opd, int32_t prec, const void
     }
     if (nrhs == 0) return DP_OK;
     OpPrep op;
-    DP_TRY(prepare_operator(ctx, *opd, prec, op, stream));
+    DP_TRY(prepare_operator(ctx, *opd, prec, op, stream, false));
     SolveCfg cfg;
     cfg.inner = prec;
     int W = 1;

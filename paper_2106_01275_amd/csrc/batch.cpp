@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -64,12 +65,17 @@ struct Job {
 
 }  // namespace
 
-dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg, int W, bool trace_mode,
-                    hipStream_t s) {
+static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg, int W, bool trace_mode,
+                            hipStream_t s) {
     const int ninst = (int)in.size();
     const bool mixed = cfg.inner != kF64;
     const int nc = in[0].nc;
     const bool links = in[0].links;
+    const int eo = in[0].lat.eo;  // (the same for every instance of a run)
+    // even-odd order: a step counts as two iterations (solve_block)
+    const int mult = eo ? 2 : 1;
+    const int max_steps = (cfg.max_iter + mult - 1) / mult, ru_gap = std::max(1, cfg.ru_gap / mult);
+    const int check_every = std::max(1, ctx->check_every / mult);
     for (auto &I : in)
         if (!block_fits(I.lat, nc, W, cfg.inner)) {
             ctx->err = "rhs_block too wide for an instance: a block vector (N * nc * rhs_block elements) must "
@@ -120,7 +126,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
     // workgroups of a launch: enough for every slot to run its largest
     // lattice with a full grid, at most kLaunchBlk, a multiple of 8
     const int spt = kBlock >> logW;
-    const int maxtiles = (maxN + spt - 1) / spt;
+    const int maxtiles = ((eo ? maxN / 2 : maxN) + spt - 1) / spt;
     int gblk = (int)std::min<long long>(kLaunchBlk, (long long)nslots * grid_blocks(maxtiles));
     gblk = std::max(8 * nslots, gblk - gblk % 8);
 
@@ -201,10 +207,12 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
         cs.ctrld = (double *)(ctrl_all + 16 * k + 8);
         cs.live = live_all + k;
         cs.tol2 = cfg.tol * cfg.tol;
-        cs.delta2 = cfg.delta * cfg.delta;
+        const double delta = cfg.delta > 0 ? cfg.delta : default_reliable_delta(cfg.inner, eo);
+        cs.delta2 = delta * delta;
         cs.hold = cfg.inner == kBF16;
         cs.rq_direct = cfg.inner == kBF16;
         cs.exact = !mixed;
+        cs.ru_restart = cfg.inner == kBF16 && eo;
     }
     std::vector<int> slot_of((size_t)gblk, nslots);
     SlotDesc *d_sd = nullptr;
@@ -221,6 +229,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
     B.nc = nc;
     B.prec = cfg.inner;
     B.links = links;
+    B.eo = eo;
     B.mode = W >= 64 ? 2 : (W >= 16 ? 1 : 0);
     B.stream = s;
 
@@ -230,12 +239,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
         const Job &jb = jobs[jidx];
         BatchInst &I = in[jb.inst];
         SlotDesc &d = hsd[k];
-        d.L.lat = I.lat;
-        d.L.nc = nc;
-        const bool half = batch_narrow_last(W, jb.nv);
-        d.L.W = half ? W / 2 : W;
-        d.L.logW = half ? logW - 1 : logW;
-        d.L.ntiles = (I.lat.N + (kBlock >> d.L.logW) - 1) / (kBlock >> d.L.logW);
+        set_geometry(d.L, I.lat, nc, batch_narrow_last(W, jb.nv) ? W / 2 : W);
         d.L.stream = s;
         d.diag = I.m2 + 8.0;
         d.U = I.U8;
@@ -334,8 +338,21 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
             for (int k = 0; k < nslots; ++k) {
                 if (!(hsd[k].flags & kSlotInit)) continue;
                 const Job &jb = jobs[slot_job[k]];
-                launch_init_abi(hsd[k].L, cfg.inner, in[jb.inst].babi, jb.r0, jb.nv, hsd[k].b64, hsd[k].r,
-                                hsd[k].p, hsd[k].xlo, hsd[k].x64, mixed ? 1 : 0, hsd[k].rd, hsd[k].cs);
+                const SlotDesc &d = hsd[k];
+                InitArgs ia;
+                ia.b64 = d.b64;
+                ia.r = d.r;
+                ia.p = d.p;
+                ia.xlo = d.xlo;
+                ia.x64 = d.x64;
+                ia.mixed = mixed ? 1 : 0;
+                ia.links = links;
+                ia.diag = d.diag;
+                ia.U = d.U;
+                ia.nbr = d.nbr;
+                ia.rd = d.rd;
+                ia.cs = d.cs;
+                launch_init_abi(d.L, cfg.inner, in[jb.inst].babi, jb.r0, jb.nv, ia);
             }
         }
         DP_HIP(hipGetLastError());
@@ -382,8 +399,9 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
             for (int j = 0; j < jb.nv; ++j) {
                 const double bb = bbv[j];
                 I.st.max_true_resid = std::max(I.st.max_true_resid, bb > 0 ? std::sqrt(true_rr[j] / bb) : 0.0);
-                I.st.rhs_iters += iters[j];
-                I.st.max_iters = std::max(I.st.max_iters, iters[j]);
+                const int n = eo ? std::min(iters[j] * mult, cfg.max_iter) : iters[j];
+                I.st.rhs_iters += n;
+                I.st.max_iters = std::max(I.st.max_iters, n);
                 if (flags[j] & kFlagBreakdown) ++I.st.nbreakdown;
                 else if (flags[j] & kFlagConverged) ++I.st.nconverged;
                 if (trace_mode) {
@@ -401,7 +419,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
     for (int k = 0; k < nslots && next_job < jobs.size(); ++k) assign(k, (int)next_job++);
     DP_TRY(init_slots());
 
-    int steps_next = std::max(1, ctx->check_every);
+    int steps_next = check_every;
     // mixed precision: the x updates of an iteration group in pairs (as in
     // the single-instance solve)
     const bool xdefer = mixed && xdefer_enabled();
@@ -414,7 +432,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
         if (!any) break;
         int steps = steps_next;
         for (int k = 0; k < nslots; ++k)
-            if (hsd[k].flags & kSlotIter) steps = std::min(steps, std::max(1, cfg.max_iter - slot_it[k]));
+            if (hsd[k].flags & kSlotIter) steps = std::min(steps, std::max(1, max_steps - slot_it[k]));
         if (cfg.use_graph && !cfg.profile) {
             // B is fixed for the call, and the graphs are dropped before and after it
             const std::string key = "batch " + std::to_string(steps) + (xdefer ? " xdefer" : "");
@@ -432,10 +450,16 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
             }
             DP_HIP(hipGraphLaunch(g->second, s));
         } else {
-            double bytes = 0;
+            double bytes = 0, hop_bytes = 0;
             for (int k = 0; k < nslots; ++k)
-                if (hsd[k].flags & kSlotIter) bytes += stencil_alg_bytes(hsd[k].L.lat, nc, hsd[k].L.W, cfg.inner, B.links);
+                if (hsd[k].flags & kSlotIter) {
+                    bytes += stencil_alg_bytes(hsd[k].L, cfg.inner, B.links, kStFull);
+                    hop_bytes += stencil_alg_bytes(hsd[k].L, cfg.inner, B.links, kStHop);
+                }
             for (int c = 0; c < steps; ++c) {
+                if (eo)
+                    DP_TRY(timed_launch(ctx, cfg.profile != 0, hop_bytes,
+                                        [&](hipEvent_t e0, hipEvent_t e1) { launch_b_hop(B, e0, e1); }));
                 DP_TRY(timed_launch(ctx, cfg.profile != 0, bytes,
                                     [&](hipEvent_t e0, hipEvent_t e1) { launch_b_stencil(B, e0, e1); }));
                 launch_b_update(B, xmode_of(c, steps, xdefer));
@@ -460,17 +484,17 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
                 any_fin = true;
                 continue;
             }
-            if (mixed && (c[2] > 0 || c[1] == nactive || slot_it[k] >= cfg.max_iter ||
-                          slot_it[k] - slot_ru[k] >= cfg.ru_gap)) {
+            if (mixed && (c[2] > 0 || c[1] == nactive || slot_it[k] >= max_steps ||
+                          slot_it[k] - slot_ru[k] >= ru_gap)) {
                 d.flags = kSlotIter | kSlotRU;
                 slot_ru[k] = slot_it[k];
                 any_ru = true;
-            } else if (slot_it[k] >= cfg.max_iter) {
+            } else if (slot_it[k] >= max_steps) {
                 d.flags = kSlotFinal;
                 any_fin = true;
                 continue;
             }
-            next_steps = std::min(next_steps, next_check(std::max(1, ctx->check_every), ratio, ratio_prev[k],
+            next_steps = std::min(next_steps, next_check(check_every, ratio, ratio_prev[k],
                                                          slot_it[k] - it_prev[k], cfg.inner == kBF16 ? ru_ratio : 0.0));
             ratio_prev[k] = ratio;
             it_prev[k] = slot_it[k];
@@ -490,7 +514,7 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
                 if (!(d.flags & kSlotRU)) continue;
                 ++in[jobs[slot_job[k]].inst].st.reliable_updates;
                 d.flags = kSlotIter;
-                if (slot_it[k] >= cfg.max_iter) {
+                if (slot_it[k] >= max_steps) {
                     d.flags = kSlotFinal;
                     any_fin = true;
                 }
@@ -518,6 +542,39 @@ dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg
     if (cfg.profile) DP_TRY(finish_profile(ctx, &in[0].st));
     ctx->drop_graphs();
     return DP_OK;
+}
+
+dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg, int W, bool trace_mode,
+                    hipStream_t s) {
+    for (auto &I : in) I.lat.eo = eo_reducible(I.lat.D, I.m2);
+    const auto first_plain = std::stable_partition(in.begin(), in.end(), [](const BatchInst &I) { return I.lat.eo; });
+    const long n = first_plain - in.begin();
+    dp_status st = DP_OK;
+    if (n == 0 || n == (long)in.size()) {
+        st = run_engine(ctx, in, cfg, W, trace_mode, s);
+    } else {
+        std::vector<BatchInst> part(std::make_move_iterator(first_plain), std::make_move_iterator(in.end()));
+        in.resize((size_t)n);
+        st = run_engine(ctx, in, cfg, W, trace_mode, s);
+        if (st == DP_OK) st = run_engine(ctx, part, cfg, W, trace_mode, s);
+        in.insert(in.end(), std::make_move_iterator(part.begin()), std::make_move_iterator(part.end()));
+    }
+    // the launch totals, reported by each run in its first instance, belong to instance 0
+    dp_solve_stats tot{};
+    for (auto &I : in) {
+        tot.stencil_ms += I.st.stencil_ms;
+        tot.stencil_launches += I.st.stencil_launches;
+        tot.stencil_bytes += I.st.stencil_bytes;
+        tot.stencil_bytes_all += I.st.stencil_bytes_all;
+        I.st.stencil_ms = I.st.stencil_bytes = I.st.stencil_bytes_all = 0;
+        I.st.stencil_launches = 0;
+    }
+    std::sort(in.begin(), in.end(), [](const BatchInst &a, const BatchInst &b) { return a.index < b.index; });
+    in[0].st.stencil_ms = tot.stencil_ms;
+    in[0].st.stencil_launches = tot.stencil_launches;
+    in[0].st.stencil_bytes = tot.stencil_bytes;
+    in[0].st.stencil_bytes_all = tot.stencil_bytes_all;
+    return st;
 }
 
 }  // namespace dp

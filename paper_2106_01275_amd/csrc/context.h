@@ -48,6 +48,7 @@ struct BlockStats {
     long long iters_sum = 0;
     int iters_max = 0, nconv = 0, nbreak = 0, nvalid = 0, ru = 0;
     double max_rel = 0;
+    int it_mult = 1, it_cap = 0;  // reported iterations: state's count * it_mult, at most it_cap (0: no cap)
 };
 
 }  // namespace dp
@@ -108,13 +109,16 @@ struct SolveCfg {
     double tol = 1e-10;
     int max_iter = 100000;
     int inner = kF64;
-    double delta = 0.1;
+    double delta = 0;     // residual drop between reliable updates; 0: default_reliable_delta
     int ru_gap = 100;     // a reliable update at least every ru_gap iterations (mixed)
     int profile = 0;
     int W = 0, logW = 0;
 };
 
-dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep &out, hipStream_t s);
+// reduce: put the sites in even-odd order where the operator allows it (the
+// solves); otherwise, and for the operator itself, index order
+dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep &out, hipStream_t s,
+                           bool reduce = true);
 // Looks up (once per device, with `device` current) the device address of
 // the static scratch array of dp_solve_noalloc.
 dp_status noalloc_attach(int device, std::string &err);
@@ -122,13 +126,21 @@ dp_status noalloc_attach(int device, std::string &err);
 // largest number the stencil tuner may pick (partial-sum buffers are sized
 // for it)
 int launch_blocks(const Lat &lat, int W);
+// One CG step: the stencil (in even-odd order the odd half of p first) with
+// its reduction, the finishing kernel and the vector update.  a: the even (or
+// whole-lattice) stencil.
+void launch_cg_step(const Launch &L, int prec, const StencilArgs &a, void *xlo, int xmode);
+// the odd half of p, H p_e / c, for the stencil a of an even-odd step
+StencilArgs hop_args(const StencilArgs &a, void *p);
+// what a block's initialisation writes (slots of the context's workspace)
+InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, double *x64, const Red &rd, const CgState &cs);
 // update mode (launch_update's xmode) of iteration c of a group of n
 int xmode_of(int c, int n, bool defer);
 bool xdefer_enabled();
 // The solve options' defaults shared by every entry point: the residual drop
 // between reliable updates (reliable_delta = 0) and the longest run of
 // iterations without one.
-double default_reliable_delta(int inner);
+double default_reliable_delta(int inner, int eo);
 int default_ru_gap(int inner);
 int max_launch_blocks(const Lat &lat, int W);
 // bytes of workspace slot `slot` that prepare_operator and make_launch need
@@ -191,7 +203,8 @@ dp_status timed_launch(dp_ctx *ctx, bool profile, double bytes, F launch, unsign
     ctx->ev_bytes += bytes;
     return DP_OK;
 }
-double stencil_alg_bytes(const Lat &lat, int nc, int W, int prec, bool links);
+// algorithmic bytes of a stencil launch of the given kind on L
+double stencil_alg_bytes(const Launch &L, int prec, bool links, int kind);
 // Iterations until the next host check (2..16): what the slowest lane needs
 // to reach tol and, with ru_ratio > 1 (mixed precision), what the first lane
 // needs to be due a reliable update, both from the slowest lane's decay of
@@ -218,6 +231,7 @@ struct BatchInst {
     const void *links_abi = nullptr;   // caller's complex128 [4][N][nc][nc]
     void *U64 = nullptr, *U8 = nullptr;
     int *nbr = nullptr;
+    int index = 0;                     // position in the caller's arrays
     long long nrhs = 0;
     dp_probe_spec ps{};                // trace mode
     int disp = 0;
@@ -226,6 +240,8 @@ struct BatchInst {
     std::vector<double> tj;            // [2 * nrhs] contractions (trace mode)
     dp_solve_stats st{};
 };
+// Solves (and in trace mode contracts) every instance: those that take the
+// even-odd reduced system in one run of the engine, the others in another.
 dp_status run_batch(dp_ctx *ctx, std::vector<BatchInst> &in, const SolveCfg &cfg, int W, bool trace_mode,
                     hipStream_t s);
 
@@ -237,9 +253,8 @@ struct InitProbe {
     const Red *rd;
     const CgState *cs;
     dp_ctx *ctx;
-    void operator()(void *xlo, double *x64) const {
-        launch_init_probe(*L, prec, g, (double *)ctx->at(kSlotB64), ctx->at(kSlotR), ctx->at(kSlotP), xlo, x64,
-                          prec != kF64, *rd, *cs);
+    void operator()(const OpPrep &op, void *xlo, double *x64) const {
+        launch_init_probe(*L, prec, g, init_args(ctx, op, xlo, x64, *rd, *cs));
     }
     const ProbeGen *probe() const { return &g; }  // b is these probes
     static constexpr bool kLanesNonzero = true;     // a probe has a site of its colour
@@ -253,9 +268,8 @@ struct InitAbi {
     const Red *rd;
     const CgState *cs;
     dp_ctx *ctx;
-    void operator()(void *xlo, double *x64) const {
-        launch_init_abi(*L, prec, babi, rhs0, nvalid, (double *)ctx->at(kSlotB64), ctx->at(kSlotR),
-                        ctx->at(kSlotP), xlo, x64, prec != kF64, *rd, *cs);
+    void operator()(const OpPrep &op, void *xlo, double *x64) const {
+        launch_init_abi(*L, prec, babi, rhs0, nvalid, init_args(ctx, op, xlo, x64, *rd, *cs));
     }
     const ProbeGen *probe() const { return nullptr; }  // b is read back from b64
     static constexpr bool kLanesNonzero = false;       // the caller's b may be zero
@@ -269,8 +283,9 @@ dp_status deflate_rhs(dp_ctx *ctx, const dp_deflation &d, const Launch &L, doubl
 dp_status deflation_trace_part(dp_ctx *ctx, const dp_deflation &d, int p, hipStream_t s, double out[2]);
 dp_status deflation_vectors(dp_ctx *ctx, const dp_deflation &d, double *out, hipStream_t s);
 
-// Probes with the deflation applied: z is generated into b64, projected
-// there, and the CG vectors are initialised from the result; the true
+// Probes with the deflation applied: z is generated (in index order, the
+// deflation vectors' own) into the buffer that A x takes later, projected
+// there, and b64 and the CG vectors are initialised from the result; the true
 // residual then reads b64 (the probes are no longer the right-hand sides).
 struct InitDeflated {
     const Launch *L;
@@ -281,12 +296,12 @@ struct InitDeflated {
     dp_ctx *ctx;
     const dp_deflation *d;
     dp_status *status;  // set when the projection fails
-    void operator()(void *xlo, double *x64) const {
-        double *b64 = (double *)ctx->at(kSlotB64);
-        launch_init_probe(*L, prec, g, b64, ctx->at(kSlotR), ctx->at(kSlotP), xlo, x64, prec != kF64, *rd, *cs);
-        const dp_status e = deflate_rhs(ctx, *d, *L, b64);
+    void operator()(const OpPrep &op, void *xlo, double *x64) const {
+        double *z = (double *)ctx->at(prec != kF64 ? kSlotQ64 : kSlotQ);
+        launch_probe_fill(*L, g, z);
+        const dp_status e = deflate_rhs(ctx, *d, *L, z);
         if (e != DP_OK) *status = e;
-        launch_init_b64(*L, prec, b64, ctx->at(kSlotR), ctx->at(kSlotP), xlo, x64, prec != kF64, *rd, *cs);
+        launch_init_b64(*L, prec, z, init_args(ctx, op, xlo, x64, *rd, *cs));
     }
     const ProbeGen *probe() const { return nullptr; }
     static constexpr bool kLanesNonzero = true;  // (assumed; a zero lane only costs one group)

@@ -114,13 +114,7 @@ struct Bufs {
 
 Launch block_launch(const Lat &lat, int nc, int W, hipStream_t s) {
     Launch L;
-    int logW = 0;
-    while ((1 << logW) < W) ++logW;
-    L.lat = lat;
-    L.nc = nc;
-    L.W = W;
-    L.logW = logW;
-    L.ntiles = (lat.N + (kBlock >> logW) - 1) / (kBlock >> logW);
+    set_geometry(L, lat, nc, W);
     L.nblk = grid_blocks(L.ntiles);
     L.stream = s;
     return L;
@@ -136,7 +130,7 @@ size_t gram_part_bytes(long long n, int WX, int WY) {
 dp_status deflation_build(dp_ctx *ctx, const dp_operator &opd, int nvec, const dp_eig_opts &eo, dp_deflation &D,
                           hipStream_t s) {
     OpPrep op;
-    DP_TRY(prepare_operator(ctx, opd, kF64, op, s));
+    DP_TRY(prepare_operator(ctx, opd, kF64, op, s, false));
     int W = 1;
     while (W < nvec + std::max(4, nvec / 4)) W *= 2;
     if (nvec < 1 || W > 128) {

@@ -58,6 +58,8 @@ struct CgState {
     int rq_direct;       // 1 exactly for BF16 storage, whose stencil sums r^H q and
                          //    r^H p itself; 0: the finishing kernel forms r^H q from
                          //    p^H q and Re q^H p
+    int ru_restart;      // 1: a reliable update restarts every direction (BF16 storage in
+                         //    even-odd order, see kEpiRU)
     int *live;           // multi-instance slots: the slot's active lanes (device),
                          //    written by the control kernel, set by the initialisation;
                          //    iteration kernels skip a slot with none.  Null otherwise.
@@ -72,11 +74,25 @@ struct CgState {
 // iterations beyond delta cost them nothing.)
 enum { kFlagBreakdown = 1, kFlagConverged = 2, kFlagRestart = 4, kFlagHold = 8 };
 
-// Geometry of a lattice on the device.
+// Geometry of a lattice on the device.  eo: the internal site order of a
+// solve's vectors, links and neighbour table is even-odd (all extents even):
+// the sites of even x0+x1+x2+x3 first, then the odd ones, each half in index
+// order (D3 is even, so internal index = parity * N/2 + index / 2).  eo = 0:
+// the internal order is the index order of the ABI.
 struct Lat {
     int D[4];
     int N;
+    int eo = 0;
 };
+
+// Whether the solves of an operator run on the even-odd reduced system
+// S x_e = b_e + H b_o / c, S = c - H H / c (c = m2 + 8, H the hopping term,
+// which connects even and odd sites only when every extent is even).
+inline bool eo_reducible(const int *D, double m2) {
+    for (int d = 0; d < 4; ++d)
+        if (D[d] % 2) return false;
+    return m2 + 8.0 > 0.0;
+}
 
 // How probing vectors are enumerated (device copy of dp_probe_spec fields).
 struct ProbeGen {
@@ -98,10 +114,24 @@ enum Prec { kF64 = 0, kF32 = 1, kBF16 = 2 };
 struct Launch {
     Lat lat;
     int nc, W, logW;
-    int nblk, ntiles;   // grid size and number of site tiles
+    int nblk, ntiles;   // grid size and number of tiles of the ns sites
+    int ns;             // sites the CG vectors cover: N, or the even half of an even-odd order
     hipStream_t stream;
     int smode = -1;     // stencil mode (kernels.hip); -1: the built-in choice for the shape
 };
+
+// geometry fields of a launch of W right-hand sides (grid, stream and mode
+// are the caller's)
+inline void set_geometry(Launch &L, const Lat &lat, int nc, int W) {
+    int logW = 0;
+    while ((1 << logW) < W) ++logW;
+    L.lat = lat;
+    L.nc = nc;
+    L.W = W;
+    L.logW = logW;
+    L.ns = lat.eo ? lat.N / 2 : lat.N;
+    L.ntiles = (L.ns + (kBlock >> logW) - 1) / (kBlock >> logW);
+}
 
 // One job of a multi-instance launch: a block of W right-hand sides of one
 // lattice instance, with its own buffers and CG state.  All slots of a
@@ -110,7 +140,7 @@ struct SlotDesc {
     Launch L;            // geometry; L.nblk workgroups starting at blk0
     int blk0;
     int flags;           // kSlot* phases this slot takes part in
-    double diag;         // m2 + 8
+    double diag;         // c = m2 + 8
     const void *U;       // inner-precision hop links [N][8][nc][nc]
     const void *U64;     // FP64 hop links [N][8][nc][nc] (the true residual)
     const int *nbr;
@@ -135,11 +165,14 @@ struct BatchLaunch {
     const SlotDesc *sd;  // device array [nslots]
     const int *slot_of;  // device array [total workgroups]
     int nslots, nblocks, W, nc, prec, links, mode;
+    int eo;              // every slot's lattice is in even-odd order
     hipStream_t stream;
 };
 void launch_b_init(const BatchLaunch &B, int mixed);
 // xmode: as launch_update's (the slots of mixed precision have cs.xdef)
 void launch_b_iteration(const BatchLaunch &B, int xmode = 0);
+// even-odd order: the odd half of p, H p_e / c, before the stencil
+void launch_b_hop(const BatchLaunch &B, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // the stencil with its three dot products (ev0/ev1: its own start and stop)
 void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_b_update(const BatchLaunch &B, int xmode = 0);  // the finishing kernel, then the vector update
@@ -167,20 +200,43 @@ int grid_blocks(int ntiles);
 void prepare_links(const Lat &lat, int nc, const void *abi, int *nbr, double *u64, int prec, void *u8,
                    double *u8x, hipStream_t s);
 
-void launch_init_probe(const Launch &L, int prec, const ProbeGen &g, double *b64, void *r, void *p,
-                       void *xlo, double *x64, int mixed, const Red &rd, const CgState &cs);
+// What the initialisation of a block writes, and the operator (the even-odd
+// start needs it: r = p = b_e + H b_o / c).
+struct InitArgs {
+    double *b64;
+    void *r, *p, *xlo;
+    double *x64;
+    int mixed;
+    bool links;
+    double diag;
+    const void *U;       // inner-precision hop links
+    const int *nbr;
+    Red rd;
+    CgState cs;
+};
+// b generated from probes (b64 is not written: whoever needs b regenerates it)
+void launch_init_probe(const Launch &L, int prec, const ProbeGen &g, const InitArgs &ia);
 void launch_init_abi(const Launch &L, int prec, const double *babi, long long rhs0, long long nvalid,
-                     double *b64, void *r, void *p, void *xlo, double *x64, int mixed, const Red &rd,
-                     const CgState &cs);
+                     const InitArgs &ia);
 // Arguments of the stencil launch: q = A pin; with cg (a CG iteration) also
 // p^H q and |q|^2 per lane (BF16 storage: r^H q and r^H p too, rin = r), then
 // the finishing kernel that forms alpha, the new |r|^2 and beta.
+// kind kStFull is that; the others belong to the even-odd order, where
+// kStFull covers the even sites (c p_e - H p_o):
+//   kStHop   odd sites of q = diag * (H pin), diag the scale (1 / c)
+//   kStHopB  odd sites of q = diag * (b + H pin), FP64 (b from gen or b64)
+//   kStInit  even sites: q and q2 = diag pin - H pin, |q|^2 per lane, then the
+//            epilogue that sets up the lanes (cg must be set)
+enum StKind { kStFull = 0, kStHop = 1, kStHopB = 2, kStInit = 3 };
 struct StencilArgs {
+    int kind = kStFull;
     bool links = false;
     double diag = 0;
     const void *pin = nullptr;
     const void *rin = nullptr;
-    void *q = nullptr;
+    void *q = nullptr, *q2 = nullptr;
+    const double *b64 = nullptr;
+    const ProbeGen *gen = nullptr;
     const void *U = nullptr;     // hop links [N][8][nc][nc] (gather_links)
     const int *nbr = nullptr;
     int cg = 0;
@@ -225,11 +281,12 @@ void launch_force(const Launch &L, const double *x64, const double *l64, const i
 // control word
 void launch_ctrl(const Red &rd, const CgState &cs, int W, hipStream_t s);
 
-// Deflation (dense pieces over FP64 blocks [n rows][width], internal layout)
-// r = p = b read from b64 in place, xlo = 0, |b|^2 (the init of probes that
-// were modified in b64)
-void launch_init_b64(const Launch &L, int prec, double *b64, void *r, void *p, void *xlo, double *x64, int mixed,
-                     const Red &rd, const CgState &cs);
+// Deflation (dense pieces over FP64 blocks [n rows][width], index order)
+// the probes of g, FP64, index order
+void launch_probe_fill(const Launch &L, const ProbeGen &g, double *out);
+// the initialisation from src (FP64 [site][nc][W], index order; it may be
+// ia.b64 itself when the internal order is the index order)
+void launch_init_b64(const Launch &L, int prec, const double *src, const InitArgs &ia);
 // cs.tj[j] = sum_x sum_b conj(u_j(x,b)) w_j(x + p e0, b)
 void launch_dot_shift(const Launch &L, const double *u, const double *w, int p, const Red &rd, const CgState &cs);
 // cs.true_rr[j] = |u_j - theta_j w_j|^2 (theta: device double[W])

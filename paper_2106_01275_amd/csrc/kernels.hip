@@ -174,20 +174,26 @@ __device__ __forceinline__ void tile_range(const Blk &bk, int ntiles, int &t0, i
 // few x2-rows instead, so that the x1-neighbour planes of a window are
 // those just read, cut the stencil's fetched bytes at 32^4 by a tenth but
 // not its time, which is set by load latency rather than bytes.)
+//
+// In even-odd order a launch covers one half (half 0 or 1), whose index order
+// is that of the lattice with D3 / 2 sites along x3: the same walk over
+// N / 2 sites and V3 / 2 sites per slice, from site off = half * N / 2.
 struct SiteWalk {
     int items;      // work items of this XCD
     int n0, x0_lo;  // x0-slices of the slab (n0 == 0: plain range)
     int base;       // first site (plain range)
     int V3;         // sites per x0-slice
+    int off;        // first site of the half
     int first, stride;  // first tile of this workgroup and tile stride
     int n0s;            // log2 n0 if n0 is a power of two, else -1
 };
 
-__device__ __forceinline__ SiteWalk site_walk(const Launch &L, const Blk &bk) {
+__device__ __forceinline__ SiteWalk site_walk(const Launch &L, const Blk &bk, int half = 0) {
     const Lat &lat = L.lat;
     SiteWalk w;
-    const int nb = bk.nb, b = bk.b;
-    w.V3 = lat.D[1] * lat.D[2] * lat.D[3];
+    const int nb = bk.nb, b = bk.b, N = L.ns;
+    w.V3 = (lat.D[1] * lat.D[2] * lat.D[3]) >> lat.eo;
+    w.off = half * N;
     if (nb >= 8 && nb % 8 == 0) {
         const int x = b % 8;
         w.first = b / 8;
@@ -200,8 +206,8 @@ __device__ __forceinline__ SiteWalk site_walk(const Launch &L, const Blk &bk) {
         } else {
             w.n0 = 0;
             w.x0_lo = 0;
-            w.base = (int)(((long long)x * lat.N) / 8);
-            w.items = (int)(((long long)(x + 1) * lat.N) / 8) - w.base;
+            w.base = (int)(((long long)x * N) / 8);
+            w.items = (int)(((long long)(x + 1) * N) / 8) - w.base;
         }
     } else {
         w.first = b;
@@ -209,7 +215,7 @@ __device__ __forceinline__ SiteWalk site_walk(const Launch &L, const Blk &bk) {
         w.n0 = 0;
         w.x0_lo = 0;
         w.base = 0;
-        w.items = lat.N;
+        w.items = N;
     }
     w.n0s = w.n0 > 0 && (w.n0 & (w.n0 - 1)) == 0 ? __builtin_ctz(w.n0) : -1;
     return w;
@@ -218,9 +224,32 @@ __device__ __forceinline__ SiteWalk site_walk(const Launch &L, const Blk &bk) {
 // (a shift and a mask where n0 is a power of two: the walk is taken for
 // every staged link element; 32^4, FP32, W = 32: 1.4% off the stencil)
 __device__ __forceinline__ int walk_site(const SiteWalk &w, int item) {
-    if (w.n0 == 0) return w.base + item;
-    if (w.n0s >= 0) return (w.x0_lo + (item & (w.n0 - 1))) * w.V3 + (item >> w.n0s);
-    return (w.x0_lo + item % w.n0) * w.V3 + item / w.n0;
+    if (w.n0 == 0) return w.off + w.base + item;
+    if (w.n0s >= 0) return w.off + (w.x0_lo + (item & (w.n0 - 1))) * w.V3 + (item >> w.n0s);
+    return w.off + (w.x0_lo + item % w.n0) * w.V3 + item / w.n0;
+}
+
+// ABI index of internal site s, and internal site of ABI index x (see Lat).
+// The extents of an even-odd order are even, so the parity of x0 + x1 + x2 is
+// that of the three quotients of the row number.
+__device__ __forceinline__ int row_parity(const Lat &L, int row) {
+    const int r1 = row / L.D[2];
+    return (row + r1 + r1 / L.D[1]) & 1;
+}
+__device__ __forceinline__ int lex_of(const Lat &L, int s) {
+    if (!L.eo) return s;
+    const int nh = L.N >> 1, par = s >= nh, x = 2 * (s - par * nh);
+    return x + ((row_parity(L, x / L.D[3]) + par) & 1);
+}
+__device__ __forceinline__ int site_of(const Lat &L, int x) {
+    if (!L.eo) return x;
+    return ((row_parity(L, x / L.D[3]) + x) & 1) * (L.N >> 1) + (x >> 1);
+}
+
+// tiles of the whole lattice (L.ntiles: of the sites a launch iterates on)
+__device__ __forceinline__ int full_tiles(const Launch &L) {
+    const int spt = kBlock >> L.logW;
+    return (L.lat.N + spt - 1) / spt;
 }
 
 __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
@@ -277,7 +306,8 @@ __device__ __forceinline__ ProbeLane probe_lane(const ProbeGen &g, int nc, long 
     return pl;
 }
 
-// value of that lane's probe at (site, colour b); 0 outside its support
+// value of that lane's probe at (site of ABI index `site`, colour b); 0
+// outside its support
 __device__ __forceinline__ void probe_at(const ProbeGen &g, unsigned long long seedmix, const Lat &L, int nc,
                                          const ProbeLane &pl, int site, int b, double &re, double &im) {
     re = 0.0;
@@ -401,7 +431,7 @@ __device__ __forceinline__ void lane_total_wave(const double *src, int nblk, dou
 // Epilogues of the finishing kernels.  Those marked (part2, NV = 2) total
 // the |r|^2 and Re q^H p partials of the last vector update, initialisation
 // or reliable update; kEpiTj and kEpiStatsP1 total rd.part1.
-enum Epi { kEpiInit, kEpiCheck, kEpiRU, kEpiStats, kEpiStatsP1, kEpiTj };
+enum Epi { kEpiInit, kEpiCheck, kEpiRU, kEpiStats, kEpiStatsP1, kEpiTj, kEpiInitEo };
 
 // One workgroup per lane: total of the lane's partials (fixed order), then
 // the scalar epilogue of that lane (thread 0; only this workgroup reads or
@@ -412,10 +442,41 @@ enum Epi { kEpiInit, kEpiCheck, kEpiRU, kEpiStats, kEpiStatsP1, kEpiTj };
 //   kEpiRU (part2)     the FP64 true residual of a reliable update
 //   kEpiStats (part2), kEpiStatsP1 (part1)  a norm into true_rr only
 //   kEpiTj (part1, NV = 2)  a complex dot product into tj
+//   kEpiInitEo (part1, NV = 4, and part2)  even-odd order: |b|^2 of the whole
+//                      lattice is in part2, |r|^2 of the reduced system's first
+//                      residual in part1 (the |q|^2 entry); part2 then gets
+//                      that |r|^2, as if an update had written r
 template <int NV, int EPI>
 __device__ __forceinline__ void k_finish_body(int lane, const Red &rd, const CgState &cs) {
     __shared__ double sm[NV * kBlock / 64];
     const int tid = threadIdx.x;
+    if constexpr (EPI == kEpiInitEo) {
+        __shared__ double sm2[2 * kBlock / 64], rr_all;
+        double t4[4], t2[2];
+        lane_total<4>(rd.part1 + (size_t)lane * rd.nblk * 4, rd.nblk, t4, sm);
+        lane_total<2>(rd.part2 + (size_t)lane * rd.nblk * 2, rd.nblk, t2, sm2);
+        if (tid == 0) {
+            const double bb = t2[0], rr = t4[2];
+            rr_all = rr;
+            cs.bb[lane] = bb;
+            cs.rr[lane] = rr;
+            cs.qp[lane] = 0.0;
+            cs.rr_ref[lane] = rr;
+            cs.true_rr[lane] = rr;
+            cs.alpha[lane] = 0.0;
+            cs.beta[lane] = 0.0;
+            cs.iters[lane] = 0;
+            cs.active[lane] = bb > 0.0;
+            cs.flags[lane] = bb > 0.0 ? 0 : kFlagConverged;
+            if (cs.live && lane == 0) *cs.live = 1;  // iterate until a control kernel counts the lanes
+        }
+        __syncthreads();  // (every partial has been read, too)
+        for (int b = tid; b < rd.nblk; b += kBlock) {
+            rd.part2[((size_t)lane * rd.nblk + b) * 2] = b == 0 ? rr_all : 0.0;
+            rd.part2[((size_t)lane * rd.nblk + b) * 2 + 1] = 0.0;
+        }
+        return;
+    }
     constexpr bool kPart2 = EPI == kEpiInit || EPI == kEpiCheck || EPI == kEpiRU || EPI == kEpiStats;
     static_assert(!kPart2 || NV == 2, "part2 holds two values per lane and workgroup");
     const double *src = (kPart2 ? rd.part2 : rd.part1) + (size_t)lane * rd.nblk * NV;
@@ -463,8 +524,12 @@ __device__ __forceinline__ void k_finish_body(int lane, const Red &rd, const CgS
             cs.rr[j] = t;
             cs.qp[j] = tot[NV - 1];
             cs.rr_ref[j] = t;
-            // a restarted direction is the residual itself (no previous one)
-            if (st_flags & kFlagRestart) cs.beta[j] = 0.0;
+            // a restarted direction is the residual itself (no previous one).
+            // BF16 storage keeps its directions in index order; in even-odd
+            // order, where a drop takes half as many steps, the kept ones cost
+            // more than they bring (8^4 x 3, 1e-8, an FP64-emulated run: 29.8
+            // steps kept, 26.1 restarted at drop 0.002; 28.7 and 21.3 at 0.01)
+            if ((st_flags & kFlagRestart) || cs.ru_restart) cs.beta[j] = 0.0;
             if (t <= cs.tol2 * st_bb) {
                 cs.active[j] = 0;
                 flags |= kFlagConverged;
@@ -671,7 +736,7 @@ __global__ void k_prepare(Lat L, int nc, const double2 *__restrict__ abi, int *_
     if (e >= 8LL * L.N * ne) return;
     const int ab = (int)(e % ne);
     const long long t = e / ne;
-    const int dir = (int)(t % 8), site = (int)(t / 8), mu = dir & 3;
+    const int dir = (int)(t % 8), s = (int)(t / 8), site = lex_of(L, s), mu = dir & 3;
     int r = site, x = 0, stride = 1;
     for (int d = 3; d >= mu; --d) {
         if (d == mu) x = r % L.D[d];
@@ -680,22 +745,25 @@ __global__ void k_prepare(Lat L, int nc, const double2 *__restrict__ abi, int *_
     }
     const int y = dir < 4 ? site + (x + 1 == L.D[mu] ? -(L.D[mu] - 1) : 1) * stride
                           : site + (x == 0 ? L.D[mu] - 1 : -1) * stride;
-    if (ab == 0) stg(nbr + (size_t)site * 8 + dir, y);
+    if (ab == 0) stg(nbr + (size_t)s * 8 + dir, site_of(L, y));
     if (!abi) return;
     const double2 v = ldg(abi + ((size_t)mu * L.N + (dir < 4 ? site : y)) * nc * nc + ab);
     if (u8) St<LS>::st(u8, e, (typename St<LS>::R)v.x, (typename St<LS>::R)v.y);
     if (u8x) stg(u8x + e, v);
-    if (u64 && dir < 4) stg(u64 + ((size_t)site * 4 + mu) * nc * nc + ab, v);
+    if (u64 && dir < 4) stg(u64 + ((size_t)s * 4 + mu) * nc * nc + ab, v);
 }
 
-// Initialise one block of W right-hand sides: b (FP64), r = p = b (storage
-// precision), x = 0, and |b|^2 per lane; the finishing workgroup sets up
-// the CG scalars.  SRC 0: probes generated from ProbeGen; 1: from ABI b.
+// Initialise one block of W right-hand sides: r = p = b (storage precision),
+// x = 0, and |b|^2 per lane; the finishing workgroup sets up the CG scalars.
+// SRC 0: probes generated from ProbeGen (whoever needs b again regenerates
+// it); 1: from ABI b; 2: from an FP64 block src in index order; these two
+// also write b (FP64).  In even-odd order the odd half of p is -b / c, from
+// which the stencil that follows (kStInit) forms r = p = b_e + H b_o / c.
 template <typename S, int SRC>
-__device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g, const double2 *__restrict__ babi,
-                                                 long long rhs0, long long nvalid, double2 *__restrict__ b64,
-                                                 S *__restrict__ r, S *__restrict__ p, S *__restrict__ xlo,
-                                                 double2 *__restrict__ x64, int mixed, Red rd, CgState cs) {
+__device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g, const double2 *babi, long long rhs0,
+                                            long long nvalid, double2 *b64, S *__restrict__ r, S *__restrict__ p,
+                                            S *__restrict__ xlo, double2 *__restrict__ x64, int mixed, double hop_scale,
+                                            Red rd) {
     __shared__ double sm[2 * kBlock];
     const int tid = threadIdx.x, W = L.W, logW = L.logW;
     const int j = tid & (W - 1);
@@ -704,43 +772,61 @@ __device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g,
     const ProbeLane pl = SRC == 0 ? probe_lane(g, nc, g.rhs0 + j) : ProbeLane{};
     double acc[2] = {0.0, 0.0};  // |b|^2, and 0 for q^H p (no previous direction)
     int t0, t1;
-    tile_range(bk, L.ntiles, t0, t1);
+    tile_range(bk, full_tiles(L), t0, t1);
     for (int t = t0; t < t1; ++t) {
         const int site = t * (kBlock >> logW) + (tid >> logW);
         if (site >= L.lat.N) continue;
+        const int x = lex_of(L.lat, site);
+        const bool odd = site >= L.ns;  // (even-odd order only)
+        const double f = odd ? -hop_scale : 1.0;
         for (int a = 0; a < nc; ++a) {
             double re = 0.0, im = 0.0;
             const size_t i = ((size_t)(site * nc + a) << logW) + j;
             if (SRC == 0) {
-                if (j < g.nvalid) probe_at(g, seedmix, L.lat, nc, pl, site, a, re, im);
+                if (j < g.nvalid) probe_at(g, seedmix, L.lat, nc, pl, x, a, re, im);
             } else if (SRC == 1) {
                 if (j < nvalid) {
-                    const double2 v = babi[((size_t)(rhs0 + j) * L.lat.N + site) * nc + a];
+                    const double2 v = babi[((size_t)(rhs0 + j) * L.lat.N + x) * nc + a];
                     re = v.x;
                     im = v.y;
                 }
             } else {
-                const double2 v = b64[i];  // b already in place
+                const double2 v = babi[((size_t)(x * nc + a) << logW) + j];
                 re = v.x;
                 im = v.y;
             }
-            if (SRC != 2) b64[i] = make_double2(re, im);
-            St<S>::st(r, i, (typename St<S>::R)re, (typename St<S>::R)im);
-            St<S>::st(p, i, (typename St<S>::R)re, (typename St<S>::R)im);
-            St<S>::st(xlo, i, 0, 0);
-            if (mixed) x64[i] = make_double2(0.0, 0.0);
+            if (SRC != 0) b64[i] = make_double2(re, im);
+            St<S>::st(p, i, (typename St<S>::R)(f * re), (typename St<S>::R)(f * im));
             acc[0] += re * re + im * im;
+            if (mixed) x64[i] = make_double2(0.0, 0.0);
+            if (odd) continue;
+            if (!L.lat.eo) St<S>::st(r, i, (typename St<S>::R)re, (typename St<S>::R)im);
+            St<S>::st(xlo, i, 0, 0);
         }
     }
     block_partials_to<2>(bk, acc, W, logW, rd.part2, rd.nblk, sm);
 }
 
 template <typename S, int SRC>
-__global__ __launch_bounds__(kBlock) void k_init(Launch L, ProbeGen g, const double2 *__restrict__ babi,
-                                                 long long rhs0, long long nvalid, double2 *__restrict__ b64,
-                                                 S *__restrict__ r, S *__restrict__ p, S *__restrict__ xlo,
-                                                 double2 *__restrict__ x64, int mixed, Red rd, CgState cs) {
-    k_init_body<S, SRC>(own_blk(), L, g, babi, rhs0, nvalid, b64, r, p, xlo, x64, mixed, rd, cs);
+__global__ __launch_bounds__(kBlock) void k_init(Launch L, ProbeGen g, const double2 *babi, long long rhs0,
+                                                 long long nvalid, double2 *b64, S *__restrict__ r, S *__restrict__ p,
+                                                 S *__restrict__ xlo, double2 *__restrict__ x64, int mixed,
+                                                 double hop_scale, Red rd) {
+    k_init_body<S, SRC>(own_blk(), L, g, babi, rhs0, nvalid, b64, r, p, xlo, x64, mixed, hop_scale, rd);
+}
+
+// the probes of g in FP64, index order [site][nc][W]
+__global__ __launch_bounds__(kBlock) void k_probe_fill(Launch L, ProbeGen g, double2 *__restrict__ out) {
+    const int j = threadIdx.x & (L.W - 1);
+    const unsigned long long seedmix = mix64(g.seed);
+    const ProbeLane pl = probe_lane(g, L.nc, g.rhs0 + j);
+    const int spt = kBlock >> L.logW;
+    for (int x = (int)blockIdx.x * spt + (int)(threadIdx.x >> L.logW); x < L.lat.N; x += (int)gridDim.x * spt)
+        for (int a = 0; a < L.nc; ++a) {
+            double re = 0.0, im = 0.0;
+            if (j < g.nvalid) probe_at(g, seedmix, L.lat, L.nc, pl, x, a, re, im);
+            stg(out + ((size_t)(x * L.nc + a) << L.logW) + j, make_double2(re, im));
+        }
 }
 
 // q = A p for one block of right-hand sides; with CG, also p^H q per lane
@@ -1016,11 +1102,13 @@ __device__ __forceinline__ void dma_wait_barrier() {
 // hop is two packed bf16 dot products accumulated in FP32 (the loaded words
 // are used as they are, no unpacking); the modes are those of the generic
 // body below.
-template <int NC, bool LINKS, int MODE>
-__device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, float diag, const bf16x2 *__restrict__ pin,
-                                                    const bf16x2 *__restrict__ rin, bf16x2 *__restrict__ q,
-                                                    const bf16x2 *__restrict__ U, const int *__restrict__ nbr, int cg,
-                                                    Red rd) {
+template <int NC, bool LINKS, int MODE, int KIND>
+__device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, float diag, const bf16x2 *pin,
+                                                    const bf16x2 *__restrict__ rin, bf16x2 *q,
+                                                    bf16x2 *q2, const bf16x2 *__restrict__ U,
+                                                    const int *__restrict__ nbr, int cg, Red rd) {
+    constexpr bool HOP = KIND == kStHop;
+    constexpr bool INIT = KIND == kStInit;  // no residual yet: only |q|^2 is summed
     constexpr bool STAGE = MODE == 1 && LINKS;
     constexpr int kMaxSites = kBlock / 16;
     // STAGE: two tile buffers, each [site][8 NC^2] link words then [site][8]
@@ -1037,9 +1125,9 @@ __device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, flo
     const int sl = MODE == 2 ? __builtin_amdgcn_readfirstlane(tid >> logW) : tid >> logW;
     const int sites_per_tile = kBlock >> logW;
     const Rows<const bf16x2, NC> P(pin, logW), Rr(rin ? rin : pin, logW);
-    const Rows<bf16x2, NC> Q(q, logW);
+    const Rows<bf16x2, NC> Q(q, logW), Q2(INIT ? q2 : q, logW);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const SiteWalk wk = site_walk(L, bk);
+    const SiteWalk wk = site_walk(L, bk, HOP ? 1 : 0);
     // STAGE: the copy of the next tile is in flight while this tile is worked
     // on, so that a tile waits for one round trip to memory rather than two
     // (at most 16 sites of 8 NC^2 + 8 words: two pieces per thread)
@@ -1058,6 +1146,7 @@ __device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, flo
             bf16x2 o;
             o.v = qw[a];
             stg(at32(Q.b[a], qi), o);
+            if (INIT) stg(at32(Q2.b[a], qi), o);
         }
         qpend = false;
     };
@@ -1085,13 +1174,13 @@ __device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, flo
             y[dir + 1] = STAGE ? tnb[sl * 8 + dir] : (MODE == 1 ? snb[sl * 8 + dir] : ldg(nbr + site * 8 + dir));
         uint32_t v[9][NC];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
+        for (int k = HOP ? 1 : 0; k < 9; ++k) {
             const unsigned i = vidx(y[k], NC, 0, logW, j);
 #pragma unroll
             for (int b = 0; b < NC; ++b) v[k][b] = ldg(at32(P.b[b], i)).v;
         }
         uint32_t rv[NC];  // the residual at the site (CG: r^H q and r^H p summed here)
-        if (cg) {
+        if (cg && !INIT) {
             const unsigned i = vidx(site, NC, 0, logW, j);
 #pragma unroll
             for (int b = 0; b < NC; ++b) rv[b] = ldg(at32(Rr.b[b], i)).v;
@@ -1123,12 +1212,18 @@ __device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, flo
         float pqs = 0, rqs = 0, qqs = 0, rps = 0;
 #pragma unroll
         for (int a = 0; a < NC; ++a) {
+            bf16x2 o;
+            if (HOP) {
+                qw[a] = pack_bf16(diag * hr[a], diag * hi[a]);
+                continue;
+            }
             const float pr = __uint_as_float(v[0][a] << 16), pi = __uint_as_float(v[0][a] & 0xffff0000u);
             const float ar = fmaf(diag, pr, -hr[a]), ai = fmaf(diag, pi, -hi[a]);
-            bf16x2 o;
             o.v = pack_bf16(ar, ai);
             qw[a] = o.v;
-            if (cg) {
+            if (INIT) {
+                qqs = dot2_bf16(o.v, o.v, qqs);
+            } else if (cg) {
                 // the real parts of the dot products of the stored words (the
                 // rounded q): one packed dot each, the products exact in FP32
                 pqs = dot2_bf16(v[0][a], o.v, pqs);
@@ -1145,7 +1240,7 @@ __device__ __forceinline__ void k_stencil_bf16_body(const Blk &bk, Launch L, flo
         acc[3] += (double)rps;
     }
     store_q();
-    if (!cg) return;
+    if (HOP || !cg) return;
     if (kReuse) __syncthreads();  // every wavefront is done with the link tile
     block_partials<4>(bk, acc, W, logW, rd, sm);
 }
@@ -1176,14 +1271,28 @@ __device__ __forceinline__ void ld_hop(const LS *__restrict__ U8, int site, int 
 // with two or four neighbouring sites per thread (k_stencil_group_body).  In every mode the vector loads of the site and its eight
 // neighbours are issued before any arithmetic, so they are in flight
 // together.
-template <typename S, typename LS, int NC, bool LINKS, int MODE>
-__device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename St<S>::R diag, const S *__restrict__ pin,
-                                               const S *__restrict__ rin, S *__restrict__ q, const LS *__restrict__ U,
-                                               const int *__restrict__ nbr, int cg, Red rd) {
+// KIND (StKind): in even-odd order a launch covers one half, the even sites
+// with the formula above or the odd sites with the scaled hop sum alone.  (p
+// and q are one vector in a hop launch, which reads its even half and writes
+// its odd one; in kStInit each even site is read by the thread that
+// overwrites it.)
+struct HopB {  // kStHopB: where b comes from
+    const double2 *b64;
+    ProbeGen g;
+    int gen;
+};
+
+template <typename S, typename LS, int NC, bool LINKS, int MODE, int KIND>
+__device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename St<S>::R diag, const S *pin,
+                                               const S *__restrict__ rin, S *q, S *q2, const LS *__restrict__ U,
+                                               const int *__restrict__ nbr, int cg, Red rd, const HopB &hb) {
     if constexpr (std::is_same<S, bf16x2>::value) {
-        k_stencil_bf16_body<NC, LINKS, MODE>(bk, L, diag, pin, rin, q, U, nbr, cg, rd);
+        k_stencil_bf16_body<NC, LINKS, MODE, KIND>(bk, L, diag, pin, rin, q, q2, U, nbr, cg, rd);
         return;
     }
+    constexpr bool HOP = KIND == kStHop || KIND == kStHopB;
+    constexpr bool HOPB = KIND == kStHopB;
+    constexpr bool INIT = KIND == kStInit;
     using R = typename St<S>::R;
     constexpr bool STAGE = MODE == 1 && LINKS;
     constexpr int kMaxSites = kBlock / 16;
@@ -1199,9 +1308,11 @@ __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename
     const int sites_per_tile = kBlock >> logW;
     const WaveItems wi = wave_items(logW, 1);
     const Rows<const S, NC> P(pin, logW);
-    const Rows<S, NC> Q(q, logW);
+    const Rows<S, NC> Q(q, logW), Q2(INIT ? q2 : q, logW);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const SiteWalk wk = site_walk(L, bk);
+    const SiteWalk wk = site_walk(L, bk, HOP ? 1 : 0);
+    const unsigned long long seedmix = HOPB && hb.gen ? mix64(hb.g.seed) : 0ull;
+    const ProbeLane pl = HOPB && hb.gen ? probe_lane(hb.g, NC, hb.g.rhs0 + j) : ProbeLane{};
     for (int t = wk.first; t * sites_per_tile < wk.items; t += wk.stride) {
         const int item0 = t * sites_per_tile;
         if (MODE == 1) stage_hops_wave<LS, R, NC, LINKS>(su, snb, wk, item0, wi, U, nbr);
@@ -1213,12 +1324,25 @@ __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename
         for (int dir = 0; dir < 8; ++dir) y[dir + 1] = MODE == 1 ? snb[wi.slot * 8 + dir] : ldg(nbr + site * 8 + dir);
         R vr[9][NC], vi[9][NC];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) ld_rows<S, NC>(P, y[k], logW, j, vr[k], vi[k]);
+        for (int k = HOP ? 1 : 0; k < 9; ++k) ld_rows<S, NC>(P, y[k], logW, j, vr[k], vi[k]);
         R ar[NC], ai[NC];
 #pragma unroll
         for (int a = 0; a < NC; ++a) {
-            ar[a] = diag * vr[0][a];
-            ai[a] = diag * vi[0][a];
+            ar[a] = HOP ? (R)0 : diag * vr[0][a];
+            ai[a] = HOP ? (R)0 : diag * vi[0][a];
+        }
+        if constexpr (HOPB) {
+            const int x = hb.gen ? lex_of(L.lat, site) : 0;
+#pragma unroll
+            for (int a = 0; a < NC; ++a) {
+                double br = 0.0, bi = 0.0;
+                if (!hb.gen)
+                    St<double2>::ld(hb.b64, vidx(site, NC, a, logW, j), br, bi);
+                else if (j < hb.g.nvalid)
+                    probe_at(hb.g, seedmix, L.lat, NC, pl, x, a, br, bi);
+                ar[a] = -br;
+                ai[a] = -bi;
+            }
         }
 #pragma unroll
         for (int dir = 0; dir < 8; ++dir) {
@@ -1245,16 +1369,21 @@ __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename
         R pqs = 0, qqs = 0;
 #pragma unroll
         for (int a = 0; a < NC; ++a) {
+            if (HOP) {  // the hops were subtracted
+                st_rows<S, NC>(Q, site, logW, j, a, -diag * ar[a], -diag * ai[a]);
+                continue;
+            }
             st_rows<S, NC>(Q, site, logW, j, a, ar[a], ai[a]);
+            if (INIT) st_rows<S, NC>(Q2, site, logW, j, a, ar[a], ai[a]);
             if (cg) {
-                pqs = fmaR(vr[0][a], ar[a], fmaR(vi[0][a], ai[a], pqs));
+                if (!INIT) pqs = fmaR(vr[0][a], ar[a], fmaR(vi[0][a], ai[a], pqs));
                 qqs = fmaR(ar[a], ar[a], fmaR(ai[a], ai[a], qqs));
             }
         }
         acc[0] += (double)pqs;
         acc[2] += (double)qqs;
     }
-    if (!cg) return;
+    if (HOP || !cg) return;
     if (kReuse) __syncthreads();  // every wavefront is done with the link tile
     block_partials<4>(bk, acc, W, logW, rd, sm);
 }
@@ -1400,19 +1529,21 @@ __device__ __forceinline__ void k_stencil_group_body(const Blk &bk, Launch L, ty
 // of hop h's product U v (rows a >= nc idle), the eight hops of a row are
 // summed by a butterfly over lanes 4, 8 and 16 apart, and hop 0's threads
 // write q.  Eight sites per workgroup pass.
-template <typename S, typename LS, int NC, bool LINKS>
-__device__ __forceinline__ void k_stencil_split_body(const Blk &bk, Launch L, typename St<S>::R diag,
-                                                     const S *__restrict__ pin, const S *__restrict__ rin,
-                                                     S *__restrict__ q, const LS *__restrict__ U,
-                                                     const int *__restrict__ nbr, int cg, Red rd) {
+template <typename S, typename LS, int NC, bool LINKS, int KIND>
+__device__ __forceinline__ void k_stencil_split_body(const Blk &bk, Launch L, typename St<S>::R diag, const S *pin,
+                                                     const S *__restrict__ rin, S *q, S *q2, const LS *__restrict__ U,
+                                                     const int *__restrict__ nbr, int cg, Red rd, const HopB &hb) {
+    constexpr bool HOP = KIND == kStHop || KIND == kStHopB;
+    constexpr bool HOPB = KIND == kStHopB;
+    constexpr bool INIT = KIND == kStInit;
     using R = typename St<S>::R;
     __shared__ double sm[4 * kBlock];
     const int tid = threadIdx.x, lane = tid & 31, h = lane >> 2, a = lane & 3;
-    const int ngroups = (L.lat.N + 7) / 8;
+    const int ngroups = (L.ns + 7) / 8;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int g = bk.b; g < ngroups; g += bk.nb) {
-        const int site = g * 8 + (tid >> 5);
-        const bool live = site < L.lat.N;
+        const int item = g * 8 + (tid >> 5), site = item + (HOP ? L.ns : 0);
+        const bool live = item < L.ns;
         R sr = 0, si = 0;
         if (live && a < NC) {
             const int y = nbr[site * 8 + h];
@@ -1439,25 +1570,38 @@ __device__ __forceinline__ void k_stencil_split_body(const Blk &bk, Launch L, ty
             si += __shfl_xor(si, off, 64);
         }
         if (live && h == 0 && a < NC) {
+            if constexpr (HOPB) {
+                double br = 0.0, bi = 0.0;
+                if (!hb.gen)
+                    St<double2>::ld(hb.b64, (size_t)site * NC + a, br, bi);
+                else if (0 < hb.g.nvalid)
+                    probe_value(hb.g, mix64(hb.g.seed), L.lat, NC, hb.g.rhs0, lex_of(L.lat, site), a, br, bi);
+                sr += br;
+                si += bi;
+            }
+            if (HOP) {
+                St<S>::st(q, (size_t)site * NC + a, diag * sr, diag * si);
+                continue;
+            }
             R pr, pi;
             St<S>::ld(pin, (size_t)site * NC + a, pr, pi);
             R qr = fmaR(diag, pr, -sr), qi = fmaR(diag, pi, -si);
             St<S>::st(q, (size_t)site * NC + a, qr, qi);
+            if (INIT) St<S>::st(q2, (size_t)site * NC + a, qr, qi);
             if (cg) {
-                acc[0] += (double)fmaR(pr, qr, pi * qi);
+                if (!INIT) acc[0] += (double)fmaR(pr, qr, pi * qi);
                 acc[2] += (double)fmaR(qr, qr, qi * qi);
             }
         }
     }
-    if (!cg) return;
+    if (HOP || !cg) return;
     block_partials<4>(bk, acc, 1, 0, rd, sm);
 }
 
-template <typename S, typename LS, int NC, bool LINKS, int MODE>
-__global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R diag, const S *__restrict__ pin,
-                                                    const S *__restrict__ rin, S *__restrict__ q,
-                                                    const LS *__restrict__ U, const int *__restrict__ nbr, int cg,
-                                                    Red rd) {
+template <typename S, typename LS, int NC, bool LINKS, int MODE, int KIND>
+__global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R diag, const S *pin,
+                                                    const S *__restrict__ rin, S *q, S *q2, const LS *__restrict__ U,
+                                                    const int *__restrict__ nbr, int cg, Red rd, HopB hb) {
     // the bodies are inlined once with cg = 1 and once with cg = 0: with a
     // run-time flag the compiler keeps the registers of both paths live
     // (the BF16 body went from 69 to 187 registers)
@@ -1468,14 +1612,20 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R 
         else if constexpr (MODE == 6)
             k_stencil_group_body<S, LS, NC, LINKS, 4, true>(own_blk(), L, diag, pin, rin, q, U, nbr, cg_, rd);
         else if constexpr (MODE == 5)
-            k_stencil_split_body<S, LS, NC, LINKS>(own_blk(), L, diag, pin, rin, q, U, nbr, cg_, rd);
+            k_stencil_split_body<S, LS, NC, LINKS, KIND>(own_blk(), L, diag, pin, rin, q, q2, U, nbr, cg_, rd, hb);
         else
-            k_stencil_body<S, LS, NC, LINKS, MODE>(own_blk(), L, diag, pin, rin, q, U, nbr, cg_, rd);
+            k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(own_blk(), L, diag, pin, rin, q, q2, U, nbr, cg_, rd, hb);
     };
-    if (cg)
-        body(1);
-    else
+    if constexpr (KIND == kStHop || KIND == kStHopB) {
         body(0);
+    } else if constexpr (KIND == kStInit) {
+        body(1);
+    } else {
+        if (cg)
+            body(1);
+        else
+            body(0);
+    }
 }
 
 // The vector update of a CG iteration (second kernel; alpha and beta from
@@ -1527,7 +1677,7 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
     // element e = ((site * nc + a) << logW) + j: lane j is tid & (W-1) for
     // every e = e0 + tid + k * kBlock since kBlock is a multiple of W
     const size_t e0 = (size_t)t0 * sites_per_tile * L.nc * W;
-    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.lat.N) * L.nc * W;
+    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.ns) * L.nc * W;
     R part = 0, partq = 0;
     int cnt = 0;
     size_t e = e0 + tid;
@@ -1621,7 +1771,7 @@ __device__ __forceinline__ void k_fold_body(const Blk &bk, Launch L, double2 *__
     int t0, t1;
     tile_range(bk, L.ntiles, t0, t1);
     const size_t e0 = (size_t)t0 * sites_per_tile * L.nc * W;
-    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.lat.N) * L.nc * W;
+    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.ns) * L.nc * W;
     for (size_t e = e0 + tid; e < e1; e += kBlock) {
         R xr, xi;
         St<S>::ld(xlo, e, xr, xi);
@@ -1672,7 +1822,7 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
     const SiteWalk wk = site_walk(L, bk);
     const unsigned long long seedmix = gen ? mix64(g.seed) : 0ull;
     const ProbeLane pl = gen ? probe_lane(g, NC, g.rhs0 + j) : ProbeLane{};
-    const bool restart = ru && (cs.flags[j] & kFlagRestart);
+    const bool restart = ru && ((cs.flags[j] & kFlagRestart) || cs.ru_restart);
     if (STAGE && wk.first * sites_per_tile < wk.items)
         dma_tile<double2, NC>(sbuf, wk, wk.first * sites_per_tile, sites_per_tile, U, nbr);
     int cur = 0;
@@ -1703,10 +1853,11 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
         for (int k = 0; k < 5; ++k) ld_site<double2, NC>(x64, y[k], logW, j, vr[k], vi[k]);
         if (gen) {
             // probes are regenerated instead of read back (exact values)
+            const int x = lex_of(L.lat, site);
 #pragma unroll
             for (int a = 0; a < NC; ++a) {
                 br[a] = bi[a] = 0.0;
-                if (j < g.nvalid) probe_at(g, seedmix, L.lat, NC, pl, site, a, br[a], bi[a]);
+                if (j < g.nvalid) probe_at(g, seedmix, L.lat, NC, pl, x, a, br[a], bi[a]);
             }
         } else {
             ld_site<double2, NC>(b64, site, logW, j, br, bi);
@@ -1802,21 +1953,21 @@ __device__ __forceinline__ void k_resid_q_body(const Blk &bk, Launch L, const do
     const int sites_per_tile = kBlock >> logW;
     const unsigned long long seedmix = gen ? mix64(g.seed) : 0ull;
     const ProbeLane pl = gen ? probe_lane(g, NC, g.rhs0 + j) : ProbeLane{};
-    const bool restart = ru && (ldg(cs.flags + j) & kFlagRestart);
+    const bool restart = ru && ((ldg(cs.flags + j) & kFlagRestart) || cs.ru_restart);
     double acc[2] = {0.0, 0.0};
     int t0, t1;
     tile_range(bk, L.ntiles, t0, t1);
     // element e = ((site * NC + a) << logW) + j: lane j is tid % W for every
     // e = e0 + tid + k kBlock (kBlock is a multiple of W)
     const size_t e0 = (size_t)t0 * sites_per_tile * NC * W;
-    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.lat.N) * NC * W;
+    const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.ns) * NC * W;
     for (size_t e = e0 + tid; e < e1; e += kBlock) {
         double qr, qi, br, bi;
         St<double2>::ld(q64, e, qr, qi);
         if (gen) {
             const int row = (int)(e >> logW), site = row / NC, a = row - site * NC;
             br = bi = 0.0;
-            if (j < g.nvalid) probe_at(g, seedmix, L.lat, NC, pl, site, a, br, bi);
+            if (j < g.nvalid) probe_at(g, seedmix, L.lat, NC, pl, lex_of(L.lat, site), a, br, bi);
         } else {
             St<double2>::ld(b64, e, br, bi);
         }
@@ -1863,14 +2014,14 @@ __device__ __forceinline__ void k_displaced_dot_body(const Blk &bk, Launch L, Pr
     const unsigned long long seedmix = mix64(g.seed);
     double acc[2] = {0.0, 0.0};
     int t0, t1;
-    tile_range(bk, L.ntiles, t0, t1);
+    tile_range(bk, full_tiles(L), t0, t1);
     if (j < g.nvalid) {
         ProbeLane pl = probe_lane(g, nc, g.rhs0 + j);
         if (g.cmap) pl.c = g.cmap[pl.c];  // the parent class's probe: same noise, coarse colour
         for (int t = t0; t < t1; ++t) {
             const int site = t * sites_per_tile + sl;
             if (site >= L.lat.N || g.colors[site] != pl.c) continue;
-            const int y = shift0(L.lat, site, p);
+            const int y = site_of(L.lat, shift0(L.lat, site, p));
             for (int b = 0; b < nc; ++b) {
                 double zr, zi;
                 probe_at(g, seedmix, L.lat, nc, pl, site, b, zr, zi);
@@ -1924,7 +2075,7 @@ __device__ __forceinline__ void k_dot_body(const Blk &bk, Launch L, const double
     const int sites_per_tile = kBlock >> L.logW;
     double acc[2] = {0.0, 0.0};
     int t0, t1;
-    tile_range(bk, L.ntiles, t0, t1);
+    tile_range(bk, full_tiles(L), t0, t1);
     const size_t e0 = (size_t)t0 * sites_per_tile * L.nc * W;
     const size_t e1 = min((size_t)t1 * sites_per_tile, (size_t)L.lat.N) * L.nc * W;
     for (size_t e = e0 + tid; e < e1; e += kBlock) {
@@ -1969,7 +2120,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Launch L, const double2 *__res
         vr += x2.x * l2.x + x2.y * l2.y;  // x conj(l)
         vi += x2.y * l2.x - x2.x * l2.y;
     }
-    const size_t o = ((size_t)mu * L.lat.N + site) * nc * nc + a * nc + b;
+    const size_t o = ((size_t)mu * L.lat.N + lex_of(L.lat, site)) * nc * nc + a * nc + b;
     double2 du = make_double2(scale * ur, scale * ui), db = make_double2(scale * vr, scale * vi);
     if (!first) {
         if (dU) {
@@ -1994,9 +2145,9 @@ __global__ void k_to_abi(Launch L, const double2 *__restrict__ x64, double2 *__r
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     const int j = (int)(e & (L.W - 1));
-    const long long sa = e >> L.logW;  // site * nc + a
     if (j >= nvalid) return;
-    xabi[(size_t)(rhs0 + j) * L.lat.N * L.nc + sa] = x64[e];
+    const int sa = (int)(e >> L.logW), site = sa / L.nc, a = sa - site * L.nc;
+    xabi[((size_t)(rhs0 + j) * L.lat.N + lex_of(L.lat, site)) * L.nc + a] = x64[e];
 }
 
 template <typename S>
@@ -2069,17 +2220,40 @@ __global__ __launch_bounds__(kBlock) void k_b_init(BatchLaunch B, int mixed) {
     const SlotDesc *d = slot_of_block(B, bk, kSlotInit);
     if (!d) return;
     k_init_body<S, 0>(bk, d->L, d->g, nullptr, 0, 0, (double2 *)d->b64, (S *)d->r, (S *)d->p,
-                      (S *)d->xlo, (double2 *)d->x64, mixed, d->rd, d->cs);
+                      (S *)d->xlo, (double2 *)d->x64, mixed, 1.0 / d->diag, d->rd);
 }
 
-template <typename S, typename LS, int NC, bool LINKS, int MODE>
+// KIND kStFull: q = A p (even-odd: its even half); kStHop: the odd half of p;
+// kStInit: the first residual of the even-odd start.
+template <typename S, typename LS, int NC, bool LINKS, int MODE, int KIND>
 __global__ __launch_bounds__(kBlock) void k_b_stencil(BatchLaunch B) {
     Blk bk;
-    const SlotDesc *d = slot_of_block(B, bk, kSlotIter);
+    const SlotDesc *d = slot_of_block(B, bk, KIND == kStInit ? kSlotInit : kSlotIter);
     if (!d) return;
-    k_stencil_body<S, LS, NC, LINKS, MODE>(bk, d->L, (typename St<S>::R)d->diag, (const S *)d->p,
-                                           (const S *)d->r, (S *)d->q, (const LS *)d->U,
-                                           d->nbr, 1, d->rd);
+    const HopB none{};
+    if constexpr (KIND == kStHop)
+        k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)(1.0 / d->diag), (const S *)d->p,
+                                                     nullptr, (S *)d->p, nullptr, (const LS *)d->U, d->nbr, 0, d->rd,
+                                                     none);
+    else if constexpr (KIND == kStInit)
+        k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)1, (const S *)d->p, nullptr,
+                                                     (S *)d->r, (S *)d->p, (const LS *)d->U, d->nbr, 1, d->rd, none);
+    else
+        k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)d->diag, (const S *)d->p,
+                                                     (const S *)d->r, (S *)d->q, nullptr, (const LS *)d->U, d->nbr, 1,
+                                                     d->rd, none);
+}
+
+// Even-odd order: the odd half of the FP64 solution, x_o = (b_o + H x_e) / c
+template <int NC, bool LINKS, int MODE>
+__global__ __launch_bounds__(kBlock) void k_b_odd_x(BatchLaunch B, int phase) {
+    Blk bk;
+    const SlotDesc *d = slot_of_block(B, bk, phase);
+    if (!d) return;
+    const HopB hb{(const double2 *)d->b64, d->g, d->gen_b};
+    k_stencil_body<double2, double2, NC, LINKS, MODE, kStHopB>(bk, d->L, 1.0 / d->diag, (const double2 *)d->x64,
+                                                               nullptr, (double2 *)d->x64, nullptr,
+                                                               (const double2 *)d->U64, d->nbr, 0, d->rd, hb);
 }
 
 template <typename S, int XM>
@@ -2382,23 +2556,41 @@ void prepare_links(const Lat &lat, int nc, const void *abi, int *nbr, double *u6
         }                                       \
     } while (0)
 
-void launch_init_probe(const Launch &L, int prec, const ProbeGen &g, double *b64, void *r, void *p, void *xlo,
-                       double *x64, int mixed, const Red &rd, const CgState &cs) {
+template <int SRC>
+static void init_block(const Launch &L, int prec, const ProbeGen &g, const double *src, long long rhs0,
+                       long long nvalid, const InitArgs &ia) {
     DP_DISPATCH_PREC(prec, S,
-                     k_init<S, 0><<<L.nblk, kBlock, 0, L.stream>>>(L, g, nullptr, 0, 0, (double2 *)b64, (S *)r,
-                                                                   (S *)p, (S *)xlo, (double2 *)x64, mixed, rd,
-                                                                   cs));
-    k_finish<2, kEpiInit><<<L.W, kBlock, 0, L.stream>>>(rd, cs);
+                     k_init<S, SRC><<<L.nblk, kBlock, 0, L.stream>>>(L, g, (const double2 *)src, rhs0, nvalid,
+                                                                     (double2 *)ia.b64, (S *)ia.r, (S *)ia.p,
+                                                                     (S *)ia.xlo, (double2 *)ia.x64, ia.mixed,
+                                                                     1.0 / ia.diag, ia.rd));
+    if (!L.lat.eo) {
+        k_finish<2, kEpiInit><<<L.W, kBlock, 0, L.stream>>>(ia.rd, ia.cs);
+        return;
+    }
+    // r = p = b_e + H b_o / c: the odd half of p holds -b_o / c
+    StencilArgs a;
+    a.kind = kStInit;
+    a.links = ia.links;
+    a.diag = 1.0;
+    a.pin = ia.p;
+    a.q = ia.r;
+    a.q2 = ia.p;
+    a.U = ia.U;
+    a.nbr = ia.nbr;
+    a.cg = 1;
+    a.rd = ia.rd;
+    a.cs = ia.cs;
+    launch_stencil(L, prec, a);
 }
 
-void launch_init_abi(const Launch &L, int prec, const double *babi, long long rhs0, long long nvalid, double *b64,
-                     void *r, void *p, void *xlo, double *x64, int mixed, const Red &rd, const CgState &cs) {
-    ProbeGen g{};
-    DP_DISPATCH_PREC(prec, S,
-                     k_init<S, 1><<<L.nblk, kBlock, 0, L.stream>>>(L, g, (const double2 *)babi, rhs0, nvalid,
-                                                                   (double2 *)b64, (S *)r, (S *)p, (S *)xlo,
-                                                                   (double2 *)x64, mixed, rd, cs));
-    k_finish<2, kEpiInit><<<L.W, kBlock, 0, L.stream>>>(rd, cs);
+void launch_init_probe(const Launch &L, int prec, const ProbeGen &g, const InitArgs &ia) {
+    init_block<0>(L, prec, g, nullptr, 0, 0, ia);
+}
+
+void launch_init_abi(const Launch &L, int prec, const double *babi, long long rhs0, long long nvalid,
+                     const InitArgs &ia) {
+    init_block<1>(L, prec, ProbeGen{}, babi, rhs0, nvalid, ia);
 }
 
 // Stencil modes a launch shape admits.  The grouped modes need the slab walk
@@ -2408,7 +2600,8 @@ void launch_init_abi(const Launch &L, int prec, const double *babi, long long rh
 // W >= 32 (quads, lines); mode 2 a wavefront per site (W >= 64); mode 5
 // one right-hand side (not BF16).
 bool stencil_mode_valid(const Launch &L, int prec, int mode) {
-    const bool slabs = L.nblk >= 8 && L.nblk % 8 == 0 && L.lat.D[0] % 8 == 0;
+    // (the grouped modes' members are neighbours in the index order)
+    const bool slabs = L.nblk >= 8 && L.nblk % 8 == 0 && L.lat.D[0] % 8 == 0 && !L.lat.eo;
     const int n0 = L.lat.D[0] / 8;
     switch (mode) {
         case 0: return true;
@@ -2434,19 +2627,21 @@ int stencil_mode_rule(const Launch &L, int prec) {
     return L.W >= 16 ? 1 : 0;
 }
 
-template <typename S, typename LS, int NC, bool LINKS>
+template <typename S, typename LS, int NC, bool LINKS, int KIND>
 static void stencil_nc(const Launch &L, const StencilArgs &a) {
     using R = typename St<S>::R;
     dim3 grid(L.nblk), blk(kBlock);
     const S *pin = (const S *)a.pin, *rin = (const S *)a.rin;
-    S *q = (S *)a.q;
+    S *q = (S *)a.q, *q2 = (S *)a.q2;
     const LS *U = (const LS *)a.U;
-#define DP_ST(M)                                                                                        \
-    if (a.ev0)                                                                                          \
-        hipExtLaunchKernelGGL(k_stencil<S, LS, NC, LINKS, M>, grid, blk, 0, L.stream, a.ev0, a.ev1, 0, L, \
-                              (R)a.diag, pin, rin, q, U, a.nbr, a.cg, a.rd);                            \
-    else                                                                                                \
-        k_stencil<S, LS, NC, LINKS, M><<<grid, blk, 0, L.stream>>>(L, (R)a.diag, pin, rin, q, U, a.nbr, a.cg, a.rd)
+    HopB hb{(const double2 *)a.b64, a.gen ? *a.gen : ProbeGen{}, a.gen ? 1 : 0};
+#define DP_ST(M)                                                                                              \
+    if (a.ev0)                                                                                                \
+        hipExtLaunchKernelGGL(k_stencil<S, LS, NC, LINKS, M, KIND>, grid, blk, 0, L.stream, a.ev0, a.ev1, 0, L, \
+                              (R)a.diag, pin, rin, q, q2, U, a.nbr, a.cg, a.rd, hb);                          \
+    else                                                                                                      \
+        k_stencil<S, LS, NC, LINKS, M, KIND><<<grid, blk, 0, L.stream>>>(L, (R)a.diag, pin, rin, q, q2, U, a.nbr, \
+                                                                         a.cg, a.rd, hb)
     constexpr int prec = std::is_same<S, double2>::value ? kF64 : (std::is_same<S, float2>::value ? kF32 : kBF16);
     const int mode = L.smode >= 0 && stencil_mode_valid(L, prec, L.smode) ? L.smode : stencil_mode_rule(L, prec);
     switch (mode) {
@@ -2459,36 +2654,51 @@ static void stencil_nc(const Launch &L, const StencilArgs &a) {
         case 0: DP_ST(0); break;
         case 1: DP_ST(1); break;
         case 2: DP_ST(2); break;
-        case 3: DP_ST(3); break;
-        case 4: DP_ST(4); break;
-        default: DP_ST(6); break;
+        default:  // the grouped modes: never in even-odd order
+            if constexpr (KIND == kStFull) {
+                if (mode == 3) {
+                    DP_ST(3);
+                } else if (mode == 4) {
+                    DP_ST(4);
+                } else {
+                    DP_ST(6);
+                }
+            }
+            break;
     }
 #undef DP_ST
 }
 
-template <typename S, typename LS>
+template <typename S, typename LS, int KIND>
 static void stencil_t(const Launch &L, const StencilArgs &a) {
     if (L.nc == 3) {
         if (a.links)
-            stencil_nc<S, LS, 3, true>(L, a);
+            stencil_nc<S, LS, 3, true, KIND>(L, a);
         else
-            stencil_nc<S, LS, 3, false>(L, a);
+            stencil_nc<S, LS, 3, false, KIND>(L, a);
     } else {
         if (a.links)
-            stencil_nc<S, LS, 1, true>(L, a);
+            stencil_nc<S, LS, 1, true, KIND>(L, a);
         else
-            stencil_nc<S, LS, 1, false>(L, a);
+            stencil_nc<S, LS, 1, false, KIND>(L, a);
     }
 }
 
+template <typename S>
+static void stencil_kind(const Launch &L, const StencilArgs &a) {
+    if (a.kind == kStHop) return stencil_t<S, S, kStHop>(L, a);
+    if (a.kind == kStInit) return stencil_t<S, S, kStInit>(L, a);
+    if constexpr (std::is_same<S, double2>::value)
+        if (a.kind == kStHopB) return stencil_t<S, S, kStHopB>(L, a);
+    stencil_t<S, S, kStFull>(L, a);
+}
+
 void launch_stencil(const Launch &L, int prec, const StencilArgs &a) {
-    if (prec == kF64)
-        stencil_t<double2, double2>(L, a);
-    else if (prec == kF32)
-        stencil_t<float2, float2>(L, a);
-    else
-        stencil_t<bf16x2, bf16x2>(L, a);
-    if (a.cg) k_finish_cg<<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
+    DP_DISPATCH_PREC(prec, S, stencil_kind<S>(L, a));
+    if (a.kind == kStInit)
+        k_finish<4, kEpiInitEo><<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
+    else if (a.cg)
+        k_finish_cg<<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
 }
 
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
@@ -2624,12 +2834,12 @@ __global__ __launch_bounds__(kBlock) void k_force_lanes(Launch L, const double2 
         for (int k = 0; k < NR; ++k) red[row][base + k] = v[k];
     __syncthreads();
     if (!live) return;
-    const int nw = W < 64 ? 1 : W >> 6, r0 = W < 64 ? pl : (pl * W) >> 6;
+    const int nw = W < 64 ? 1 : W >> 6, r0 = W < 64 ? pl : (pl * W) >> 6, x = lex_of(L.lat, site);
     for (int k = j; k < NV; k += W) {
         double t = red[r0][k];
         for (int w = 1; w < nw; ++w) t += red[r0 + w][k];
         const int ab = k >> 2, comp = k & 3;
-        const size_t o = 2 * (((size_t)mu * L.lat.N + site) * NC * NC + ab) + (comp & 1);
+        const size_t o = 2 * (((size_t)mu * L.lat.N + x) * NC * NC + ab) + (comp & 1);
         double *out = comp < 2 ? dU : dUbar;
         if (!out) continue;
         t *= scale;
@@ -2685,41 +2895,48 @@ void launch_make_probes_abi(const Lat &lat, int nc, const ProbeGen &g, long long
 
 // ------------------------------------------------------------ multi-instance launchers
 
-void launch_b_init(const BatchLaunch &B, int mixed) {
-    DP_DISPATCH_PREC(B.prec, S, k_b_init<S><<<B.nblocks, kBlock, 0, B.stream>>>(B, mixed));
-    k_b_finish<2, kEpiInit><<<B.nslots * B.W, kBlock, 0, B.stream>>>(B, kSlotInit);
-}
-
-template <typename S, typename LS, int NC, bool LINKS, int M>
+template <typename S, int NC, bool LINKS, int M, int KIND>
 static void b_stencil_m(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) {
     if (ev0)
-        hipExtLaunchKernelGGL(k_b_stencil<S, LS, NC, LINKS, M>, dim3(B.nblocks), dim3(kBlock), 0, B.stream, ev0, ev1,
-                              0, B);
+        hipExtLaunchKernelGGL(k_b_stencil<S, S, NC, LINKS, M, KIND>, dim3(B.nblocks), dim3(kBlock), 0, B.stream, ev0,
+                              ev1, 0, B);
     else
-        k_b_stencil<S, LS, NC, LINKS, M><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+        k_b_stencil<S, S, NC, LINKS, M, KIND><<<B.nblocks, kBlock, 0, B.stream>>>(B);
 }
 
-template <typename S, typename LS, int NC, bool LINKS>
+template <typename S, int NC, bool LINKS, int KIND>
 static void b_stencil_t(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) {
     if (B.mode == 2)
-        b_stencil_m<S, LS, NC, LINKS, 2>(B, ev0, ev1);
+        b_stencil_m<S, NC, LINKS, 2, KIND>(B, ev0, ev1);
     else if (B.mode == 1)
-        b_stencil_m<S, LS, NC, LINKS, 1>(B, ev0, ev1);
+        b_stencil_m<S, NC, LINKS, 1, KIND>(B, ev0, ev1);
     else
-        b_stencil_m<S, LS, NC, LINKS, 0>(B, ev0, ev1);
+        b_stencil_m<S, NC, LINKS, 0, KIND>(B, ev0, ev1);
 }
 
-template <typename S>
+template <int KIND>
 static void b_stencil(const BatchLaunch &B, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-    if (B.nc == 3)
-        B.links ? b_stencil_t<S, S, 3, true>(B, ev0, ev1) : b_stencil_t<S, S, 3, false>(B, ev0, ev1);
-    else
-        B.links ? b_stencil_t<S, S, 1, true>(B, ev0, ev1) : b_stencil_t<S, S, 1, false>(B, ev0, ev1);
+    DP_DISPATCH_PREC(B.prec, S, {
+        if (B.nc == 3)
+            B.links ? b_stencil_t<S, 3, true, KIND>(B, ev0, ev1) : b_stencil_t<S, 3, false, KIND>(B, ev0, ev1);
+        else
+            B.links ? b_stencil_t<S, 1, true, KIND>(B, ev0, ev1) : b_stencil_t<S, 1, false, KIND>(B, ev0, ev1);
+    });
 }
 
-void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) {
-    DP_DISPATCH_PREC(B.prec, S, b_stencil<S>(B, ev0, ev1));
+void launch_b_init(const BatchLaunch &B, int mixed) {
+    DP_DISPATCH_PREC(B.prec, S, k_b_init<S><<<B.nblocks, kBlock, 0, B.stream>>>(B, mixed));
+    if (B.eo) {
+        b_stencil<kStInit>(B);
+        k_b_finish<4, kEpiInitEo><<<B.nslots * B.W, kBlock, 0, B.stream>>>(B, kSlotInit);
+    } else {
+        k_b_finish<2, kEpiInit><<<B.nslots * B.W, kBlock, 0, B.stream>>>(B, kSlotInit);
+    }
 }
+
+void launch_b_hop(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_stencil<kStHop>(B, ev0, ev1); }
+
+void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_stencil<kStFull>(B, ev0, ev1); }
 
 void launch_b_update(const BatchLaunch &B, int xmode) {
     k_b_finish_cg<<<(B.nslots * B.W + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, B.stream>>>(B);
@@ -2737,6 +2954,7 @@ void launch_b_update(const BatchLaunch &B, int xmode) {
 void launch_b_reseed(const BatchLaunch &B) { k_b_reseed<<<B.nslots * B.W, kBlock, 0, B.stream>>>(B); }
 
 void launch_b_iteration(const BatchLaunch &B, int xmode) {
+    if (B.eo) launch_b_hop(B);
     launch_b_stencil(B);
     launch_b_update(B, xmode);
 }
@@ -2751,6 +2969,23 @@ static void b_tr_t(const BatchLaunch &B, int phase, int ru) {
         k_b_true_resid<S, NC, LINKS, 0><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase, ru);
 }
 
+template <int NC, bool LINKS>
+static void b_odd_x_t(const BatchLaunch &B, int phase) {
+    if (B.mode == 2)
+        k_b_odd_x<NC, LINKS, 2><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
+    else if (B.mode == 1)
+        k_b_odd_x<NC, LINKS, 1><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
+    else
+        k_b_odd_x<NC, LINKS, 0><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
+}
+
+static void b_odd_x(const BatchLaunch &B, int phase) {
+    if (B.nc == 3)
+        B.links ? b_odd_x_t<3, true>(B, phase) : b_odd_x_t<3, false>(B, phase);
+    else
+        B.links ? b_odd_x_t<1, true>(B, phase) : b_odd_x_t<1, false>(B, phase);
+}
+
 // Reliable update (final_stats = 0: slots flagged kSlotRU; mixed precision:
 // fold, then the true residual replaces r and continues p) or the final
 // statistics (final_stats = 1: slots flagged kSlotFinal; FP64, whose iterate
@@ -2760,6 +2995,7 @@ void launch_b_ru(const BatchLaunch &B, int final_stats) {
     const int ru = final_stats ? 0 : 1;
     DP_DISPATCH_PREC(B.prec, S, {
         if (B.prec != kF64) k_b_fold<S><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
+        if (B.eo) b_odd_x(B, phase);
         if (B.nc == 3)
             B.links ? b_tr_t<S, 3, true>(B, phase, ru) : b_tr_t<S, 3, false>(B, phase, ru);
         else
@@ -2814,14 +3050,12 @@ void launch_b_state_out(const BatchLaunch &B, const char *st_all, char *dst, siz
 }
 
 
-void launch_init_b64(const Launch &L, int prec, double *b64, void *r, void *p, void *xlo, double *x64, int mixed,
-                     const Red &rd, const CgState &cs) {
-    ProbeGen g{};
-    DP_DISPATCH_PREC(prec, S,
-                     k_init<S, 2><<<L.nblk, kBlock, 0, L.stream>>>(L, g, nullptr, 0, 0, (double2 *)b64, (S *)r,
-                                                                   (S *)p, (S *)xlo, (double2 *)x64, mixed, rd,
-                                                                   cs));
-    k_finish<2, kEpiInit><<<L.W, kBlock, 0, L.stream>>>(rd, cs);
+void launch_probe_fill(const Launch &L, const ProbeGen &g, double *out) {
+    k_probe_fill<<<L.nblk, kBlock, 0, L.stream>>>(L, g, (double2 *)out);
+}
+
+void launch_init_b64(const Launch &L, int prec, const double *src, const InitArgs &ia) {
+    init_block<2>(L, prec, ProbeGen{}, src, 0, 0, ia);
 }
 
 void launch_dot_shift(const Launch &L, const double *u, const double *w, int p, const Red &rd, const CgState &cs) {

@@ -12,6 +12,18 @@
 //             direct r^H p, the line search along p), beta, convergence flags
 //   update    x += alpha p, r -= alpha q, p = r + beta p; |r|^2 and
 //             Re q^H p of the new p as stored
+// Where every extent is even (and c = m2 + 8 > 0) the hopping term H connects
+// even and odd sites only, and CG runs on the even sites' Schur complement
+// S x_e = b_e + H b_o / c, S = c - H H / c, with x_o = (b_o + H x_e) / c at the
+// end: vectors half as long, and half the steps (the condition number at 16^4,
+// m2 = 0.05, falls from 12.5 to 3.7; a step's rate is the square of CG's on A).
+// The residual of (x_e, x_o) vanishes on the odd sites and is the reduced
+// system's on the even ones, so the stopping rule |b - A x| <= tol |b| is
+// unchanged.  The vectors are stored even sites first (Lat::eo); a step adds
+// one launch, p_o = H p_e / c, before q_e = c p_e - H p_o.  Traces to 1e-11:
+// 16^4 x 3, 2880 probes, FP32: 424 -> 226 ms; 8^4 x 3, 192 probes, FP64:
+// 5.7 -> 2.5 ms; 64 uneven lattices, BF16: 122 -> 60 ms; 32^4 gradient, FP32:
+// 472 -> 259 ms; one 8^4 solve, FP64 (launch bound): 0.99 -> 0.67 ms.
 // The host reads a control word after groups of iterations whose length is
 // predicted from the residual decay.
 //
@@ -163,10 +175,9 @@ static size_t prec_bytes(int prec) { return prec == kF64 ? 16 : (prec == kF32 ? 
 // workgroup, so the launch takes up to N / 8 workgroups; the other kernels
 // leave the extra ones idle)
 static int launch_units(const Lat &lat, int W) {
-    int logW = 0;
-    while ((1 << logW) < W) ++logW;
-    const int ntiles = (lat.N + (kBlock >> logW) - 1) / (kBlock >> logW);
-    return W == 1 ? std::max(ntiles, (lat.N + 7) / 8) : ntiles;
+    Launch L;
+    set_geometry(L, lat, 1, W);
+    return W == 1 ? std::max(L.ntiles, (L.ns + 7) / 8) : L.ntiles;
 }
 
 int launch_blocks(const Lat &lat, int W) { return grid_blocks(launch_units(lat, W)); }
@@ -207,7 +218,7 @@ size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W)
     }
 }
 
-dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep &out, hipStream_t s) {
+dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep &out, hipStream_t s, bool reduce) {
     for (int d = 0; d < 4; ++d)
         if (op.dims[d] < 1) {
             ctx->err = "operator dims must be >= 1";
@@ -232,6 +243,7 @@ dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep
     }
     out.lat.N = (int)N;
     for (int d = 0; d < 4; ++d) out.lat.D[d] = op.dims[d];
+    out.lat.eo = reduce && eo_reducible(op.dims, op.m2);
     out.nc = op.nc;
     out.m2 = op.m2;
     out.links = op.links != nullptr;
@@ -265,8 +277,8 @@ dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep
 // them.
 static std::string stencil_key(const OpPrep &op, int inner, int W) {
     char k[160];
-    std::snprintf(k, sizeof k, "stencil gfx950 dims=%dx%dx%dx%d nc=%d prec=%d links=%d W=%d", op.lat.D[0],
-                  op.lat.D[1], op.lat.D[2], op.lat.D[3], op.nc, inner, op.links ? 1 : 0, W);
+    std::snprintf(k, sizeof k, "stencil gfx950 dims=%dx%dx%dx%d nc=%d prec=%d links=%d W=%d%s", op.lat.D[0],
+                  op.lat.D[1], op.lat.D[2], op.lat.D[3], op.nc, inner, op.links ? 1 : 0, W, op.lat.eo ? " eo" : "");
     return k;
 }
 
@@ -296,8 +308,7 @@ static dp_status time_iterations(dp_ctx *ctx, const OpPrep &op, int inner, const
     g.ncolors = 1;
     g.noise = DP_NOISE_Z2_COMPLEX;
     g.nvalid = Lc.W;
-    launch_init_probe(Lc, inner, g, (double *)ctx->at(kSlotB64), ctx->at(kSlotR), ctx->at(kSlotP), xlo,
-                      (double *)ctx->at(kSlotX64), mixed ? 1 : 0, rd, cs);
+    launch_init_probe(Lc, inner, g, init_args(ctx, op, xlo, (double *)ctx->at(kSlotX64), rd, cs));
     StencilArgs a;
     a.links = op.links;
     a.diag = op.m2 + 8.0;
@@ -311,10 +322,7 @@ static dp_status time_iterations(dp_ctx *ctx, const OpPrep &op, int inner, const
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
     const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
-    auto iter = [&](int xm) {
-        launch_stencil(Lc, inner, a);
-        launch_update(Lc, inner, xlo, ctx->at(kSlotR), ctx->at(kSlotP), ctx->at(kSlotQ), rd, cs, xm);
-    };
+    auto iter = [&](int xm) { launch_cg_step(Lc, inner, a, xlo, xm); };
     iter(0);
     DP_HIP(hipEventRecord(e0, Lc.stream));
     for (int k = 0; k < 4; ++k) iter(xmode_of(k, 4, xdefer));
@@ -400,13 +408,7 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
                    "under 4 GiB";
         return DP_EINVAL;
     }
-    int logW = 0;
-    while ((1 << logW) < W) ++logW;
-    L.lat = op.lat;
-    L.nc = op.nc;
-    L.W = W;
-    L.logW = logW;
-    L.ntiles = (op.lat.N + (kBlock >> logW) - 1) / (kBlock >> logW);
+    set_geometry(L, op.lat, op.nc, W);
     L.nblk = launch_blocks(op.lat, W);
     L.stream = s;
     L.smode = -1;
@@ -434,10 +436,12 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     cs.flags = iv + 2 * kMaxW;
     cs.ctrl = ctx->ctrl_dev;
     cs.tol2 = cfg.tol * cfg.tol;
-    cs.delta2 = cfg.delta * cfg.delta;
+    const double delta = cfg.delta > 0 ? cfg.delta : default_reliable_delta(cfg.inner, op.lat.eo);
+    cs.delta2 = delta * delta;
     cs.hold = cfg.inner == kBF16;
     cs.rq_direct = cfg.inner == kBF16;  // see the finishing kernel
     cs.exact = cfg.inner == kF64;
+    cs.ru_restart = cfg.inner == kBF16 && op.lat.eo;
     DP_TRY(pick_stencil(ctx, op, cfg, L, cs));
     rd.part1 = (double *)ctx->at(kSlotPart1);
     rd.part2 = rd.part1 + (size_t)L.nblk * W * 4;
@@ -475,7 +479,10 @@ int xmode_of(int c, int n, bool defer) {
 // of BF16 storage (2^-9; the fastest drop measured on the 16^4 single
 // instance and the uneven batch, where 0.05 took 1.4x the time), and 1e-3
 // for FP32, where the drop hardly matters.
-double default_reliable_delta(int inner) { return inner == kBF16 ? 0.002 : 1e-3; }
+// In even-odd order, where BF16 restarts its directions at each reliable
+// update and a drop takes half as many steps, the deeper drops cost more steps
+// than the updates they save (kEpiRU in kernels.hip).
+double default_reliable_delta(int inner, int eo) { return inner == kBF16 ? (eo ? 0.01 : 0.002) : 1e-3; }
 
 // A reliable update at least every ru_gap iterations (mixed precision).
 int default_ru_gap(int inner) { return inner == kBF16 ? 24 : 100; }
@@ -486,22 +493,60 @@ bool xdefer_enabled() {
     return !(e && std::strcmp(e, "0") == 0);
 }
 
-double stencil_alg_bytes(const Lat &lat, int nc, int W, int prec, bool links) {
+double stencil_alg_bytes(const Launch &L, int prec, bool links, int kind) {
     const double c = (double)prec_bytes(prec);  // one complex number
-    return (double)lat.N * (2.0 * W * nc * c + (links ? 4.0 * nc * nc * c : 0.0));
+    // index order: p read, q written, each link once.  Even-odd: a half reads
+    // the other half's vector (the even half p_e too) and writes its own, and
+    // each of the 4 N links is a hop into either half
+    const double vec = !L.lat.eo || kind == kStHop ? 2.0 : 3.0;
+    return (double)L.ns * vec * L.W * L.nc * c + (links ? (double)L.lat.N * 4.0 * L.nc * L.nc * c : 0.0);
 }
 
 static dp_status timed_stencil(dp_ctx *ctx, const SolveCfg &cfg, const Launch &L, const StencilArgs &a) {
-    // the launches of one block are equal: below 256 MB of algorithmic
-    // traffic per launch, time every 8th
-    const double bytes = stencil_alg_bytes(L.lat, L.nc, L.W, cfg.inner, a.links);
+    // the launches of one block are equal (even-odd: alternate between two
+    // kinds): below 256 MB of algorithmic traffic per launch, time every 8th
+    // (9th, which alternates too)
+    const double bytes = stencil_alg_bytes(L, cfg.inner, a.links, a.kind);
     return timed_launch(ctx, cfg.profile != 0, bytes,
                         [&](hipEvent_t e0, hipEvent_t e1) {
                             StencilArgs ta = a;
                             ta.ev0 = e0;
                             ta.ev1 = e1;
                             launch_stencil(L, cfg.inner, ta);
-                        }, bytes < 256e6 ? 8u : 1u);
+                        }, bytes < 256e6 ? (L.lat.eo ? 9u : 8u) : 1u);
+}
+
+StencilArgs hop_args(const StencilArgs &a, void *p) {
+    StencilArgs h = a;
+    h.kind = kStHop;
+    h.diag = 1.0 / a.diag;
+    h.q = p;
+    h.rin = nullptr;
+    h.cg = 0;
+    return h;
+}
+
+void launch_cg_step(const Launch &L, int prec, const StencilArgs &a, void *xlo, int xmode) {
+    if (L.lat.eo) launch_stencil(L, prec, hop_args(a, (void *)a.pin));
+    launch_stencil(L, prec, a);
+    launch_update(L, prec, xlo, (void *)a.rin, (void *)a.pin, a.q, a.rd, a.cs, xmode);
+}
+
+InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, double *x64, const Red &rd, const CgState &cs) {
+    InitArgs ia;
+    ia.b64 = (double *)ctx->at(kSlotB64);
+    ia.r = ctx->at(kSlotR);
+    ia.p = ctx->at(kSlotP);
+    ia.xlo = xlo;
+    ia.x64 = x64;
+    ia.mixed = op.inner != kF64;
+    ia.links = op.links;
+    ia.diag = op.m2 + 8.0;
+    ia.U = op.U8;
+    ia.nbr = op.nbr;
+    ia.rd = rd;
+    ia.cs = cs;
+    return ia;
 }
 
 dp_status finish_profile(dp_ctx *ctx, dp_solve_stats *st) {
@@ -531,8 +576,10 @@ void block_stats(const void *state, BlockStats &bs, dp_solve_stats *acc) {
         const double bb = bbv[j];
         const double rel = bb > 0 ? std::sqrt(true_rr[j] / bb) : 0.0;
         bs.max_rel = std::max(bs.max_rel, rel);
-        bs.iters_sum += iters[j];
-        bs.iters_max = std::max(bs.iters_max, iters[j]);
+        int n = iters[j] * bs.it_mult;
+        if (bs.it_cap > 0) n = std::min(n, bs.it_cap);
+        bs.iters_sum += n;
+        bs.iters_max = std::max(bs.iters_max, n);
         if (flags[j] & kFlagBreakdown) ++bs.nbreak;
         else if (flags[j] & kFlagConverged) ++bs.nconv;
     }
@@ -557,6 +604,7 @@ static std::string graph_key(int steps, int inner, const Launch &L, const Stenci
     val(inner);
     for (int d = 0; d < 4; ++d) val(L.lat.D[d]);
     val(L.lat.N);
+    val(L.lat.eo);
     val(L.nc);
     val(L.W);
     val(L.logW);
@@ -586,6 +634,7 @@ static std::string graph_key(int steps, int inner, const Launch &L, const Stenci
     val(c.exact);
     val(c.hold);
     val(c.rq_direct);
+    val(c.ru_restart);
     val(xlo);
     return k;
 }
@@ -599,7 +648,25 @@ static void true_residual(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, co
                           const CgState &cs, const double *b64, double *x64, int ru, const ProbeGen *gen) {
     const bool mixed = cfg.inner != kF64;
     double *q64 = (double *)ctx->at(mixed ? kSlotQ64 : kSlotQ);
+    Launch L64 = L;
+    L64.smode = -1;
     StencilArgs a;
+    if (L.lat.eo) {
+        // the odd half of the solution, x_o = (b_o + H x_e) / c: the residual
+        // on the odd sites is then zero and that on the even ones is the
+        // reduced system's
+        a.kind = kStHopB;
+        a.links = op.links;
+        a.diag = 1.0 / (op.m2 + 8.0);
+        a.pin = x64;
+        a.q = x64;
+        a.b64 = b64;
+        a.gen = gen;
+        a.U = op.U8x;
+        a.nbr = op.nbr;
+        launch_stencil(L64, kF64, a);
+        a = StencilArgs();
+    }
     a.links = op.links;
     a.diag = op.m2 + 8.0;
     a.pin = x64;
@@ -607,12 +674,10 @@ static void true_residual(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, co
     a.U = op.U8x;
     a.nbr = op.nbr;
     a.cg = 0;
-    // the built-in choice, the fastest measured: 16^4, W = 32: FP64 quads
-    // 100 us (although they hold 177 registers: two waves per SIMD), the LDS
-    // tile 105, x0 pairs 108, per-lane links 157; 32^4: x0 lines 1504 us,
-    // pairs 1672, the LDS tile 1756, per-lane links 2417
-    Launch L64 = L;
-    L64.smode = -1;
+    // the built-in choice, the fastest measured in index order: 16^4, W = 32:
+    // FP64 quads 100 us (although they hold 177 registers: two waves per
+    // SIMD), the LDS tile 105, x0 pairs 108, per-lane links 157; 32^4: x0
+    // lines 1504 us, pairs 1672, the LDS tile 1756, per-lane links 2417
     launch_stencil(L64, kF64, a);
     launch_resid_q(L, cfg.inner, b64, q64, ctx->at(kSlotR), ctx->at(kSlotP), ctx->at(kSlotQ), ru, rd, cs, gen);
 }
@@ -626,7 +691,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     void *r = ctx->at(kSlotR), *p = ctx->at(kSlotP), *q = ctx->at(kSlotQ);
     const double *b64 = (const double *)ctx->at(kSlotB64);
     const double diag = op.m2 + 8.0;
-    init(xlo, x64);  // b, r = p = b, xlo = 0 (x64 = 0)
+    init(op, xlo, x64);  // b, r = p = b (even-odd: b_e + H b_o / c), xlo = 0 (x64 = 0)
     DP_HIP(hipGetLastError());
     int nactive = bs.nvalid;
     if (!Init::kLanesNonzero) {
@@ -645,16 +710,24 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     a.cg = 1;
     a.rd = rd;
     a.cs = cs;
+    // Even-odd order: a step advances the Krylov space of A by two degrees, as
+    // two iterations of CG on A would, and counts as two (reported counts, the
+    // caller's limit and the gap between reliable updates are in iterations)
+    const int mult = op.lat.eo ? 2 : 1;
+    bs.it_mult = mult;
+    bs.it_cap = op.lat.eo ? cfg.max_iter : 0;
+    const int max_steps = (cfg.max_iter + mult - 1) / mult, ru_gap = std::max(1, cfg.ru_gap / mult);
+    const int check_every = std::max(1, ctx->check_every / mult);
     // Iterations between host checks: start with check_every, then predict
     // from the decay of the slowest lane's residual since the last check.
-    int steps_next = std::max(1, ctx->check_every);
+    int steps_next = check_every;
     // mixed precision takes the x updates of an iteration group in pairs
     // (the update kernel's deferred mode)
     const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
     double ratio_prev = -1.0;
     int it_prev = 0, it_ru = 0;
-    while (nactive > 0 && it < cfg.max_iter) {
-        const int steps = std::min(steps_next, cfg.max_iter - it);
+    while (nactive > 0 && it < max_steps) {
+        const int steps = std::min(steps_next, max_steps - it);
         if (cfg.use_graph && !cfg.profile) {
             // the group [stencil, finish, update] x steps replayed from a
             // graph; a graph holds the kernel arguments it was captured with,
@@ -668,10 +741,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
                 hipGraph_t graph = nullptr;
                 hipGraphExec_t exec = nullptr;
                 DP_HIP(hipStreamBeginCapture(L.stream, hipStreamCaptureModeThreadLocal));
-                for (int c = 0; c < steps; ++c) {
-                    launch_stencil(L, cfg.inner, a);
-                    launch_update(L, cfg.inner, xlo, r, p, q, rd, cs, xmode_of(c, steps, xdefer));
-                }
+                for (int c = 0; c < steps; ++c) launch_cg_step(L, cfg.inner, a, xlo, xmode_of(c, steps, xdefer));
                 DP_HIP(hipStreamEndCapture(L.stream, &graph));
                 const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(graph);
@@ -681,6 +751,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             DP_HIP(hipGraphLaunch(g->second, L.stream));
         } else {
             for (int c = 0; c < steps; ++c) {
+                if (op.lat.eo) DP_TRY(timed_stencil(ctx, cfg, L, hop_args(a, p)));
                 DP_TRY(timed_stencil(ctx, cfg, L, a));
                 launch_update(L, cfg.inner, xlo, r, p, q, rd, cs, xmode_of(c, steps, xdefer));
             }
@@ -693,14 +764,14 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             double ratio, ru_ratio;
             std::memcpy(&ratio, ctx->ctrl_host + 4, sizeof(double));
             std::memcpy(&ru_ratio, ctx->ctrl_host + 6, sizeof(double));
-            steps_next = next_check(std::max(1, ctx->check_every), ratio, ratio_prev, it - it_prev,
+            steps_next = next_check(check_every, ratio, ratio_prev, it - it_prev,
                                     cfg.inner == kBF16 ? ru_ratio : 0.0);
             ratio_prev = ratio;
             it_prev = it;
         }
         if (mixed && nactive > 0 &&
-            (ctx->ctrl_host[2] > 0 || ctx->ctrl_host[1] == nactive || it >= cfg.max_iter ||
-             it - it_ru >= cfg.ru_gap)) {
+            (ctx->ctrl_host[2] > 0 || ctx->ctrl_host[1] == nactive || it >= max_steps ||
+             it - it_ru >= ru_gap)) {
             it_ru = it;
             // reliable update: x64 += xlo, r = b - A x64 in FP64 (p continued
             // from it), the residual norms restart from it
@@ -751,8 +822,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
 // model (see choose_width).
 static std::string width_key(const OpPrep &op, const SolveCfg &cfg, int W) {
     char k[160];
-    std::snprintf(k, sizeof k, "width gfx950 dims=%dx%dx%dx%d nc=%d prec=%d links=%d W=%d", op.lat.D[0],
-                  op.lat.D[1], op.lat.D[2], op.lat.D[3], op.nc, cfg.inner, op.links ? 1 : 0, W);
+    std::snprintf(k, sizeof k, "width gfx950 dims=%dx%dx%dx%d nc=%d prec=%d links=%d W=%d%s", op.lat.D[0],
+                  op.lat.D[1], op.lat.D[2], op.lat.D[3], op.nc, cfg.inner, op.links ? 1 : 0, W,
+                  op.lat.eo ? " eo" : "");
     return k;
 }
 
@@ -814,8 +886,7 @@ static dp_status time_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, 
     g.nvalid = W;
     const bool mixed = cfg.inner != kF64;
     void *xlo = mixed ? ctx->at(kSlotXLo) : ctx->at(kSlotX64);
-    launch_init_probe(L, cfg.inner, g, (double *)ctx->at(kSlotB64), ctx->at(kSlotR), ctx->at(kSlotP), xlo,
-                      (double *)ctx->at(kSlotX64), mixed ? 1 : 0, rd, cs);
+    launch_init_probe(L, cfg.inner, g, init_args(ctx, op, xlo, (double *)ctx->at(kSlotX64), rd, cs));
     StencilArgs a;
     a.links = op.links;
     a.diag = op.m2 + 8.0;
@@ -829,10 +900,7 @@ static dp_status time_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, 
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
     const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
-    auto iter = [&](int xm) {
-        launch_stencil(L, cfg.inner, a);
-        launch_update(L, cfg.inner, xlo, ctx->at(kSlotR), ctx->at(kSlotP), ctx->at(kSlotQ), rd, cs, xm);
-    };
+    auto iter = [&](int xm) { launch_cg_step(L, cfg.inner, a, xlo, xm); };
     iter(xmode_of(0, 2, xdefer));
     iter(xmode_of(1, 2, xdefer));
     hipEvent_t e0, e1;
