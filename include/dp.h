@@ -185,13 +185,15 @@ typedef struct {
                                iterations here and in dp_solve_stats */
     int32_t inner;          /* DP_PREC_*: storage of the inner CG vectors and links;
                                F32 and BF16 accumulate in FP32 and are refined by
-                               FP64 reliable updates */
+                               FP64 reliable updates.  (Small problems, solved by one
+                               persistent launch per block, are held in FP64 whatever
+                               this says; the stopping rule stays inner's) */
     int32_t rhs_block;      /* right-hand sides solved together (W): 0 = autotune
                                (one instance: a few timed CG iterations per width,
                                cached, DP_TUNE_CACHE names a file; the least time
                                for all right-hand sides, padding of the last block
-                               included; several: the least traffic per useful
-                               lane-site, padding of each instance's last block
+                               included; small problems: all in one block; several:
+                               the least traffic per useful lane-site, padding of each instance's last block
                                included), else a power of two <= 256 whose block
                                vectors (N * nc * W elements of the inner precision)
                                stay under 4 GiB (DP_EINVAL otherwise) */
@@ -204,7 +206,8 @@ typedef struct {
     int32_t use_graph;      /* 1: replay the iteration loop from a captured hipGraph */
     int32_t profile;        /* 1: time stencil kernel launches with HIP events (single
                                instance: every 8th when a launch moves less than 256 MB of
-                               algorithmic traffic, else all; many instances: all) */
+                               algorithmic traffic, else all; many instances: all);
+                               small problems then take the launched kernels too */
 } dp_solve_opts;
 
 typedef struct {

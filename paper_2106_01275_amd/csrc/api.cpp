@@ -189,6 +189,13 @@ dp_status dp_create(dp_ctx **out, int32_t hip_device) {
         dp_destroy(ctx);
         return DP_ENOMEM;
     }
+    std::memset(ctx->ctrl_host, 0, 64);
+    if (hipMalloc((void **)&ctx->small_part, kSmallPartBytes) != hipSuccess ||
+        hipMemset(ctx->small_part, 0, kSmallPartBytes) != hipSuccess) {
+        g_err = "dp_create: device allocation failed";
+        dp_destroy(ctx);
+        return DP_ENOMEM;
+    }
     if (hipHostGetDevicePointer((void **)&ctx->ctrl_dev, ctx->ctrl_host, 0) != hipSuccess) {
         g_err = "dp_create: hipHostGetDevicePointer failed";
         dp_destroy(ctx);
@@ -206,6 +213,7 @@ void dp_destroy(dp_ctx *ctx) {
         if (ctx->slot[s]) (void)hipFree(ctx->slot[s]);
     for (auto &b : ctx->pool) (void)hipFree(b.first);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    if (ctx->small_part) (void)hipFree(ctx->small_part);
     for (auto e : ctx->ev_pool) (void)hipEventDestroy(e);
     for (auto &pr : ctx->ev_pending) {
         (void)hipEventDestroy(pr.first);
@@ -305,6 +313,34 @@ dp_status dp_make_probes(dp_ctx *ctx, const dp_probe_spec *ps, int64_t rhs0, int
     return DP_OK;
 }
 
+// nrhs right-hand sides of one operator; s: their statistics
+static dp_status solve_one(dp_ctx *ctx, const dp_operator &opd, const double *b, double *x, int64_t nrhs,
+                           int32_t rhs_block, SolveCfg cfg, hipStream_t stream, dp_solve_stats &s) {
+    const double t0 = now_s();
+    s = dp_solve_stats{};
+    OpPrep op;
+    int W = 1;
+    DP_TRY(plan_solve(ctx, opd, nrhs, rhs_block, stream, cfg, op, W));
+    s.rhs_block = W;
+    Launch L;
+    Red rd{};
+    CgState cs{};
+    DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
+    for (long long r0 = 0; r0 < nrhs; r0 += W) {
+        const long long nv = std::min<long long>(W, nrhs - r0);
+        BlockStats bs;
+        bs.nvalid = (int)nv;
+        InitAbi init{&L, cfg.inner, b, r0, nv, &rd, &cs, ctx};
+        double *x64 = (double *)ctx->at(kSlotX64);
+        DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, x64, init, bs, &s));
+        launch_to_abi(L, x64, x, r0, nv);
+        DP_HIP(hipGetLastError());
+    }
+    DP_HIP(hipStreamSynchronize(stream));
+    s.seconds = now_s() - t0;
+    return DP_OK;
+}
+
 dp_status dp_solve_batch(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, const void *const *b, void *const *x,
                          const int64_t *nrhs, const dp_solve_opts *o, dp_solve_stats *st, hipStream_t stream) {
     DP_TRY(check_ctx(ctx));
@@ -370,33 +406,14 @@ dp_status dp_solve_batch(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, con
         return worst;
     }
     for (int i = 0; i < ninst; ++i) {
-        const double t0 = now_s();
         dp_solve_stats s{};
         if (nrhs[i] < 0 || (nrhs[i] > 0 && (!b[i] || !x[i]))) {
             ctx->err = "solve_batch: bad right-hand sides";
             return DP_EINVAL;
         }
-        OpPrep op;
-        DP_TRY(prepare_operator(ctx, ops[i], cfg.inner, op, stream));
-        int W = 1;
-        DP_TRY(choose_width(ctx, op, cfg, nrhs[i], o->rhs_block, stream, W));
-        s.rhs_block = W;
-        Launch L;
-        Red rd{};
-        CgState cs{};
-        DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
-        for (long long r0 = 0; r0 < nrhs[i]; r0 += W) {
-            const long long nv = std::min<long long>(W, nrhs[i] - r0);
-            BlockStats bs;
-            bs.nvalid = (int)nv;
-            InitAbi init{&L, cfg.inner, (const double *)b[i], r0, nv, &rd, &cs, ctx};
-            double *x64 = (double *)ctx->at(kSlotX64);
-            DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, x64, init, bs, &s));
-            launch_to_abi(L, x64, (double *)x[i], r0, nv);
-            DP_HIP(hipGetLastError());
-        }
-        DP_HIP(hipStreamSynchronize(stream));
-        s.seconds = now_s() - t0;
+        DP_TRY(with_small(ctx, [&] {
+            return solve_one(ctx, ops[i], (const double *)b[i], (double *)x[i], nrhs[i], o->rhs_block, cfg, stream, s);
+        }));
         if (st) st[i] = s;
         dp_status fs = final_status(s);
         if (fs != DP_OK && worst == DP_OK) worst = fs;
@@ -477,17 +494,16 @@ struct Staging {
 // with the probe of colour cmap[c] of the colouring colors[n] instead of its
 // own (the parent class on a coarser nested level).
 static dp_status trace_displacements(dp_ctx *ctx, const dp_operator &opd, const int32_t *disp, int ndisp,
-                                     const dp_probe_spec &ps, const dp_solve_opts *o, const SolveCfg &cfg,
+                                     const dp_probe_spec &ps, const dp_solve_opts *o, SolveCfg cfg,
                                      dp_trace_result *outs, hipStream_t stream,
                                      const int32_t *const *colors = nullptr, const int *const *cmaps = nullptr) {
     const double t0 = now_s();
     DP_TRY(check_spec(ctx, ps, &opd));
     OpPrep op;
-    DP_TRY(prepare_operator(ctx, opd, cfg.inner, op, stream));
     const int ndil = ps.dilute ? ps.nc : 1;
     const long long nrhs = (long long)ps.nsamples * ps.ncolors * ndil;
     int W = 1;
-    DP_TRY(choose_width(ctx, op, cfg, nrhs, o->rhs_block, stream, W));
+    DP_TRY(plan_solve(ctx, opd, nrhs, o->rhs_block, stream, cfg, op, W));
     Launch L;
     Red rd{};
     CgState cs{};
@@ -517,6 +533,7 @@ static dp_status trace_displacements(dp_ctx *ctx, const dp_operator &opd, const 
         }
         if (stg.drain_after(k, nblocks)) {
             DP_HIP(hipStreamSynchronize(stream));
+            DP_TRY(small_check(ctx));
             for (; k0 <= k; ++k0) {
                 const long long b0 = k0 * W, bn = std::min<long long>(W, nrhs - b0);
                 block_stats(stg.state(k0), stg.stats(k0, 0, -1), &s);
@@ -540,7 +557,7 @@ static dp_status trace_one(dp_ctx *ctx, const dp_operator &opd, int32_t p, const
         ctx->err = "trace_estimate: p must be >= 0";
         return DP_EINVAL;
     }
-    return trace_displacements(ctx, opd, &p, 1, ps, o, cfg, &out, stream);
+    return with_small(ctx, [&] { return trace_displacements(ctx, opd, &p, 1, ps, o, cfg, &out, stream); });
 }
 
 dp_status dp_trace_estimate(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, const int32_t *p,
@@ -637,7 +654,8 @@ dp_status dp_trace_multi(dp_ctx *ctx, const dp_operator *op, const int32_t *disp
         WorkStream &w;
         ~Leave() { (void)w.leave(); }
     } leave_{ws_};
-    dp_status st = trace_displacements(ctx, *op, disp, ndisp, *ps, o, cfg, out, ws_.s);
+    dp_status st =
+        with_small(ctx, [&] { return trace_displacements(ctx, *op, disp, ndisp, *ps, o, cfg, out, ws_.s); });
     if (st == DP_ENOCONV) ctx->err = "trace_multi: some right-hand sides did not converge";
     if (st == DP_EBREAKDOWN) ctx->err = "trace_multi: CG breakdown";
     return st;
@@ -691,8 +709,10 @@ dp_status dp_trace_levels(dp_ctx *ctx, const dp_operator *op, int32_t p, const d
         }
     }
     std::vector<int32_t> disp(ncoarse + 1, p);
-    dp_status st = trace_displacements(ctx, *op, disp.data(), ncoarse + 1, *ps, o, cfg, out, ws_.s, cols.data(),
-                                       maps.data());
+    dp_status st = with_small(ctx, [&] {
+        return trace_displacements(ctx, *op, disp.data(), ncoarse + 1, *ps, o, cfg, out, ws_.s, cols.data(),
+                                   maps.data());
+    });
     if (st == DP_ENOCONV) ctx->err = "trace_levels: some right-hand sides did not converge";
     if (st == DP_EBREAKDOWN) ctx->err = "trace_levels: CG breakdown";
     return st;
@@ -707,78 +727,82 @@ dp_status dp_trace_grad(dp_ctx *ctx, const dp_operator *opd, int32_t p, const dp
         return DP_EINVAL;
     }
     const double t0 = now_s();
-    SolveCfg cfg;
-    DP_TRY(solve_cfg(ctx, o, cfg));
+    SolveCfg cfg0;
+    DP_TRY(solve_cfg(ctx, o, cfg0));
     DP_TRY(check_spec(ctx, *ps, opd));
     WorkStream ws_;
-    DP_TRY(ws_.enter(ctx, stream, cfg.use_graph));
+    DP_TRY(ws_.enter(ctx, stream, cfg0.use_graph));
     struct Leave {
         WorkStream &w;
         ~Leave() { (void)w.leave(); }
     } leave_{ws_};
     stream = ws_.s;
-
-    OpPrep op;
-    DP_TRY(prepare_operator(ctx, *opd, cfg.inner, op, stream));
-    const int ndil = ps->dilute ? ps->nc : 1;
-    const long long nrhs = (long long)ps->nsamples * ps->ncolors * ndil;
-    int W = 1;
-    DP_TRY(choose_width(ctx, op, cfg, nrhs, o->rhs_block, stream, W));
-    Launch L;
-    Red rd{};
-    CgState cs{};
-    DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
-    DP_TRY(ctx->ensure(kSlotX64b, (size_t)op.lat.N * op.nc * W * 16));
-    double *xsol = (double *)ctx->at(kSlotX64b);
-    double *lsol = (double *)ctx->at(kSlotX64);
-    const double norm = noise_norm(ps->noise) / ps->nsamples;
     dp_solve_stats s{};
-    s.rhs_block = W;
-    const long long nblocks = (nrhs + W - 1) / W;
-    Staging stg;
-    DP_TRY(stg.init(ctx, nblocks, 2, 4 * (size_t)W));
-    std::vector<double> tj(2 * nrhs, 0.0), lx(2 * nrhs, 0.0);
-    long long k0 = 0;  // first block not yet drained
-    for (long long k = 0; k < nblocks; ++k) {
-        const long long r0 = k * W, nv = std::min<long long>(W, nrhs - r0);
-        BlockStats &bs1 = stg.stats(k, 0, (int)nv), &bs2 = stg.stats(k, 1, (int)nv);
-        InitProbe ix{&L, cfg.inner, make_gen(*ps, r0, nv, 0), &rd, &cs, ctx};
-        DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, xsol, ix, bs1, &s, stg.state(k, 0)));
-        launch_displaced_dot(L, make_gen(*ps, r0, nv, 0), p, xsol, rd, cs);
-        DP_HIP(hipMemcpyAsync(stg.result(k), cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost, stream));
-        InitProbe il{&L, cfg.inner, make_gen(*ps, r0, nv, p), &rd, &cs, ctx};
-        DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, lsol, il, bs2, &s, stg.state(k, 1)));
-        launch_dot(L, lsol, xsol, rd, cs);
-        DP_HIP(hipMemcpyAsync(stg.result(k) + 2 * W, cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost,
-                              stream));
-        if (dT_dU || dT_dUbar)
-            launch_force(L, xsol, lsol, op.nbr, norm, r0 == 0, (double *)dT_dU, (double *)dT_dUbar);
-        DP_HIP(hipGetLastError());
-        if (stg.drain_after(k, nblocks)) {
-            DP_HIP(hipStreamSynchronize(stream));
-            for (; k0 <= k; ++k0) {
-                const long long b0 = k0 * W, bn = std::min<long long>(W, nrhs - b0);
-                for (int i = 0; i < 2; ++i) block_stats(stg.state(k0, i), stg.stats(k0, i, -1), &s);
-                std::memcpy(tj.data() + 2 * b0, stg.result(k0), 2 * bn * sizeof(double));
-                std::memcpy(lx.data() + 2 * b0, stg.result(k0) + 2 * W, 2 * bn * sizeof(double));
+    DP_TRY(with_small(ctx, [&]() -> dp_status {
+        SolveCfg cfg = cfg0;
+        OpPrep op;
+        const int ndil = ps->dilute ? ps->nc : 1;
+        const long long nrhs = (long long)ps->nsamples * ps->ncolors * ndil;
+        int W = 1;
+        DP_TRY(plan_solve(ctx, *opd, nrhs, o->rhs_block, stream, cfg, op, W));
+        Launch L;
+        Red rd{};
+        CgState cs{};
+        DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
+        DP_TRY(ctx->ensure(kSlotX64b, (size_t)op.lat.N * op.nc * W * 16));
+        double *xsol = (double *)ctx->at(kSlotX64b);
+        double *lsol = (double *)ctx->at(kSlotX64);
+        const double norm = noise_norm(ps->noise) / ps->nsamples;
+        s = dp_solve_stats{};
+        s.rhs_block = W;
+        const long long nblocks = (nrhs + W - 1) / W;
+        Staging stg;
+        DP_TRY(stg.init(ctx, nblocks, 2, 4 * (size_t)W));
+        std::vector<double> tj(2 * nrhs, 0.0), lx(2 * nrhs, 0.0);
+        long long k0 = 0;  // first block not yet drained
+        for (long long k = 0; k < nblocks; ++k) {
+            const long long r0 = k * W, nv = std::min<long long>(W, nrhs - r0);
+            BlockStats &bs1 = stg.stats(k, 0, (int)nv), &bs2 = stg.stats(k, 1, (int)nv);
+            InitProbe ix{&L, cfg.inner, make_gen(*ps, r0, nv, 0), &rd, &cs, ctx};
+            DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, xsol, ix, bs1, &s, stg.state(k, 0)));
+            launch_displaced_dot(L, make_gen(*ps, r0, nv, 0), p, xsol, rd, cs);
+            DP_HIP(hipMemcpyAsync(stg.result(k), cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost, stream));
+            InitProbe il{&L, cfg.inner, make_gen(*ps, r0, nv, p), &rd, &cs, ctx};
+            DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, lsol, il, bs2, &s, stg.state(k, 1)));
+            launch_dot(L, lsol, xsol, rd, cs);
+            DP_HIP(hipMemcpyAsync(stg.result(k) + 2 * W, cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost,
+                                  stream));
+            if (dT_dU || dT_dUbar)
+                launch_force(L, xsol, lsol, op.nbr, norm, r0 == 0, (double *)dT_dU, (double *)dT_dUbar);
+            DP_HIP(hipGetLastError());
+            if (stg.drain_after(k, nblocks)) {
+                DP_HIP(hipStreamSynchronize(stream));
+                DP_TRY(small_check(ctx));
+                for (; k0 <= k; ++k0) {
+                    const long long b0 = k0 * W, bn = std::min<long long>(W, nrhs - b0);
+                    for (int i = 0; i < 2; ++i) block_stats(stg.state(k0, i), stg.stats(k0, i, -1), &s);
+                    std::memcpy(tj.data() + 2 * b0, stg.result(k0), 2 * bn * sizeof(double));
+                    std::memcpy(lx.data() + 2 * b0, stg.result(k0) + 2 * W, 2 * bn * sizeof(double));
+                }
             }
         }
-    }
-    DP_TRY(finish_profile(ctx, &s));
-    double Tr = 0, Ti = 0, gr = 0, gi = 0;
-    for (long long j = 0; j < nrhs; ++j) {
-        Tr += tj[2 * j];
-        Ti += tj[2 * j + 1];
-        gr += lx[2 * j];
-        gi += lx[2 * j + 1];
-    }
-    out->tr[0] = norm * Tr;
-    out->tr[1] = norm * Ti;
-    out->stderr_ = NAN;
-    if (out->per_rhs) std::memcpy(out->per_rhs, tj.data(), tj.size() * sizeof(double));
-    dT_dm2[0] = -norm * gr;
-    dT_dm2[1] = -norm * gi;
-    s.seconds = now_s() - t0;
+        DP_TRY(finish_profile(ctx, &s));
+        double Tr = 0, Ti = 0, gr = 0, gi = 0;
+        for (long long j = 0; j < nrhs; ++j) {
+            Tr += tj[2 * j];
+            Ti += tj[2 * j + 1];
+            gr += lx[2 * j];
+            gi += lx[2 * j + 1];
+        }
+        out->tr[0] = norm * Tr;
+        out->tr[1] = norm * Ti;
+        out->stderr_ = NAN;
+        if (out->per_rhs) std::memcpy(out->per_rhs, tj.data(), tj.size() * sizeof(double));
+        dT_dm2[0] = -norm * gr;
+        dT_dm2[1] = -norm * gi;
+        s.seconds = now_s() - t0;
+        return DP_OK;
+    }));
     out->solve = s;
     dp_status fs = final_status(s);
     if (fs == DP_ENOCONV) ctx->err = "trace_grad: some right-hand sides did not converge";
@@ -901,11 +925,11 @@ dp_status dp_trace_deflated(dp_ctx *ctx, const dp_operator *opd, const dp_deflat
         return DP_EINVAL;
     }
     const double t0 = now_s();
-    SolveCfg cfg;
-    DP_TRY(solve_cfg(ctx, o, cfg));
+    SolveCfg cfg0;
+    DP_TRY(solve_cfg(ctx, o, cfg0));
     DP_TRY(check_spec(ctx, *ps, opd));
     WorkStream ws_;
-    DP_TRY(ws_.enter(ctx, stream, cfg.use_graph));
+    DP_TRY(ws_.enter(ctx, stream, cfg0.use_graph));
     struct Leave {
         WorkStream &w;
         ~Leave() { (void)w.leave(); }
@@ -913,45 +937,51 @@ dp_status dp_trace_deflated(dp_ctx *ctx, const dp_operator *opd, const dp_deflat
     stream = ws_.s;
     double td[2] = {0.0, 0.0};
     DP_TRY(deflation_trace_part(ctx, *d, p, stream, td));
-    OpPrep op;
-    DP_TRY(prepare_operator(ctx, *opd, cfg.inner, op, stream));
-    const int ndil = ps->dilute ? ps->nc : 1;
-    const long long nrhs = (long long)ps->nsamples * ps->ncolors * ndil;
-    int W = 1;
-    DP_TRY(choose_width(ctx, op, cfg, nrhs, o->rhs_block, stream, W));
-    Launch L;
-    Red rd{};
-    CgState cs{};
-    DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
     dp_solve_stats s{};
-    s.rhs_block = W;
-    const long long nblocks = (nrhs + W - 1) / W;
-    Staging stg;
-    DP_TRY(stg.init(ctx, nblocks, 1, 2 * (size_t)W));
-    std::vector<double> tj(2 * nrhs, 0.0);
-    dp_status proj = DP_OK;
-    long long k0 = 0;  // first block not yet drained
-    for (long long k = 0; k < nblocks; ++k) {
-        const long long r0 = k * W, nv = std::min<long long>(W, nrhs - r0);
-        BlockStats &bs = stg.stats(k, 0, (int)nv);
-        InitDeflated init{&L, cfg.inner, make_gen(*ps, r0, nv, 0), &rd, &cs, ctx, d, &proj};
-        double *x64 = (double *)ctx->at(kSlotX64);
-        DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, x64, init, bs, &s, stg.state(k)));
-        DP_TRY(proj);
-        launch_displaced_dot(L, make_gen(*ps, r0, nv, 0), p, x64, rd, cs);
-        DP_HIP(hipGetLastError());
-        DP_HIP(hipMemcpyAsync(stg.result(k), cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost, stream));
-        if (stg.drain_after(k, nblocks)) {
-            DP_HIP(hipStreamSynchronize(stream));
-            for (; k0 <= k; ++k0) {
-                const long long b0 = k0 * W, bn = std::min<long long>(W, nrhs - b0);
-                block_stats(stg.state(k0), stg.stats(k0, 0, -1), &s);
-                std::memcpy(tj.data() + 2 * b0, stg.result(k0), 2 * bn * sizeof(double));
+    std::vector<double> tj;
+    DP_TRY(with_small(ctx, [&]() -> dp_status {
+        SolveCfg cfg = cfg0;
+        OpPrep op;
+        const int ndil = ps->dilute ? ps->nc : 1;
+        const long long nrhs = (long long)ps->nsamples * ps->ncolors * ndil;
+        int W = 1;
+        DP_TRY(plan_solve(ctx, *opd, nrhs, o->rhs_block, stream, cfg, op, W));
+        Launch L;
+        Red rd{};
+        CgState cs{};
+        DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
+        s = dp_solve_stats{};
+        s.rhs_block = W;
+        const long long nblocks = (nrhs + W - 1) / W;
+        Staging stg;
+        DP_TRY(stg.init(ctx, nblocks, 1, 2 * (size_t)W));
+        tj.assign(2 * nrhs, 0.0);
+        dp_status proj = DP_OK;
+        long long k0 = 0;  // first block not yet drained
+        for (long long k = 0; k < nblocks; ++k) {
+            const long long r0 = k * W, nv = std::min<long long>(W, nrhs - r0);
+            BlockStats &bs = stg.stats(k, 0, (int)nv);
+            InitDeflated init{&L, cfg.inner, make_gen(*ps, r0, nv, 0), &rd, &cs, ctx, d, &proj};
+            double *x64 = (double *)ctx->at(kSlotX64);
+            DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, x64, init, bs, &s, stg.state(k)));
+            DP_TRY(proj);
+            launch_displaced_dot(L, make_gen(*ps, r0, nv, 0), p, x64, rd, cs);
+            DP_HIP(hipGetLastError());
+            DP_HIP(hipMemcpyAsync(stg.result(k), cs.tj, 2 * nv * sizeof(double), hipMemcpyDeviceToHost, stream));
+            if (stg.drain_after(k, nblocks)) {
+                DP_HIP(hipStreamSynchronize(stream));
+                DP_TRY(small_check(ctx));
+                for (; k0 <= k; ++k0) {
+                    const long long b0 = k0 * W, bn = std::min<long long>(W, nrhs - b0);
+                    block_stats(stg.state(k0), stg.stats(k0, 0, -1), &s);
+                    std::memcpy(tj.data() + 2 * b0, stg.result(k0), 2 * bn * sizeof(double));
+                }
             }
         }
-    }
-    DP_TRY(finish_profile(ctx, &s));
-    s.seconds = now_s() - t0;
+        DP_TRY(finish_profile(ctx, &s));
+        s.seconds = now_s() - t0;
+        return DP_OK;
+    }));
     combine(*ps, tj, *out);
     out->tr[0] += td[0];
     out->tr[1] += td[1];

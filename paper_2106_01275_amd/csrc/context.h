@@ -29,7 +29,7 @@ namespace dp {
 
 enum Slot {
     kSlotNbr, kSlotU8, kSlotU8x, kSlotB64, kSlotX64, kSlotX64b, kSlotR, kSlotP, kSlotQ, kSlotQ64,
-    kSlotXLo, kSlotPart1, kSlotState, kSlotColors, kSlotVec, kSlotCmap, kNumSlots
+    kSlotXLo, kSlotPart1, kSlotState, kSlotColors, kSlotVec, kSlotCmap, kSlotSmall, kNumSlots
 };
 
 // A prepared operator: neighbour table and links in the internal layout.
@@ -48,6 +48,7 @@ struct BlockStats {
     long long iters_sum = 0;
     int iters_max = 0, nconv = 0, nbreak = 0, nvalid = 0, ru = 0;
     double max_rel = 0;
+    int small = 0;                // a small solve: its state counts the true-residual checks
     int it_mult = 1, it_cap = 0;  // reported iterations: state's count * it_mult, at most it_cap (0: no cap)
 };
 
@@ -89,6 +90,13 @@ struct dp_ctx {
     size_t pinned_bytes = 0;
     dp_status host_pinned(size_t bytes, void **out);  // at least `bytes`, kept for later calls
 
+    // small solves (k_small): the workgroups' tagged partial sums (device,
+    // zeroed once), the last tag given out, and whether a call's waits ran
+    // out, after which it is repeated with small_off
+    unsigned long long *small_part = nullptr;
+    unsigned small_tag = 0;
+    bool small_off = false, small_failed = false;
+
     // set while a call runs on the static scratch array (dp_solve_noalloc):
     // ensure() and pool_get() then fail instead of allocating or freeing
     bool no_alloc = false;
@@ -113,6 +121,8 @@ struct SolveCfg {
     int ru_gap = 100;     // a reliable update at least every ru_gap iterations (mixed)
     int profile = 0;
     int W = 0, logW = 0;
+    int small = 0;        // each block is one persistent launch (inner is then kF64)
+    int refine = 0;       // small, for a mixed-precision request: the true residual decides
 };
 
 // reduce: put the sites in even-odd order where the operator allows it (the
@@ -146,6 +156,36 @@ int max_launch_blocks(const Lat &lat, int W);
 // bytes of workspace slot `slot` that prepare_operator and make_launch need
 // for this operator, inner precision and width (0: the slot is not used)
 size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W);
+// the same for small solves; nring (>= 2) slots of the steps' vectors, between
+// whose uses the caches are dropped: few make that more frequent
+constexpr int kSmallRing = 8;
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int nring = kSmallRing);
+// Whether nrhs right-hand sides take the small solves (whatever the width).
+bool small_problem(const dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg);
+inline int pow2_above(long long n) {
+    int w = 1;
+    while (w < n) w *= 2;
+    return w;
+}
+// Chooses how nrhs right-hand sides of an operator are solved (small solves or
+// launched kernels, cfg.small) and the width, and prepares the operator.
+dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int requested, hipStream_t s, SolveCfg &cfg,
+                     OpPrep &op, int &W);
+// after a synchronisation: DP_EHIP, with ctx->small_failed set, when a small
+// solve gave up
+dp_status small_check(dp_ctx *ctx);
+// Runs f; when a small solve of it gave up, once more without them.
+template <typename F>
+dp_status with_small(dp_ctx *ctx, F f) {
+    ctx->small_failed = false;
+    dp_status st = f();
+    if (!ctx->small_failed) return st;
+    ctx->small_failed = false;
+    ctx->small_off = true;
+    st = f();
+    ctx->small_off = false;
+    return st;
+}
 dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launch &L, Red &rd, CgState &cs,
                       const SolveCfg &cfg);
 // the stencil launch (mode, workgroups) of L's shape: cached,
@@ -256,6 +296,12 @@ struct InitProbe {
     void operator()(const OpPrep &op, void *xlo, double *x64) const {
         launch_init_probe(*L, prec, g, init_args(ctx, op, xlo, x64, *rd, *cs));
     }
+    dp_status small_source(SmallArgs &a) const {
+        a.src = 0;
+        a.g = g;
+        a.nvalid = g.nvalid;
+        return DP_OK;
+    }
     const ProbeGen *probe() const { return &g; }  // b is these probes
     static constexpr bool kLanesNonzero = true;     // a probe has a site of its colour
 };
@@ -270,6 +316,13 @@ struct InitAbi {
     dp_ctx *ctx;
     void operator()(const OpPrep &op, void *xlo, double *x64) const {
         launch_init_abi(*L, prec, babi, rhs0, nvalid, init_args(ctx, op, xlo, x64, *rd, *cs));
+    }
+    dp_status small_source(SmallArgs &a) const {
+        a.src = 1;
+        a.b = babi;
+        a.rhs0 = rhs0;
+        a.nvalid = nvalid;
+        return DP_OK;
     }
     const ProbeGen *probe() const { return nullptr; }  // b is read back from b64
     static constexpr bool kLanesNonzero = false;       // the caller's b may be zero
@@ -302,6 +355,16 @@ struct InitDeflated {
         const dp_status e = deflate_rhs(ctx, *d, *L, z);
         if (e != DP_OK) *status = e;
         launch_init_b64(*L, prec, z, init_args(ctx, op, xlo, x64, *rd, *cs));
+    }
+    dp_status small_source(SmallArgs &a) const {
+        DP_TRY(ctx->ensure(kSlotB64, (size_t)L->lat.N * L->nc * L->W * 16));
+        double *z = (double *)ctx->at(kSlotB64);
+        launch_probe_fill(*L, g, z);
+        const dp_status e = deflate_rhs(ctx, *d, *L, z);
+        a.src = 2;
+        a.b = z;
+        a.nvalid = L->W;
+        return e;
     }
     const ProbeGen *probe() const { return nullptr; }
     static constexpr bool kLanesNonzero = true;  // (assumed; a zero lane only costs one group)

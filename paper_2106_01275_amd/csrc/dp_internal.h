@@ -281,6 +281,39 @@ void launch_force(const Launch &L, const double *x64, const double *l64, const i
 // control word
 void launch_ctrl(const Red &rd, const CgState &cs, int W, hipStream_t s);
 
+// A whole CG solve of one block in one persistent launch (small problems).
+// FP64 throughout.  b: generated probes (src 0), the caller's vectors (1), or
+// an FP64 block in index order (2).
+struct SmallArgs {
+    Lat lat;
+    int nc, W;
+    int wg, ngroups, nwg;    // lanes of a group (1, 2 or 4), groups, workgroups of a group
+    int ns;                  // sites CG runs on (the even half in even-odd order)
+    double c;                // m2 + 8
+    int links;
+    const double *U;         // FP64 hop links
+    const int *nbr;
+    int src;
+    ProbeGen g;
+    const double *b;
+    long long rhs0, nvalid;
+    double *x;               // solution, all sites [site][nc][W]
+    double *ring;            // [ngroups][nring][2] vectors of ns sites (r, p_o)
+    int nring;
+    size_t vec;              // complex numbers between vectors of the ring
+    unsigned long long *part;    // [2][ngroups][nwg][8][2] partial sums, tagged words
+    unsigned tag;            // of the launch's sums: the numbers from tag + 1 up
+    int max_steps, refine;   // refine: converged means the true residual meets tol
+    int polls;               // after which a wait gives up
+    int *err;                // set when a wait ran out
+    CgState cs;
+    int *nref;               // true-residual checks made (refine)
+};
+constexpr int kSmallThreads = 512;
+constexpr int kSmallMaxGrid = 256;       // one workgroup per CU
+constexpr size_t kSmallPartBytes = (size_t)2 * kSmallMaxGrid * 8 * 2 * 8;
+void launch_small(const SmallArgs &a, hipStream_t s);
+
 // Deflation (dense pieces over FP64 blocks [n rows][width], index order)
 // the probes of g, FP64, index order
 void launch_probe_fill(const Launch &L, const ProbeGen &g, double *out);

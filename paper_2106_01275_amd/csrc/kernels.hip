@@ -2335,6 +2335,474 @@ __global__ void k_b_ctrl(BatchLaunch B) {
     k_ctrl_body(d->cs, d->L.W);
 }
 
+// ============================================================ small solves
+//
+// k_small: the whole CG solve of a block in one launch, for problems whose
+// step is a few microseconds of work: with a launch per kernel a step of one
+// 8^4 x 3 right-hand side took 30 us for 16 us of kernels that each mostly
+// start, wait for memory and drain.  A group of workgroups (one per CU, all
+// resident) solves WG right-hand sides, several groups the lanes of a block
+// side by side, and the workgroups of a group meet at two sums per step:
+//   A   p = r + beta p, p_o = H p / c on the odd sites, with |p|^2 and
+//       |p_o|^2; p^H S p = c (|p|^2 - |p_o|^2), hence alpha
+//   B   q = c p - H p_o on the even sites, r -= alpha q, x += alpha p, with
+//       |r|^2, hence beta
+// (index order: A forms q = A p on every site with p^H q, B updates).
+//
+// Eight threads share a site, one per hop.  A thread keeps, for the whole
+// solve, the matrix of its hop into its odd and into its even site, and the
+// direction p at the even neighbour its odd site's hop comes from, which it
+// advances itself from r there: p is never stored.  The hop sums are
+// reduce-scattered over the eight threads (seven exchanges), after which
+// thread h holds real component h of the site and keeps that component of r,
+// p and x.  A step loads the neighbours' r and p_o and stores one component of
+// each, nothing else.
+//
+// After convergence x_o = (b_o + H x) / c and the true residual; with `refine`
+// (mixed-precision requests, whose stopping rule is the true residual) lanes
+// that miss the tolerance go on from it.
+//
+// Memory between workgroups.  Stores that others read go through agent-scope
+// atomics, past the L2 of their XCD, and have completed (s_waitcnt) before the
+// workgroup's partial sums are stored, which everyone waits for and which are
+// their own flags: each half of a double travels in a word with the number of
+// the sum (one more round trip for separate flags: 8.0 -> 7.5 us a step).
+// The vectors are loaded as usual, through the caches, which is coherent
+// because no address is loaded from a cache that may hold an older value:
+// every step writes its r and p_o to a slot of a ring that nothing has read
+// since the last agent-scope acquire (which drops the caches' lines: the start
+// of every launch is one, and there is one whenever the ring wraps), a
+// workgroup's share of a vector is whole 128-byte lines, and a slot is read
+// only after the sum that follows its writing.  (An acquire in every sum took
+// 9 us with 64 workgroups and 32 with 256: they queue at the XCD's L2.)
+// Every wait is bounded: should some workgroup not become resident (other
+// work holding the CUs), all give up, set *err and the host solves the block
+// with the launched kernels instead.
+
+__device__ __forceinline__ double ldc(const double *p) {
+    return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void stc(double *p, double v) {
+    __hip_atomic_store((unsigned long long *)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// v of the thread whose index differs in the bits of CTRL's permutation
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Sum of the eight threads' t[h] over an aligned group of eight threads, in
+// the thread with index h in the group.  Three halvings between threads i and
+// i ^ 7, i ^ 3, i ^ 1 (lane permutations inside the vector unit): each keeps
+// the half of its values that holds its own.
+__device__ __forceinline__ double reduce_scatter8(const double (&t)[8], int h) {
+    double u[4], w[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double keep = (h & 4) ? t[k + 4] : t[k], give = (h & 4) ? t[k] : t[k + 4];
+        u[k] = keep + dpp<0x141>(give);  // row_half_mirror: i ^ 7
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const double keep = (h & 2) ? u[k + 2] : u[k], give = (h & 2) ? u[k] : u[k + 2];
+        w[k] = keep + dpp<0x1B>(give);  // quad_perm 3, 2, 1, 0: i ^ 3
+    }
+    const double keep = (h & 1) ? w[1] : w[0], give = (h & 1) ? w[0] : w[1];
+    return keep + dpp<0xB1>(give);  // quad_perm 1, 0, 3, 2: i ^ 1
+}
+
+struct SmallShared {
+    double sm[kSmallThreads / 64][8];
+    double out[4];
+    int any;
+};
+
+// Sums over the workgroups of a group of the values v[k] (k < 2 WG), in a
+// fixed order (threads, wavefronts, workgroups), and a barrier among them.
+// Thread l < WG then calls step(v[2l], v[2l + 1]), the scalar part of lane l's
+// iteration (in every workgroup, with the same values), which returns what
+// every thread gets in out[l]; any: whether some lane's `active` is set after
+// it.  False when a wait ran out.
+template <int WG, typename F>
+__device__ __forceinline__ bool small_sum(const SmallArgs &A, SmallShared &sh, unsigned &tag, const double (&v)[8],
+                                          const int &active, F step, double (&out)[WG], int &any) {
+    const int tid = threadIdx.x, n = A.nwg, lane = tid & 63, wave = tid >> 6;
+    const int group = blockIdx.x % A.ngroups, wb = blockIdx.x / A.ngroups;
+    auto wave_sum = [&](double a) {  // a: value tid % 8
+        a += __shfl_xor(a, 8, 64);
+        a += __shfl_xor(a, 16, 64);
+        a += __shfl_xor(a, 32, 64);
+        if (lane < 8) sh.sm[wave][lane] = a;
+    };
+    auto total = [&]() {
+        double a = 0.0;
+        if (tid < 8)
+#pragma unroll
+            for (int k = 0; k < kSmallThreads / 64; ++k) a += sh.sm[k][tid];
+        return a;
+    };
+    ++tag;
+    wave_sum(reduce_scatter8(v, tid & 7));
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's stores have completed
+    __syncthreads();                     // and the workgroup's
+    unsigned long long *part = A.part + ((size_t)(tag & 1) * A.ngroups + group) * n * 16;
+    const unsigned long long mark = (unsigned long long)tag << 32;
+    if (tid < 8) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, total());
+        unsigned long long *e = part + ((size_t)wb * 8 + tid) * 2;
+        __hip_atomic_store(e, mark | (u & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(e + 1, mark | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    int good = 1;
+    double a = 0.0;
+    for (int w = tid >> 3; w < n; w += kSmallThreads >> 3) {
+        const unsigned long long *e = part + ((size_t)w * 8 + (tid & 7)) * 2;
+        unsigned long long lo = 0, hi = 0;
+        int k = 0;
+        for (; k < A.polls; ++k) {
+            lo = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            hi = __hip_atomic_load(e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((lo >> 32) == tag && (hi >> 32) == tag) break;
+        }
+        good &= k < A.polls;
+        a += __builtin_bit_cast(double, (hi << 32) | (lo & 0xffffffffull));
+    }
+    if (!__syncthreads_and(good)) return false;
+    wave_sum(a);
+    __syncthreads();
+    if (wave == 0) {
+        a = total();
+        const double t0 = __shfl(a, (2 * tid) & 63, 64), t1 = __shfl(a, (2 * tid + 1) & 63, 64);
+        if (tid < WG) sh.out[tid] = step(t0, t1);
+        const int some = __any(tid < WG && active);
+        if (tid == 0) sh.any = some;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < WG; ++l) out[l] = sh.out[l];
+    any = sh.any;
+    return true;
+}
+
+template <int NC, bool LINKS, bool EO, int WG>
+__global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
+    static_assert(2 * WG <= 8, "two sums per lane");
+    __shared__ SmallShared sh;
+    // with four lanes the matrices live in LDS ([element][thread], up to 144 KB
+    // of a CU's 160), where with them in registers 176 spilled; with fewer in
+    // registers (two lanes: 374 us a solve of 16 right-hand sides, 417 from LDS)
+    constexpr bool kLds = LINKS && WG > 2;
+    __shared__ double2 su[kLds ? (EO ? 2 : 1) * NC * NC * kSmallThreads : 1];
+    const int tid = threadIdx.x, h = tid & 7;
+    const int group = blockIdx.x % A.ngroups, wb = blockIdx.x / A.ngroups;
+    const int ns = A.ns, s = wb * (kSmallThreads / 8) + (tid >> 3);
+    const bool live = s < ns;
+    // this thread's component of its sites: colour ca, real or imaginary part
+    const bool own = live && h < 2 * NC;
+    const int ca = own ? h >> 1 : 0, im = h & 1;
+    const double c = A.c, ic = 1.0 / A.c;
+    const unsigned long long seedmix = A.src == 0 ? mix64(A.g.seed) : 0ull;
+    const CgState &cs = A.cs;
+    // the hops into site s (odd: site ns + s of the even-odd order): the
+    // neighbour's index in its half, and the matrix (conjugate transposed for
+    // a backward hop)
+    struct Hop {
+        int y;
+        double2 u[LINKS && !kLds ? NC * NC : 1];
+        double2 *lds;
+    };
+    auto load_hop = [&](int site, int half) {
+        Hop g{};
+        g.lds = su + (kLds ? half * NC * NC * kSmallThreads + tid : 0);
+        if (live) g.y = ldg(A.nbr + (size_t)site * 8 + h);
+        if (LINKS) {
+            const double2 *u = (const double2 *)A.U + ((size_t)(live ? site : 0) * 8 + h) * NC * NC;
+#pragma unroll
+            for (int a = 0; a < NC; ++a)
+#pragma unroll
+                for (int b = 0; b < NC; ++b) {
+                    double2 e = ldg(u + (h < 4 ? a * NC + b : b * NC + a));
+                    if (h >= 4) e.y = -e.y;
+                    if (kLds) g.lds[(a * NC + b) * kSmallThreads] = e;  // (read by this thread only)
+                    else g.u[a * NC + b] = e;
+                }
+        }
+        return g;
+    };
+    const Hop he = load_hop(s, 0), ho = EO ? load_hop(ns + s, 1) : he;
+    const int ye = EO ? he.y - ns : he.y, yo = ho.y;  // (an even site's neighbours are odd)
+    // component `own` of the sum over the hops of U v
+    auto hop_sum = [&](const Hop &g, const double2 (&v)[NC]) {
+        double t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            if (!LINKS) {
+                t[2 * a] = v[a].x;
+                t[2 * a + 1] = v[a].y;
+                continue;
+            }
+#pragma unroll
+            for (int b = 0; b < NC; ++b) {
+                const double2 e = kLds ? g.lds[(a * NC + b) * kSmallThreads] : g.u[kLds ? 0 : a * NC + b];
+                t[2 * a] = fma(e.x, v[b].x, fma(-e.y, v[b].y, t[2 * a]));
+                t[2 * a + 1] = fma(e.x, v[b].y, fma(e.y, v[b].x, t[2 * a + 1]));
+            }
+        }
+        return reduce_scatter8(t, h);
+    };
+    // vectors of the group's ring: element (site of a half, colour, lane l)
+    double2 *ring = (double2 *)A.ring + (size_t)group * A.nring * 2 * A.vec;
+    auto Rk = [&](int k) { return ring + (size_t)(2 * k) * A.vec; };
+    auto Wk = [&](int k) { return ring + (size_t)(2 * k + 1) * A.vec; };
+    auto publish = [&](double2 *v, int l, double x) {
+        if (own) stc((double *)(v + ((size_t)(s * NC + ca) * WG + l)) + im, x);
+    };
+    auto gather = [&](const double2 *v, int y, int l, double2 (&out)[NC]) {
+#pragma unroll
+        for (int b = 0; b < NC; ++b)
+            out[b] = live ? ldg(v + ((size_t)(y * NC + b) * WG + l)) : make_double2(0.0, 0.0);
+    };
+
+    unsigned tag = A.tag;
+    int cur = 0;
+    double v[8], out[WG];
+    auto give_up = [&]() {
+        if (tid == 0) *A.err = 1;
+    };
+    auto advance = [&]() {
+        cur = cur + 1 < A.nring ? cur + 1 : 0;
+        // the slots are read a second time from here on
+        if (cur == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    };
+    // blocks of WG lanes, the group's share of the W lanes in turn
+    for (int l0 = group * WG; l0 < A.W; l0 += A.ngroups * WG) {
+        // b at a site (of the internal order), colour a, lane l of this block
+        auto b_at = [&](int site, int a, int l) {
+            double re = 0.0, bi = 0.0;
+            const int x = lex_of(A.lat, site), j = l0 + l;
+            if (j < A.nvalid) {
+                if (A.src == 0) {
+                    const ProbeLane pl = probe_lane(A.g, NC, A.g.rhs0 + j);
+                    probe_at(A.g, seedmix, A.lat, NC, pl, x, a, re, bi);
+                } else {
+                    const double2 t = ldg((const double2 *)A.b +
+                                          (A.src == 1 ? ((size_t)(A.rhs0 + j) * A.lat.N + x) * NC + a
+                                                      : (size_t)(x * NC + a) * A.W + j));
+                    re = t.x;
+                    bi = t.y;
+                }
+            }
+            return make_double2(re, bi);
+        };
+        auto b_own = [&](int site, int l) {
+            if (!own) return 0.0;
+            const double2 t = b_at(site, ca, l);
+            return im ? t.y : t.x;
+        };
+        // own components, and p at the neighbour of the A phase's hop
+        double r[WG], p[WG], x[WG], q[WG];
+        double2 pn[WG][NC];
+        int it = 0, nref = 0, any;
+        // the scalars of lane l, in thread l
+        double rr = 0.0, bb = 0.0, rr_first = 0.0, true_rr = 0.0;
+        int active = 0, flags = 0, iters = 0;
+        const auto none = [](double, double) { return 0.0; };
+        const auto clear = [&]() {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = 0.0;
+        };
+        // the top of an iteration: a lane that meets the tolerance stops
+        const auto check = [&]() {
+            if (active && rr <= cs.tol2 * bb) {
+                active = 0;
+                flags |= kFlagConverged;
+            }
+        };
+
+        // first residual, |r|^2 and |b|^2
+        clear();
+#pragma unroll
+        for (int l = 0; l < WG; ++l) {
+            r[l] = b_own(s, l);
+            v[2 * l + 1] = r[l] * r[l];
+            if (EO) {
+                const double bo = b_own(ns + s, l);
+                v[2 * l + 1] += bo * bo;
+                double2 t[NC];
+#pragma unroll
+                for (int b = 0; b < NC; ++b) t[b] = live ? b_at(he.y, b, l) : make_double2(0.0, 0.0);
+                const double g = hop_sum(he, t);
+                if (own) r[l] = fma(ic, g, r[l]);
+            }
+            v[2 * l] = r[l] * r[l];
+            p[l] = x[l] = 0.0;
+#pragma unroll
+            for (int b = 0; b < NC; ++b) pn[l][b] = make_double2(0.0, 0.0);
+            publish(Rk(cur), l, r[l]);
+        }
+        double beta[WG];
+        if (!small_sum<WG>(A, sh, tag, v, active,
+                           [&](double t0, double t1) {
+                               rr = rr_first = t0;
+                               bb = t1;
+                               active = bb > 0.0;
+                               flags = active ? 0 : kFlagConverged;
+                               check();
+                               return 0.0;
+                           },
+                           beta, any))
+            return give_up();
+        for (;;) {
+            while (any && it < A.max_steps) {  // (the same in every thread of the group)
+                ++it;
+                // A
+                clear();
+#pragma unroll
+                for (int l = 0; l < WG; ++l) {
+                    double2 t[NC];
+                    gather(Rk(cur), yo, l, t);
+#pragma unroll
+                    for (int b = 0; b < NC; ++b) {
+                        pn[l][b].x = fma(beta[l], pn[l][b].x, t[b].x);
+                        pn[l][b].y = fma(beta[l], pn[l][b].y, t[b].y);
+                    }
+                    const double g = hop_sum(ho, pn[l]);
+                    p[l] = fma(beta[l], p[l], r[l]);
+                    if (EO) {
+                        const double po = ic * g;
+                        publish(Wk(cur), l, po);
+                        v[2 * l] = p[l] * p[l];
+                        v[2 * l + 1] = own ? po * po : 0.0;
+                    } else {
+                        q[l] = fma(c, p[l], -g);
+                        v[2 * l] = own ? p[l] * q[l] : 0.0;
+                    }
+                }
+                double alpha[WG];
+                if (!small_sum<WG>(A, sh, tag, v, active,
+                                   [&](double t0, double t1) {
+                                       const double pq = EO ? c * (t0 - t1) : t0;
+                                       if (!active) return 0.0;
+                                       if (!(pq > 0.0) || !isfinite(pq)) {
+                                           active = 0;
+                                           if (!A.refine) flags |= kFlagBreakdown;
+                                           return 0.0;
+                                       }
+                                       ++iters;
+                                       return rr / pq;
+                                   },
+                                   alpha, any))
+                    return give_up();
+                // B
+                const int next = cur + 1 < A.nring ? cur + 1 : 0;
+                clear();
+#pragma unroll
+                for (int l = 0; l < WG; ++l) {
+                    if (EO) {
+                        double2 t[NC];
+                        gather(Wk(cur), ye, l, t);
+                        q[l] = fma(c, p[l], -hop_sum(he, t));
+                    }
+                    if (own) {
+                        r[l] = fma(-alpha[l], q[l], r[l]);
+                        x[l] = fma(alpha[l], p[l], x[l]);
+                    }
+                    publish(Rk(next), l, r[l]);
+                    v[2 * l] = r[l] * r[l];
+                }
+                if (!small_sum<WG>(A, sh, tag, v, active,
+                                   [&](double t0, double) {
+                                       if (!active) return 0.0;
+                                       const double f = t0 / rr;
+                                       rr = t0;
+                                       check();
+                                       return active ? f : 0.0;
+                                   },
+                                   beta, any))
+                    return give_up();
+                advance();
+            }
+            // the odd half of x, then the true residual; x_e takes the place
+            // of the r that no one has read
+#pragma unroll
+            for (int l = 0; l < WG; ++l) publish(Rk(cur), l, x[l]);
+            clear();
+            if (!small_sum<WG>(A, sh, tag, v, active, none, out, any)) return give_up();
+            if (EO) {
+#pragma unroll
+                for (int l = 0; l < WG; ++l) {
+                    double2 t[NC];
+                    gather(Rk(cur), yo, l, t);
+                    const double g = hop_sum(ho, t);
+                    const double xo = ic * (b_own(ns + s, l) + g);
+                    publish(Wk(cur), l, xo);
+                    if (own && l0 + l < A.W) A.x[2 * ((size_t)((ns + s) * NC + ca) * A.W + l0 + l) + im] = xo;
+                }
+                if (!small_sum<WG>(A, sh, tag, v, active, none, out, any)) return give_up();
+            }
+            const int next = cur + 1 < A.nring ? cur + 1 : 0;
+#pragma unroll
+            for (int l = 0; l < WG; ++l) {
+                double2 t[NC];
+                gather(EO ? Wk(cur) : Rk(cur), ye, l, t);
+                const double g = hop_sum(he, t);
+                const double rt = own ? b_own(s, l) - fma(c, x[l], -g) : 0.0;
+                v[2 * l] = rt * rt;
+                if (A.refine) {
+                    r[l] = rt;
+                    publish(Rk(next), l, rt);
+                }
+            }
+            ++nref;
+            if (!small_sum<WG>(A, sh, tag, v, active,
+                               [&](double t0, double) {
+                                   true_rr = t0;
+                                   if (!A.refine) {
+                                       active = 0;  // (done; flags and iters stay)
+                                       return 0.0;
+                                   }
+                                   // the true residual decides: a lane that misses the tolerance goes on
+                                   rr = t0;
+                                   if (t0 <= cs.tol2 * bb) {
+                                       flags |= kFlagConverged;
+                                       active = 0;
+                                   } else if (flags & kFlagConverged) {
+                                       flags &= ~kFlagConverged;
+                                       active = 1;
+                                   }
+                                   return 0.0;
+                               },
+                               beta, any))
+                return give_up();
+            advance();
+            if (!any || it >= A.max_steps) break;
+        }
+#pragma unroll
+        for (int l = 0; l < WG; ++l)
+            if (own && l0 + l < A.W) A.x[2 * ((size_t)(s * NC + ca) * A.W + l0 + l) + im] = x[l];
+        if (wb == 0 && tid < WG && l0 + tid < A.W) {
+            const int j = l0 + tid;
+            cs.rr[j] = rr;
+            cs.qp[j] = 0.0;
+            cs.rr_ref[j] = rr_first;
+            cs.bb[j] = bb;
+            cs.alpha[j] = 0.0;
+            cs.beta[j] = 0.0;
+            cs.true_rr[j] = true_rr;
+            cs.active[j] = active;
+            cs.iters[j] = iters;
+            cs.flags[j] = flags;
+            if (j == 0) *A.nref = A.refine ? nref : 0;
+        }
+    }
+}
+
 // ============================================================ deflation
 //
 // Dense pieces of the deflated estimator (Sec. Deflation) on blocks of FP64
@@ -2865,6 +3333,30 @@ void launch_force(const Launch &L, const double *x64, const double *l64, const i
     const long long n = (long long)L.lat.N * 4 * L.nc * L.nc;
     k_force<<<blocks_for(n), kBlock, 0, L.stream>>>(L, (const double2 *)x64, (const double2 *)l64, nbr, scale,
                                                     first, (double2 *)dU, (double2 *)dUbar);
+}
+
+template <int NC, bool LINKS, bool EO>
+static void small_t(const SmallArgs &a, hipStream_t s) {
+    const int grid = a.nwg * a.ngroups;
+    switch (a.wg) {
+        case 1: k_small<NC, LINKS, EO, 1><<<grid, kSmallThreads, 0, s>>>(a); break;
+        case 2: k_small<NC, LINKS, EO, 2><<<grid, kSmallThreads, 0, s>>>(a); break;
+        default: k_small<NC, LINKS, EO, 4><<<grid, kSmallThreads, 0, s>>>(a); break;
+    }
+}
+
+void launch_small(const SmallArgs &a, hipStream_t s) {
+    if (a.nc == 3) {
+        if (a.links)
+            a.lat.eo ? small_t<3, true, true>(a, s) : small_t<3, true, false>(a, s);
+        else
+            a.lat.eo ? small_t<3, false, true>(a, s) : small_t<3, false, false>(a, s);
+    } else {
+        if (a.links)
+            a.lat.eo ? small_t<1, true, true>(a, s) : small_t<1, true, false>(a, s);
+        else
+            a.lat.eo ? small_t<1, false, true>(a, s) : small_t<1, false, false>(a, s);
+    }
 }
 
 void launch_to_abi(const Launch &L, const double *x64, double *xabi, long long rhs0, long long nvalid) {

@@ -60,10 +60,10 @@ struct ScratchSlots {
 
 // Scratch bytes of a solve at width W (the slots that prepare_operator and
 // make_launch take; the colour slot of the autotuner is never used here).
-size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots]) {
+size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots], int nring = 0) {
     size_t tot = 0;
     for (int s = 0; s < kNumSlots; ++s) {
-        bytes[s] = slot_size(s, lat, nc, links, inner, W);
+        bytes[s] = nring ? small_slot_size(s, lat, nc, links, W, nring) : slot_size(s, lat, nc, links, inner, W);
         tot += align256(bytes[s]);
     }
     return tot;
@@ -174,10 +174,31 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
             return DP_EINVAL;
         }
     }
+    // small solves (one persistent launch per block, FP64) where they apply
+    // and their workspace fits too
+    const SolveCfg cfg0 = cfg;
+    Lat red = lat;
+    red.eo = eo_reducible(lat.D, op->m2);
+    size_t plain_bytes[kNumSlots];
+    std::memcpy(plain_bytes, bytes, sizeof bytes);
     const double t0 = std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
     dp_solve_stats s{};
-    s.rhs_block = W;
-    {
+    DP_TRY(with_small(ctx, [&]() -> dp_status {
+        SolveCfg cfg = cfg0;
+        std::memcpy(bytes, plain_bytes, sizeof bytes);
+        if (small_problem(ctx, red, op->nc, nrhs, cfg)) {
+            int nring = kSmallRing;
+            while (nring > 2 && layout(red, op->nc, links, kF64, W, bytes, nring) > kScratchBytes) --nring;
+            if (layout(red, op->nc, links, kF64, W, bytes, nring) <= kScratchBytes) {
+                cfg.small = 1;
+                cfg.refine = cfg.inner != kF64;
+                cfg.inner = kF64;
+            } else {
+                std::memcpy(bytes, plain_bytes, sizeof bytes);
+            }
+        }
+        s = dp_solve_stats{};
+        s.rhs_block = W;
         ScratchSlots scope(ctx, (char *)base, bytes);
         OpPrep opp;
         DP_TRY(prepare_operator(ctx, *op, cfg.inner, opp, stream));
@@ -201,7 +222,8 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
             DP_HIP(hipGetLastError());
         }
         DP_HIP(hipStreamSynchronize(stream));
-    }
+        return DP_OK;
+    }));
     s.seconds =
         std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count() - t0;
     if (st) *st = s;

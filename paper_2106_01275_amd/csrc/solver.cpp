@@ -218,6 +218,148 @@ size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W)
     }
 }
 
+// ---------------------------------------------------------------- small solves
+
+// DP_SMALL=0 solves every problem with the launched kernels (for comparison)
+static bool small_enabled() {
+    const char *e = std::getenv("DP_SMALL");
+    return !(e && std::strcmp(e, "0") == 0);
+}
+
+// Workgroups of a group, lanes of a group and groups for n lanes side by side
+struct SmallShape {
+    int nwg, wg, ngroups;
+};
+static SmallShape small_shape(const Lat &lat, long long n) {
+    SmallShape z;
+    const long long ns = lat.eo ? lat.N / 2 : lat.N;
+    z.nwg = (int)((ns + kSmallThreads / 8 - 1) / (kSmallThreads / 8));
+    const int fit = std::max(1, kSmallMaxGrid / z.nwg);  // groups that are resident together
+    z.wg = n <= fit ? 1 : (n <= 2 * fit ? 2 : 4);
+    z.ngroups = (int)std::min<long long>(fit, (n + z.wg - 1) / z.wg);
+    return z;
+}
+
+bool small_problem(const dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg) {
+    const long long ns = lat.eo ? lat.N / 2 : lat.N;
+    if (ctx->small_off || cfg.profile || nrhs < 1 || ns > kSmallMaxGrid * (kSmallThreads / 8) || !small_enabled())
+        return false;
+    // microseconds per CG step of all right-hand sides: a small solve's rounds
+    // one after another, against the launched kernels' latency and traffic.
+    // Measured (FP64, 8^4 x 3, per step): one right-hand side 7.6 us (launched
+    // 23), 8 (one a group) 10 (29), 16 (two) 12 (30), 32 (four) 19 (33), 64
+    // (two rounds of four) 39 (37); odd extents 9 x 10 x 7 x 12: one 7.7 (19),
+    // 8 (four) 14 (23), 20 (three rounds) 30 (30)
+    const SmallShape z = small_shape(lat, nrhs);
+    const long long rounds = (nrhs + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
+    const double base = lat.eo ? (z.wg == 1 ? 8.5 : (z.wg == 2 ? 12.0 : 19.0))
+                               : (z.wg == 1 ? 8.0 : (z.wg == 2 ? 10.0 : 13.0));
+    const double bytes = (double)ns * nrhs * nc * prec_bytes(cfg.inner) * (lat.eo ? 12.0 : 9.0);
+    return rounds * (base + 0.015 * z.nwg) < 21.0 + bytes / 4.5e6;
+}
+
+// one slot of the groups' rings (r and p_o of a step), whose vectors start on
+// 256-byte boundaries
+static size_t small_vec(const Lat &lat, int nc, const SmallShape &z) {
+    return ((size_t)(lat.eo ? lat.N / 2 : lat.N) * nc * z.wg + 15) / 16 * 16;
+}
+static size_t small_ring_bytes(const Lat &lat, int nc, const SmallShape &z) {
+    return (size_t)z.ngroups * 2 * 16 * small_vec(lat, nc, z);
+}
+
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int nring) {
+    switch (slot) {
+        case kSlotR:
+        case kSlotQ:
+        case kSlotP:
+        case kSlotB64:
+        case kSlotQ64:
+        case kSlotXLo:
+        case kSlotU8x: return 0;
+        case kSlotSmall: return nring * small_ring_bytes(lat, nc, small_shape(lat, W));
+        default: return slot_size(slot, lat, nc, links, kF64, W);
+    }
+}
+
+dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int requested, hipStream_t s, SolveCfg &cfg,
+                     OpPrep &op, int &W) {
+    Lat lat{};
+    long long N = 1;
+    for (int d = 0; d < 4; ++d) {
+        lat.D[d] = opd.dims[d];
+        N = opd.dims[d] >= 1 && N <= (1LL << 30) ? N * opd.dims[d] : 1LL << 40;
+    }
+    if (N <= (1LL << 24)) {
+        lat.N = (int)N;
+        lat.eo = eo_reducible(lat.D, opd.m2);
+        const int w = requested != 0 ? requested : pow2_above(std::min<long long>(nrhs, kMaxW));
+        if (w > 0 && w <= kMaxW && (w & (w - 1)) == 0 && small_problem(ctx, lat, opd.nc, nrhs, cfg)) {
+            cfg.small = 1;
+            cfg.refine = cfg.inner != kF64;
+            cfg.inner = kF64;
+            W = w;
+            return prepare_operator(ctx, opd, cfg.inner, op, s);
+        }
+    }
+    DP_TRY(prepare_operator(ctx, opd, cfg.inner, op, s));
+    return choose_width(ctx, op, cfg, nrhs, requested, s, W);
+}
+
+dp_status small_check(dp_ctx *ctx) {
+    if (!ctx->ctrl_host[12]) return DP_OK;
+    ctx->ctrl_host[12] = 0;
+    ctx->small_failed = true;
+    ctx->err = "internal: a persistent solve did not become resident";
+    return DP_EHIP;
+}
+
+// one block as one launch; the block's state is complete when it ends
+template <typename Init>
+static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const Launch &L, const CgState &cs,
+                             double *x64, const Init &init, int max_steps) {
+    SmallArgs a{};
+    const SmallShape z = small_shape(op.lat, L.W);
+    a.lat = op.lat;
+    a.nc = op.nc;
+    a.W = L.W;
+    a.wg = z.wg;
+    a.ngroups = z.ngroups;
+    a.nwg = z.nwg;
+    a.ns = L.ns;
+    a.c = op.m2 + 8.0;
+    a.links = op.links;
+    a.U = (const double *)op.U8;
+    a.nbr = op.nbr;
+    DP_TRY(init.small_source(a));
+    a.x = x64;
+    a.part = ctx->small_part;
+    a.ring = (double *)ctx->at(kSlotSmall);
+    a.vec = small_vec(op.lat, op.nc, z);
+    a.nring = (int)std::min<size_t>(kSmallRing, ctx->slot_bytes[kSlotSmall] / small_ring_bytes(op.lat, op.nc, z));
+    // the sums of this launch: two a step and a few for each closing residual,
+    // for every round of lanes (numbers that start over only over cleared words)
+    const unsigned long long rounds = (L.W + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
+    const unsigned long long sums = rounds * (6ull * (unsigned)max_steps + 8);
+    if (ctx->small_tag + sums >= 0xffffffffull) {
+        DP_HIP(hipStreamSynchronize(L.stream));
+        DP_HIP(hipMemset(ctx->small_part, 0, kSmallPartBytes));
+        ctx->small_tag = 0;
+    }
+    a.tag = ctx->small_tag;
+    ctx->small_tag += (unsigned)std::min<unsigned long long>(sums, 0x40000000ull);
+    a.max_steps = max_steps;
+    a.refine = cfg.refine;
+    // a wait gives up after some 0.2 s (DP_SMALL_POLLS: tests)
+    const char *polls = std::getenv("DP_SMALL_POLLS");
+    a.polls = polls ? std::atoi(polls) : 400000;
+    a.err = ctx->ctrl_dev + 12;
+    a.cs = cs;
+    a.nref = cs.flags + kMaxW;  // the first spare int of the state block
+    launch_small(a, L.stream);
+    DP_HIP(hipGetLastError());
+    return DP_OK;
+}
+
 dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep &out, hipStream_t s, bool reduce) {
     for (int d = 0; d < 4; ++d)
         if (op.dims[d] < 1) {
@@ -413,9 +555,13 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     L.stream = s;
     L.smode = -1;
     for (int slot : {kSlotB64, kSlotX64, kSlotR, kSlotP, kSlotQ, kSlotQ64, kSlotXLo, kSlotPart1, kSlotState}) {
-        const size_t b = slot_size(slot, op.lat, op.nc, op.links, cfg.inner, W);
+        const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W)
+                                   : slot_size(slot, op.lat, op.nc, op.links, cfg.inner, W);
         if (b) DP_TRY(ctx->ensure(slot, b));
     }
+    // (the scratch of a call that may not allocate holds as many ring slots as fit)
+    if (cfg.small && !ctx->no_alloc)
+        DP_TRY(ctx->ensure(kSlotSmall, small_slot_size(kSlotSmall, op.lat, op.nc, op.links, W)));
     const size_t nd = kStateDoubles;
     double *d = (double *)ctx->at(kSlotState);
     cs.rr = d;
@@ -442,7 +588,7 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     cs.rq_direct = cfg.inner == kBF16;  // see the finishing kernel
     cs.exact = cfg.inner == kF64;
     cs.ru_restart = cfg.inner == kBF16 && op.lat.eo;
-    DP_TRY(pick_stencil(ctx, op, cfg, L, cs));
+    if (!cfg.small) DP_TRY(pick_stencil(ctx, op, cfg, L, cs));
     rd.part1 = (double *)ctx->at(kSlotPart1);
     rd.part2 = rd.part1 + (size_t)L.nblk * W * 4;
     rd.nblk = L.nblk;
@@ -588,7 +734,7 @@ void block_stats(const void *state, BlockStats &bs, dp_solve_stats *acc) {
         acc->max_iters = std::max(acc->max_iters, bs.iters_max);
         acc->nconverged += bs.nconv;
         acc->nbreakdown += bs.nbreak;
-        acc->reliable_updates += bs.ru;
+        acc->reliable_updates += bs.small ? iv[3 * kMaxW] : bs.ru;
         acc->max_true_resid = std::max(acc->max_true_resid, bs.max_rel);
         acc->nrhs += bs.nvalid;
     }
@@ -691,6 +837,21 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     void *r = ctx->at(kSlotR), *p = ctx->at(kSlotP), *q = ctx->at(kSlotQ);
     const double *b64 = (const double *)ctx->at(kSlotB64);
     const double diag = op.m2 + 8.0;
+    if (cfg.small) {
+        bs.small = 1;
+        bs.it_mult = op.lat.eo ? 2 : 1;
+        bs.it_cap = op.lat.eo ? cfg.max_iter : 0;
+        DP_TRY(small_block(ctx, op, cfg, L, cs, x64, init, (cfg.max_iter + bs.it_mult - 1) / bs.it_mult));
+        if (defer) {
+            DP_HIP(hipMemcpyAsync(defer, cs.rr, state_bytes(), hipMemcpyDeviceToHost, L.stream));
+            return DP_OK;
+        }
+        DP_HIP(hipMemcpyAsync(ctx->state_host, cs.rr, state_bytes(), hipMemcpyDeviceToHost, L.stream));
+        DP_HIP(hipStreamSynchronize(L.stream));
+        DP_TRY(small_check(ctx));
+        block_stats(ctx->state_host, bs, acc);
+        return DP_OK;
+    }
     init(op, xlo, x64);  // b, r = p = b (even-odd: b_e + H b_o / c), xlo = 0 (x64 = 0)
     DP_HIP(hipGetLastError());
     int nactive = bs.nvalid;

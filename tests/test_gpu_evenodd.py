@@ -2,7 +2,8 @@
 oracle's FP64 CG on the whole operator: extents of 2 (both hops of a
 direction reach the same site), slabs of one and several x0-slices, part
 tiles, every kind of block width, right-hand sides supported on one parity
-only, and a zero one.  Solutions to the bars of the other solve tests: 1e-10
+only, and a zero one; with the launched kernels (DP_SMALL=0) and, for these
+small lattices, one persistent launch per block.  Solutions to the bars of the other solve tests: 1e-10
 (FP64 to 1e-12), 1e-8 (mixed to 1e-10)."""
 import sys
 
@@ -52,8 +53,10 @@ def _rhs(dims, nc, n, seed):
                                                    ((8, 2, 4, 6), 1, True, 33, 32), ((16, 2, 2, 4), 3, True, 40, 32),
                                                    ((8, 4, 4, 2), 3, False, 70, 64), ((4, 4, 2, 4), 3, True, 130, 128)])
 @pytest.mark.parametrize("inner", ["f64", "f32", "bf16"])
-def test_reduced_solve_matches_oracle(ctx, inner, dims, nc, links, n, block):
-    _say("even-odd solve", inner, dims, nc, links, n, block)
+@pytest.mark.parametrize("small", ["0", "1"])
+def test_reduced_solve_matches_oracle(ctx, monkeypatch, small, inner, dims, nc, links, n, block):
+    _say("even-odd solve", inner, dims, nc, links, n, block, "small", small)
+    monkeypatch.setenv("DP_SMALL", small)
     U = workloads.random_links(dims, 0.4, 5, nc) if links else None
     B = _rhs(dims, nc, n, 3)
     op = ctx.operator(dims, nc, 0.2, None if U is None else cuda(U))
@@ -89,9 +92,11 @@ def test_batch_of_even_and_odd_extents(ctx, inner):
     assert all(torch.all(z == 0) for z in Zs) and all(s["nconverged"] == 1 for s in sts)
 
 
-def test_reduced_failure_statuses(ctx):
+@pytest.mark.parametrize("small", ["0", "1"])
+def test_reduced_failure_statuses(ctx, monkeypatch, small):
     """An indefinite operator breaks down and an iteration limit is kept, as
     on the whole operator."""
+    monkeypatch.setenv("DP_SMALL", small)
     dims = (4, 4, 2, 4)
     B = cuda(_rhs(dims, 3, 5, 9)[3:])
     U = cuda(workloads.random_links(dims, 0.2, 2))
