@@ -79,6 +79,9 @@ struct dp_ctx {
     std::array<int, 2> stencil_forced{{-1, 0}};
     bool tune_loaded = false;
     int check_every = 8;
+    // decay of ln |r|^2 per CG step of the prepared operator (single instance),
+    // measured between host checks; 0: none yet
+    double pace = 0;
     hipStream_t gstream = nullptr;            // library stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     std::map<std::string, hipGraphExec_t> graphs;  // iteration groups by length and kernel arguments
@@ -250,6 +253,8 @@ double stencil_alg_bytes(const Launch &L, int prec, bool links, int kind);
 // needs to be due a reliable update, both from the slowest lane's decay of
 // |r|^2 over the last dit iterations (ratio_prev -> ratio); dflt without one.
 int next_check(int dflt, double ratio, double ratio_prev, int dit, double ru_ratio);
+// The same for a single instance whose pace is known: 1..32 steps.
+int plan_steps(double pace, double ratio, double ratio_ref, double ru_ratio, int inner);
 
 // Work stream of a call: the caller's stream, or (graph replay requested)
 // the library's own stream, ordered after the caller's stream on entry and

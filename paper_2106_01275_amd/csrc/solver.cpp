@@ -390,6 +390,7 @@ dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep
     out.m2 = op.m2;
     out.links = op.links != nullptr;
     out.inner = inner;
+    ctx->pace = 0;
     auto sz = [&](int slot) { return slot_size(slot, out.lat, op.nc, out.links, inner, 1); };
     DP_TRY(ctx->ensure(kSlotNbr, sz(kSlotNbr)));
     out.nbr = (const int *)ctx->at(kSlotNbr);
@@ -609,6 +610,28 @@ int next_check(int dflt, double ratio, double ratio_prev, int dit, double ru_rat
         if (ru_ratio > 1.0) next = std::min(next, (int)std::ceil(std::log(ru_ratio) / per_it));
     }
     return std::min(16, std::max(2, next));
+}
+
+// Steps until the next check, from the pace: what the slowest lane needs to
+// reach tol (ratio = |r|^2 / (tol^2 |b|^2) of it), with BF16 storage at most
+// what the first lane needs to be due its reliable update, and with FP32
+// storage at most what the present cycle should gain.  FP32 follows the true
+// residual over about six digits (then the recursive residual runs on alone,
+// and its steps are lost), and a reliable update costs about two steps: the
+// way to tol since the last update (ratio_ref) is taken in the fewest equal
+// cycles of at most six digits.  (16^4, 1e-11: 27 steps and three updates a
+// block became 23 and two.)  The last step of a mixed-precision cycle aims a
+// little below tol: a lane that misses it costs another update.
+int plan_steps(double pace, double ratio, double ratio_ref, double ru_ratio, int inner) {
+    const double margin = inner == kF64 ? 0.0 : 2.0 * std::log(1.25), cycle = 2.0 * std::log(1e6);
+    double left = std::log(std::max(ratio, 1.0)) + margin;
+    if (inner == kBF16 && ru_ratio > 1.0) left = std::min(left, std::log(ru_ratio));
+    if (inner == kF32) {
+        const double whole = std::log(std::max(ratio_ref, 1.0)) + margin;
+        const double n = std::max(1.0, std::ceil(whole / cycle - 0.05));
+        left = std::min(left, whole / n - std::log(std::max(ratio_ref / ratio, 1.0)));
+    }
+    return std::min(32, std::max(1, (int)std::ceil(left / pace - 1e-6)));
 }
 
 // Update mode of iteration c of a group of n: pairs (1, 2) of a deferred
@@ -881,7 +904,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     const int check_every = std::max(1, ctx->check_every / mult);
     // Iterations between host checks: start with check_every, then predict
     // from the decay of the slowest lane's residual since the last check.
-    int steps_next = check_every;
+    const double delta2 = cs.delta2, start = 1.0 / (cfg.tol * cfg.tol);
+    double ratio_ref = start;
+    int steps_next = ctx->pace > 0 ? plan_steps(ctx->pace, start, start, 1.0 / delta2, cfg.inner) : check_every;
     // mixed precision takes the x updates of an iteration group in pairs
     // (the update kernel's deferred mode)
     const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
@@ -925,8 +950,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             double ratio, ru_ratio;
             std::memcpy(&ratio, ctx->ctrl_host + 4, sizeof(double));
             std::memcpy(&ru_ratio, ctx->ctrl_host + 6, sizeof(double));
-            steps_next = next_check(check_every, ratio, ratio_prev, it - it_prev,
-                                    cfg.inner == kBF16 ? ru_ratio : 0.0);
+            const double from = ratio_prev > 0 ? ratio_prev : ratio_ref;
+            if (ratio > 0 && ratio < from) ctx->pace = std::log(from / ratio) / (it - it_prev);
+            steps_next = ctx->pace > 0 ? plan_steps(ctx->pace, ratio, ratio_ref, ru_ratio, cfg.inner) : check_every;
             ratio_prev = ratio;
             it_prev = it;
         }
@@ -942,6 +968,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             ++bs.ru;
             DP_TRY(read_ctrl(ctx, rd, cs, L.W, L.stream));
             nactive = ctx->ctrl_host[0];
+            std::memcpy(&ratio_ref, ctx->ctrl_host + 4, sizeof(double));
+            ratio_prev = ratio_ref;
+            if (ctx->pace > 0) steps_next = plan_steps(ctx->pace, ratio_ref, ratio_ref, 1.0 / delta2, cfg.inner);
         }
     }
     // Mixed precision: lanes stop only at a reliable update, which folded
