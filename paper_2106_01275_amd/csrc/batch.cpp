@@ -230,6 +230,10 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     B.prec = cfg.inner;
     B.links = links;
     B.eo = eo;
+    double it_bytes = 0;  // of the jobs resident first (the longest)
+    for (int k = 0; k < nslots; ++k)
+        it_bytes += iteration_bytes(in[jobs[k].inst].lat, nc, W, links, (double)prec_bytes(cfg.inner));
+    B.xnt = update_streams_x(it_bytes);
     B.mode = W >= 64 ? 2 : (W >= 16 ? 1 : 0);
     B.stream = s;
 

@@ -118,7 +118,18 @@ struct Launch {
     int ns;             // sites the CG vectors cover: N, or the even half of an even-odd order
     hipStream_t stream;
     int smode = -1;     // stencil mode (kernels.hip); -1: the built-in choice for the shape
+    int xnt = 0;        // the vector update passes x by the caches (update_streams_x)
 };
+
+// Whether the vector update should pass x by the caches: when the vectors
+// of an iteration (p on every site of the lattice; r, q and x) and the hop
+// links, in the storage precision, outgrow the Infinity Cache.  bytes: of one
+// complex number; several instances add up theirs.
+inline double iteration_bytes(const Lat &lat, int nc, int W, bool links, double bytes) {
+    const double vec = (double)lat.N * nc * W * bytes;
+    return vec * (lat.eo ? 2.5 : 4.0) + (links ? (double)lat.N * 8 * nc * nc * bytes : 0.0);
+}
+inline bool update_streams_x(double bytes) { return bytes > 256e6; }
 
 // geometry fields of a launch of W right-hand sides (grid, stream and mode
 // are the caller's)
@@ -166,6 +177,7 @@ struct BatchLaunch {
     const int *slot_of;  // device array [total workgroups]
     int nslots, nblocks, W, nc, prec, links, mode;
     int eo;              // every slot's lattice is in even-odd order
+    int xnt;             // Launch::xnt, of all slots together
     hipStream_t stream;
 };
 void launch_b_init(const BatchLaunch &B, int mixed);

@@ -85,19 +85,36 @@ __device__ __forceinline__ void stg(T *p, const T &v) {
     else *(gp<u32x4>)p = __builtin_bit_cast(u32x4, v);
 }
 
+// The same past the caches' normal retention (see the vector update).
+template <typename T>
+__device__ __forceinline__ T ldg_nt(const T *p) {
+    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_nontemporal_load((gp<const uint32_t>)p));
+    else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_nontemporal_load((gp<const uint64_t>)p));
+    else return __builtin_bit_cast(T, __builtin_nontemporal_load((gp<const u32x4>)p));
+}
+
+template <typename T>
+__device__ __forceinline__ void stg_nt(T *p, const T &v) {
+    if constexpr (sizeof(T) == 4) __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, v), (gp<uint32_t>)p);
+    else if constexpr (sizeof(T) == 8) __builtin_nontemporal_store(__builtin_bit_cast(uint64_t, v), (gp<uint64_t>)p);
+    else __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (gp<u32x4>)p);
+}
+
 template <typename S>
 struct St;
 
 template <>
 struct St<double2> {
     using R = double;
+    template <bool NT = false>
     __device__ static __forceinline__ void ld(const double2 *__restrict__ a, size_t i, R &re, R &im) {
-        double2 v = ldg(a + i);
+        double2 v = NT ? ldg_nt(a + i) : ldg(a + i);
         re = v.x;
         im = v.y;
     }
+    template <bool NT = false>
     __device__ static __forceinline__ void st(double2 *__restrict__ a, size_t i, R re, R im) {
-        stg(a + i, make_double2(re, im));
+        NT ? stg_nt(a + i, make_double2(re, im)) : stg(a + i, make_double2(re, im));
     }
     __device__ static __forceinline__ void round(R &, R &) {}
 };
@@ -105,13 +122,15 @@ struct St<double2> {
 template <>
 struct St<float2> {
     using R = float;
+    template <bool NT = false>
     __device__ static __forceinline__ void ld(const float2 *__restrict__ a, size_t i, R &re, R &im) {
-        float2 v = ldg(a + i);
+        float2 v = NT ? ldg_nt(a + i) : ldg(a + i);
         re = v.x;
         im = v.y;
     }
+    template <bool NT = false>
     __device__ static __forceinline__ void st(float2 *__restrict__ a, size_t i, R re, R im) {
-        stg(a + i, make_float2(re, im));
+        NT ? stg_nt(a + i, make_float2(re, im)) : stg(a + i, make_float2(re, im));
     }
     __device__ static __forceinline__ void round(R &, R &) {}
 };
@@ -119,15 +138,17 @@ struct St<float2> {
 template <>
 struct St<bf16x2> {
     using R = float;
+    template <bool NT = false>
     __device__ static __forceinline__ void ld(const bf16x2 *__restrict__ a, size_t i, R &re, R &im) {
-        uint32_t v = ldg(a + i).v;
+        uint32_t v = NT ? ldg_nt(a + i).v : ldg(a + i).v;
         re = __uint_as_float(v << 16);
         im = __uint_as_float(v & 0xffff0000u);
     }
+    template <bool NT = false>
     __device__ static __forceinline__ void st(bf16x2 *__restrict__ a, size_t i, R re, R im) {
         bf16x2 o;
         o.v = pack_bf16(re, im);
-        stg(a + i, o);
+        NT ? stg_nt(a + i, o) : stg(a + i, o);
     }
     // the value a store followed by a load would give
     __device__ static __forceinline__ void round(R &re, R &im) {
@@ -1653,7 +1674,13 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R 
 template <typename S>
 constexpr double kDeferBetaMin = std::is_same<S, bf16x2>::value ? 1.0 / 16 : 1.0 / 64;
 
-template <typename S, int XM>
+// XNT: x passes by the caches.  Of the vectors of an iteration x alone has no
+// reader before the next update; where they are together larger than the
+// 256 MB Infinity Cache (update_streams_x), keeping x out of it leaves the
+// others more room.  16^4 x 3, FP32, W = 64 (290 MB): the fine trace 182 ms
+// with x cached, 173 past the caches; where everything fits it only costs
+// (8^4 x 3, FP64, W = 256, 140 MB: 2.44 ms and 2.54).
+template <typename S, int XM, bool XNT>
 __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__restrict__ x, S *__restrict__ r,
                                               S *__restrict__ p, const S *__restrict__ q, Red rd, CgState cs) {
     using R = typename St<S>::R;
@@ -1692,7 +1719,7 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
             St<S>::ld(p, e + u * kBlock, pr[u], pi[u]);
             St<S>::ld(q, e + u * kBlock, qr[u], qi[u]);
             St<S>::ld(r, e + u * kBlock, rr_[u], ri[u]);
-            if (xio) St<S>::ld(x, e + u * kBlock, xr[u], xi[u]);
+            if (xio) St<S>::template ld<XNT>(x, e + u * kBlock, xr[u], xi[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1700,7 +1727,8 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
                 xr[u] = fmaR(cdef, pr[u] - rr_[u], xr[u]);
                 xi[u] = fmaR(cdef, pi[u] - ri[u], xi[u]);
             }
-            if (xio) St<S>::st(x, e + u * kBlock, fmaR(alpha, pr[u], xr[u]), fmaR(alpha, pi[u], xi[u]));
+            if (xio)
+                St<S>::template st<XNT>(x, e + u * kBlock, fmaR(alpha, pr[u], xr[u]), fmaR(alpha, pi[u], xi[u]));
             rr_[u] = fmaR(-alpha, qr[u], rr_[u]);
             ri[u] = fmaR(-alpha, qi[u], ri[u]);
             St<S>::st(r, e + u * kBlock, rr_[u], ri[u]);
@@ -1724,12 +1752,12 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
         St<S>::ld(p, e, pr, pi);
         St<S>::ld(q, e, qr, qi);
         St<S>::ld(r, e, rr_, ri);
-        if (xio) St<S>::ld(x, e, xr, xi);
+        if (xio) St<S>::template ld<XNT>(x, e, xr, xi);
         if (XM == 2) {
             xr = fmaR(cdef, pr - rr_, xr);
             xi = fmaR(cdef, pi - ri, xi);
         }
-        if (xio) St<S>::st(x, e, fmaR(alpha, pr, xr), fmaR(alpha, pi, xi));
+        if (xio) St<S>::template st<XNT>(x, e, fmaR(alpha, pr, xr), fmaR(alpha, pi, xi));
         rr_ = fmaR(-alpha, qr, rr_);
         ri = fmaR(-alpha, qi, ri);
         St<S>::st(r, e, rr_, ri);
@@ -1755,10 +1783,10 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
     block_partials_to<2>(bk, acc, W, logW, rd.part2, rd.nblk, sm);
 }
 
-template <typename S, int XM>
+template <typename S, int XM, bool XNT>
 __global__ __launch_bounds__(kBlock) void k_update(Launch L, S *__restrict__ x, S *__restrict__ r,
                                                    S *__restrict__ p, const S *__restrict__ q, Red rd, CgState cs) {
-    k_update_body<S, XM>(own_blk(), L, x, r, p, q, rd, cs);
+    k_update_body<S, XM, XNT>(own_blk(), L, x, r, p, q, rd, cs);
 }
 
 // Mixed precision: x64 += xlo, xlo = 0 (the low-precision iterate folded
@@ -2256,13 +2284,13 @@ __global__ __launch_bounds__(kBlock) void k_b_odd_x(BatchLaunch B, int phase) {
                                                                (const double2 *)d->U64, d->nbr, 0, d->rd, hb);
 }
 
-template <typename S, int XM>
+template <typename S, int XM, bool XNT>
 __global__ __launch_bounds__(kBlock) void k_b_update(BatchLaunch B) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, kSlotIter);
     if (!d) return;
     // FP64: the iterate is x64 itself (xlo aliases it)
-    k_update_body<S, XM>(bk, d->L, (S *)d->xlo, (S *)d->r, (S *)d->p, (const S *)d->q,
+    k_update_body<S, XM, XNT>(bk, d->L, (S *)d->xlo, (S *)d->r, (S *)d->p, (const S *)d->q,
                          d->rd, d->cs);
 }
 
@@ -3169,17 +3197,23 @@ void launch_stencil(const Launch &L, int prec, const StencilArgs &a) {
         k_finish_cg<<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
 }
 
+template <typename S, bool XNT>
+static void update_t(const Launch &L, void *x, void *r, void *p, const void *q, const Red &rd, const CgState &cs,
+                     int xmode) {
+    if (xmode == 1)
+        k_update<S, 1, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
+    else if (xmode == 2)
+        k_update<S, 2, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
+    else
+        k_update<S, 0, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
+}
+
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
                    const CgState &cs, int xmode) {
     if (prec == kF64 || !cs.xdef) xmode = 0;  // deferral: FP32 and BF16 storage
-    DP_DISPATCH_PREC(prec, S, {
-        if (xmode == 1)
-            k_update<S, 1><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
-        else if (xmode == 2)
-            k_update<S, 2><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
-        else
-            k_update<S, 0><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
-    });
+    DP_DISPATCH_PREC(prec, S,
+                     L.xnt ? update_t<S, true>(L, x, r, p, q, rd, cs, xmode)
+                           : update_t<S, false>(L, x, r, p, q, rd, cs, xmode));
 }
 
 void launch_fold(const Launch &L, int prec, double *x64, void *xlo) {
@@ -3430,17 +3464,20 @@ void launch_b_hop(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_sten
 
 void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_stencil<kStFull>(B, ev0, ev1); }
 
+template <typename S, bool XNT>
+static void b_update_t(const BatchLaunch &B, int xmode) {
+    if (xmode == 1)
+        k_b_update<S, 1, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+    else if (xmode == 2)
+        k_b_update<S, 2, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+    else
+        k_b_update<S, 0, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+}
+
 void launch_b_update(const BatchLaunch &B, int xmode) {
     k_b_finish_cg<<<(B.nslots * B.W + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, B.stream>>>(B);
     if (B.prec == kF64) xmode = 0;  // the slots' state of mixed precision has xdef
-    DP_DISPATCH_PREC(B.prec, S, {
-        if (xmode == 1)
-            k_b_update<S, 1><<<B.nblocks, kBlock, 0, B.stream>>>(B);
-        else if (xmode == 2)
-            k_b_update<S, 2><<<B.nblocks, kBlock, 0, B.stream>>>(B);
-        else
-            k_b_update<S, 0><<<B.nblocks, kBlock, 0, B.stream>>>(B);
-    });
+    DP_DISPATCH_PREC(B.prec, S, B.xnt ? b_update_t<S, true>(B, xmode) : b_update_t<S, false>(B, xmode));
 }
 
 void launch_b_reseed(const BatchLaunch &B) { k_b_reseed<<<B.nslots * B.W, kBlock, 0, B.stream>>>(B); }
