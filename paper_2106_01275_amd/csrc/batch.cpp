@@ -264,6 +264,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
         d.gen_b = trace_mode ? 1 : 0;
         d.disp = I.disp;
         d.flags = kSlotInit;
+        d.fold0 = 1;
         slot_job[k] = jidx;
         slot_it[k] = 0;
         slot_ru[k] = 0;
@@ -337,7 +338,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     auto init_slots = [&]() -> dp_status {
         DP_TRY(upload());
         if (trace_mode) {
-            launch_b_init(B, mixed ? 1 : 0);
+            launch_b_init(B);
         } else {
             for (int k = 0; k < nslots; ++k) {
                 if (!(hsd[k].flags & kSlotInit)) continue;
@@ -348,11 +349,10 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
                 ia.r = d.r;
                 ia.p = d.p;
                 ia.xlo = d.xlo;
-                ia.x64 = d.x64;
-                ia.mixed = mixed ? 1 : 0;
                 ia.links = links;
                 ia.diag = d.diag;
                 ia.U = d.U;
+                ia.U64 = (const double *)d.U64;
                 ia.nbr = d.nbr;
                 ia.rd = d.rd;
                 ia.cs = d.cs;
@@ -376,9 +376,12 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
         DP_TRY(upload());
         // mixed precision: a slot finishes only after a reliable update
         // (which folded x and took the true residual of the final x64) or
-        // with no active lane from the start; FP64: apply the deferred
-        // solution update and take the true residual now
-        if (!mixed) launch_b_ru(B, 1);
+        // with no active lane from the start (x64 is then still unwritten; a
+        // second fold of the others adds nothing); FP64: take the true
+        // residual now
+        bool unfolded = false;
+        for (auto &d : hsd) unfolded |= (d.flags & kSlotFinal) && d.fold0;
+        if (!mixed || unfolded) launch_b_ru(B, 1);
         if (trace_mode) launch_b_dot(B);
         DP_HIP(hipGetLastError());
         for (int k = 0; k < nslots; ++k) {
@@ -518,6 +521,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
                 if (!(d.flags & kSlotRU)) continue;
                 ++in[jobs[slot_job[k]].inst].st.reliable_updates;
                 d.flags = kSlotIter;
+                d.fold0 = 0;
                 if (slot_it[k] >= max_steps) {
                     d.flags = kSlotFinal;
                     any_fin = true;

@@ -146,7 +146,7 @@ void launch_cg_step(const Launch &L, int prec, const StencilArgs &a, void *xlo, 
 // the odd half of p, H p_e / c, for the stencil a of an even-odd step
 StencilArgs hop_args(const StencilArgs &a, void *p);
 // what a block's initialisation writes (slots of the context's workspace)
-InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, double *x64, const Red &rd, const CgState &cs);
+InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, const Red &rd, const CgState &cs);
 // update mode (launch_update's xmode) of iteration c of a group of n
 int xmode_of(int c, int n, bool defer);
 bool xdefer_enabled();
@@ -299,7 +299,7 @@ struct InitProbe {
     const CgState *cs;
     dp_ctx *ctx;
     void operator()(const OpPrep &op, void *xlo, double *x64) const {
-        launch_init_probe(*L, prec, g, init_args(ctx, op, xlo, x64, *rd, *cs));
+        launch_init_probe(*L, prec, g, init_args(ctx, op, xlo, *rd, *cs));
     }
     dp_status small_source(SmallArgs &a) const {
         a.src = 0;
@@ -320,7 +320,7 @@ struct InitAbi {
     const CgState *cs;
     dp_ctx *ctx;
     void operator()(const OpPrep &op, void *xlo, double *x64) const {
-        launch_init_abi(*L, prec, babi, rhs0, nvalid, init_args(ctx, op, xlo, x64, *rd, *cs));
+        launch_init_abi(*L, prec, babi, rhs0, nvalid, init_args(ctx, op, xlo, *rd, *cs));
     }
     dp_status small_source(SmallArgs &a) const {
         a.src = 1;
@@ -359,7 +359,7 @@ struct InitDeflated {
         launch_probe_fill(*L, g, z);
         const dp_status e = deflate_rhs(ctx, *d, *L, z);
         if (e != DP_OK) *status = e;
-        launch_init_b64(*L, prec, z, init_args(ctx, op, xlo, x64, *rd, *cs));
+        launch_init_b64(*L, prec, z, init_args(ctx, op, xlo, *rd, *cs));
     }
     dp_status small_source(SmallArgs &a) const {
         DP_TRY(ctx->ensure(kSlotB64, (size_t)L->lat.N * L->nc * L->W * 16));

@@ -160,6 +160,7 @@ struct SlotDesc {
     Red rd;
     CgState cs;
     ProbeGen g;          // probes of the slot's right-hand sides
+    int fold0;           // 1: the slot's block has not been folded yet
     int gen_b;           // 1: b is those probes (the true residual regenerates it)
     int disp;            // displacement of the contraction
 };
@@ -180,7 +181,7 @@ struct BatchLaunch {
     int xnt;             // Launch::xnt, of all slots together
     hipStream_t stream;
 };
-void launch_b_init(const BatchLaunch &B, int mixed);
+void launch_b_init(const BatchLaunch &B);
 // xmode: as launch_update's (the slots of mixed precision have cs.xdef)
 void launch_b_iteration(const BatchLaunch &B, int xmode = 0);
 // even-odd order: the odd half of p, H p_e / c, before the stencil
@@ -217,11 +218,10 @@ void prepare_links(const Lat &lat, int nc, const void *abi, int *nbr, double *u6
 struct InitArgs {
     double *b64;
     void *r, *p, *xlo;
-    double *x64;
-    int mixed;
     bool links;
     double diag;
     const void *U;       // inner-precision hop links
+    const double *U64;   // FP64 hop links (probes in even-odd order)
     const int *nbr;
     Red rd;
     CgState cs;
@@ -267,8 +267,8 @@ int stencil_mode_rule(const Launch &L, int prec);
 // plain update.
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
                    const CgState &cs, int xmode = 0);
-// x64 += xlo, xlo = 0 (mixed precision)
-void launch_fold(const Launch &L, int prec, double *x64, void *xlo);
+// x64 += xlo, xlo = 0 (mixed precision); first: x64 = xlo (no fold yet in this block)
+void launch_fold(const Launch &L, int prec, double *x64, void *xlo, int first);
 // The FP64 true residual r = b - q64, with q64 = A x64 computed by the FP64
 // stencil beforehand, element by element (gen set: b is regenerated from
 // those probes instead of read from b64).  ru_mode 1 (reliable update): r

@@ -281,11 +281,8 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
 }
 
 // noise value z0(s, site, b) as (re, im) in {-1, 0, 1}
-__device__ __forceinline__ void noise(unsigned long long seedmix, long long s, int N, int site, int nc,
-                                      int b, int kind, double &re, double &im) {
-    const unsigned long long ctr =
-        ((unsigned long long)s * (unsigned long long)N + (unsigned long long)site) * (unsigned long long)nc +
-        (unsigned long long)b;
+__device__ __forceinline__ void noise_at(unsigned long long seedmix, unsigned long long ctr, int kind, double &re,
+                                         double &im) {
     const unsigned long long h = mix64(seedmix ^ ctr);
     const int top = (int)(h >> 63), nxt = (int)((h >> 62) & 1ull);
     if (kind == DP_NOISE_REAL_Z2) {
@@ -299,6 +296,14 @@ __device__ __forceinline__ void noise(unsigned long long seedmix, long long s, i
         re = q == 0 ? 1.0 : (q == 2 ? -1.0 : 0.0);
         im = q == 1 ? 1.0 : (q == 3 ? -1.0 : 0.0);
     }
+}
+
+__device__ __forceinline__ void noise(unsigned long long seedmix, long long s, int N, int site, int nc,
+                                      int b, int kind, double &re, double &im) {
+    noise_at(seedmix,
+             ((unsigned long long)s * (unsigned long long)N + (unsigned long long)site) * (unsigned long long)nc +
+                 (unsigned long long)b,
+             kind, re, im);
 }
 
 __device__ __forceinline__ int shift0(const Lat &L, int site, int p) {
@@ -783,8 +788,7 @@ __global__ void k_prepare(Lat L, int nc, const double2 *__restrict__ abi, int *_
 template <typename S, int SRC>
 __device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g, const double2 *babi, long long rhs0,
                                             long long nvalid, double2 *b64, S *__restrict__ r, S *__restrict__ p,
-                                            S *__restrict__ xlo, double2 *__restrict__ x64, int mixed, double hop_scale,
-                                            Red rd) {
+                                            S *__restrict__ xlo, double hop_scale, Red rd) {
     __shared__ double sm[2 * kBlock];
     const int tid = threadIdx.x, W = L.W, logW = L.logW;
     const int j = tid & (W - 1);
@@ -819,7 +823,6 @@ __device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g,
             if (SRC != 0) b64[i] = make_double2(re, im);
             St<S>::st(p, i, (typename St<S>::R)(f * re), (typename St<S>::R)(f * im));
             acc[0] += re * re + im * im;
-            if (mixed) x64[i] = make_double2(0.0, 0.0);
             if (odd) continue;
             if (!L.lat.eo) St<S>::st(r, i, (typename St<S>::R)re, (typename St<S>::R)im);
             St<S>::st(xlo, i, 0, 0);
@@ -831,9 +834,121 @@ __device__ __forceinline__ void k_init_body(const Blk &bk, Launch L, ProbeGen g,
 template <typename S, int SRC>
 __global__ __launch_bounds__(kBlock) void k_init(Launch L, ProbeGen g, const double2 *babi, long long rhs0,
                                                  long long nvalid, double2 *b64, S *__restrict__ r, S *__restrict__ p,
-                                                 S *__restrict__ xlo, double2 *__restrict__ x64, int mixed,
-                                                 double hop_scale, Red rd) {
-    k_init_body<S, SRC>(own_blk(), L, g, babi, rhs0, nvalid, b64, r, p, xlo, x64, mixed, hop_scale, rd);
+                                                 S *__restrict__ xlo, double hop_scale, Red rd) {
+    k_init_body<S, SRC>(own_blk(), L, g, babi, rhs0, nvalid, b64, r, p, xlo, hop_scale, rd);
+}
+
+// Even-odd order, probes: the whole start of a block in one pass,
+// r = p_e = b_e + H b_o / c with |b|^2 and |r|^2 per lane.  A probe is nonzero
+// on the sites of one colour only, so a thread generates the values of its
+// site's neighbours itself where they are nonzero, and multiplies only those
+// by their links (FP64): the pass writes its vectors and reads next to
+// nothing, where writing b and x64 and then applying the hopping term to b
+// moved four times as much (16^4 x 3, FP32, W = 64, 960 colours: 184 us for
+// the two passes, 50 us in one; 16 colours, BF16: 200 and about 120).
+// The neighbours' indices and colours are found once per site, by the whole
+// workgroup for a stretch of sites at a time (the index order takes several
+// integer divisions, which the W lanes of a site would all repeat).  The odd
+// half of p is the first step's to write, x64 the first fold's.
+template <typename S, int NC, bool LINKS>
+__device__ __forceinline__ void k_init_probe_body(const Blk &bk, const Launch &L, const ProbeGen &g,
+                                                  S *__restrict__ r, S *__restrict__ p, S *__restrict__ xlo,
+                                                  double hop_scale, const double2 *__restrict__ U, const Red &rd) {
+    constexpr int kStretch = 32;  // sites at a time (W < 8: one tile's)
+    __shared__ double sm[4 * kBlock];
+    __shared__ int sx[10 * kBlock], sc[10 * kBlock];  // [neighbour][site]: ABI index (displaced) and colour
+    const int tid = threadIdx.x, W = L.W, logW = L.logW;
+    const int j = tid & (W - 1), spt = kBlock >> logW;
+    const int nst = max(kStretch, spt);
+    const Lat &lat = L.lat;
+    const unsigned long long seedmix = mix64(g.seed);
+    const ProbeLane pl = probe_lane(g, NC, g.rhs0 + j);
+    const bool valid = j < g.nvalid;
+    // the noise counter of site 0, component 0 (see noise), and |b|^2 of a lit site
+    const unsigned long long ctr0 = (unsigned long long)pl.s * (unsigned long long)lat.N * NC;
+    const double bsite = (g.noise == DP_NOISE_Z2_COMPLEX ? 2.0 : 1.0) * (g.dilute ? 1 : NC);
+    double bb[2] = {0.0, 0.0}, acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int t0, t1;
+    tile_range(bk, L.ntiles, t0, t1);
+    const int end = min(t1 * spt, L.ns);
+    for (int s0 = t0 * spt; s0 < end; s0 += nst) {
+        __syncthreads();
+        for (int k = tid; k < nst && s0 + k < end; k += kBlock) {
+            // the site's coordinates, moved by the probes' displacement; the
+            // neighbours', and the odd site of the same internal index (mate)
+            int x = lex_of(lat, s0 + k);
+            if (g.shift) x = shift0(lat, x, -g.shift);
+            int rem = x, st = 1;
+#pragma unroll
+            for (int d = 3; d >= 0; --d) {
+                const int D = lat.D[d], q = rem / D, c = rem - q * D;
+                sx[d * nst + k] = x + (c + 1 == D ? 1 - D : 1) * st;
+                sx[(d + 4) * nst + k] = x + (c == 0 ? D - 1 : -1) * st;
+                rem = q;
+                st *= D;
+            }
+            sx[8 * nst + k] = x;
+            sx[9 * nst + k] = x ^ 1;
+#pragma unroll
+            for (int d = 0; d < 10; ++d) sc[d * nst + k] = ldg(g.colors + sx[d * nst + k]);
+        }
+        __syncthreads();
+        for (int k = tid >> logW; k < nst && s0 + k < end; k += spt) {
+            const int site = s0 + k;
+            double ar[NC] = {}, ai[NC] = {};
+            // the hop from neighbour dir of the probe's component b
+            auto hop = [&](int dir, int y, int b) {
+                double vr, vi;
+                noise_at(seedmix, ctr0 + (unsigned)(y * NC + b), g.noise, vr, vi);
+                const double2 *u = U + ((size_t)site * 8 + dir) * NC * NC;
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    double2 w = make_double2(a == b ? 1.0 : 0.0, 0.0);
+                    if (LINKS) w = ldg(u + (dir < 4 ? a * NC + b : b * NC + a));
+                    if (dir >= 4) w.y = -w.y;
+                    ar[a] = fma(w.x, vr, fma(-w.y, vi, ar[a]));
+                    ai[a] = fma(w.x, vi, fma(w.y, vr, ai[a]));
+                }
+            };
+#pragma unroll
+            for (int dir = 0; dir < 8; ++dir) {
+                if (!valid || sc[dir * nst + k] != pl.c) continue;
+                const int y = sx[dir * nst + k];
+                if (g.dilute) {
+                    hop(dir, y, pl.a);
+                } else {
+#pragma unroll
+                    for (int b = 0; b < NC; ++b) hop(dir, y, b);
+                }
+            }
+            const bool own = valid && sc[8 * nst + k] == pl.c, mate = valid && sc[9 * nst + k] == pl.c;
+            bb[0] += ((own ? 1.0 : 0.0) + (mate ? 1.0 : 0.0)) * bsite;
+            const unsigned long long ctr = ctr0 + (unsigned)(sx[8 * nst + k] * NC);
+#pragma unroll
+            for (int a = 0; a < NC; ++a) {
+                double br = 0.0, bi = 0.0;
+                if (own && !(g.dilute && a != pl.a)) noise_at(seedmix, ctr + a, g.noise, br, bi);
+                const size_t i = ((size_t)(site * NC + a) << logW) + j;
+                typename St<S>::R rr = (typename St<S>::R)fma(hop_scale, ar[a], br);
+                typename St<S>::R ri = (typename St<S>::R)fma(hop_scale, ai[a], bi);
+                St<S>::st(r, i, rr, ri);
+                St<S>::st(p, i, rr, ri);
+                St<S>::st(xlo, i, 0, 0);
+                St<S>::round(rr, ri);
+                acc[2] += (double)rr * rr + (double)ri * ri;
+            }
+        }
+    }
+    block_partials_to<2>(bk, bb, W, logW, rd.part2, rd.nblk, sm);
+    __syncthreads();
+    block_partials<4>(bk, acc, W, logW, rd, sm);
+}
+
+template <typename S, int NC, bool LINKS>
+__global__ __launch_bounds__(kBlock) void k_init_probe(Launch L, ProbeGen g, S *__restrict__ r, S *__restrict__ p,
+                                                       S *__restrict__ xlo, double hop_scale,
+                                                       const double2 *__restrict__ U, Red rd) {
+    k_init_probe_body<S, NC, LINKS>(own_blk(), L, g, r, p, xlo, hop_scale, U, rd);
 }
 
 // the probes of g in FP64, index order [site][nc][W]
@@ -1790,9 +1905,11 @@ __global__ __launch_bounds__(kBlock) void k_update(Launch L, S *__restrict__ x, 
 }
 
 // Mixed precision: x64 += xlo, xlo = 0 (the low-precision iterate folded
-// into the FP64 solution before a reliable update).
+// into the FP64 solution before a reliable update).  The first fold of a block
+// sets x64 = xlo: the initialisation leaves x64 unwritten.
 template <typename S>
-__device__ __forceinline__ void k_fold_body(const Blk &bk, Launch L, double2 *__restrict__ x64, S *__restrict__ xlo) {
+__device__ __forceinline__ void k_fold_body(const Blk &bk, Launch L, double2 *__restrict__ x64, S *__restrict__ xlo,
+                                            int first) {
     using R = typename St<S>::R;
     const int tid = threadIdx.x, W = L.W;
     const int sites_per_tile = kBlock >> L.logW;
@@ -1803,7 +1920,7 @@ __device__ __forceinline__ void k_fold_body(const Blk &bk, Launch L, double2 *__
     for (size_t e = e0 + tid; e < e1; e += kBlock) {
         R xr, xi;
         St<S>::ld(xlo, e, xr, xi);
-        double2 v = x64[e];
+        double2 v = first ? make_double2(0.0, 0.0) : x64[e];
         v.x += (double)xr;
         v.y += (double)xi;
         St<S>::st(xlo, e, 0, 0);
@@ -1812,8 +1929,9 @@ __device__ __forceinline__ void k_fold_body(const Blk &bk, Launch L, double2 *__
 }
 
 template <typename S>
-__global__ __launch_bounds__(kBlock) void k_fold(Launch L, double2 *__restrict__ x64, S *__restrict__ xlo) {
-    k_fold_body<S>(own_blk(), L, x64, xlo);
+__global__ __launch_bounds__(kBlock) void k_fold(Launch L, double2 *__restrict__ x64, S *__restrict__ xlo,
+                                                 int first) {
+    k_fold_body<S>(own_blk(), L, x64, xlo, first);
 }
 
 // FP64 true residual r_new = b - A x64 with the FP64 hop links, |r_new|^2 per
@@ -2243,29 +2361,35 @@ __device__ __forceinline__ const SlotDesc *slot_of_block(const BatchLaunch &B, B
 }
 
 template <typename S>
-__global__ __launch_bounds__(kBlock) void k_b_init(BatchLaunch B, int mixed) {
+__global__ __launch_bounds__(kBlock) void k_b_init(BatchLaunch B) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, kSlotInit);
     if (!d) return;
     k_init_body<S, 0>(bk, d->L, d->g, nullptr, 0, 0, (double2 *)d->b64, (S *)d->r, (S *)d->p,
-                      (S *)d->xlo, (double2 *)d->x64, mixed, 1.0 / d->diag, d->rd);
+                      (S *)d->xlo, 1.0 / d->diag, d->rd);
 }
 
-// KIND kStFull: q = A p (even-odd: its even half); kStHop: the odd half of p;
-// kStInit: the first residual of the even-odd start.
+// the same in even-odd order
+template <typename S, int NC, bool LINKS>
+__global__ __launch_bounds__(kBlock) void k_b_init_probe(BatchLaunch B) {
+    Blk bk;
+    const SlotDesc *d = slot_of_block(B, bk, kSlotInit);
+    if (!d) return;
+    k_init_probe_body<S, NC, LINKS>(bk, d->L, d->g, (S *)d->r, (S *)d->p, (S *)d->xlo, 1.0 / d->diag,
+                                    (const double2 *)d->U64, d->rd);
+}
+
+// KIND kStFull: q = A p (even-odd: its even half); kStHop: the odd half of p.
 template <typename S, typename LS, int NC, bool LINKS, int MODE, int KIND>
 __global__ __launch_bounds__(kBlock) void k_b_stencil(BatchLaunch B) {
     Blk bk;
-    const SlotDesc *d = slot_of_block(B, bk, KIND == kStInit ? kSlotInit : kSlotIter);
+    const SlotDesc *d = slot_of_block(B, bk, kSlotIter);
     if (!d) return;
     const HopB none{};
     if constexpr (KIND == kStHop)
         k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)(1.0 / d->diag), (const S *)d->p,
                                                      nullptr, (S *)d->p, nullptr, (const LS *)d->U, d->nbr, 0, d->rd,
                                                      none);
-    else if constexpr (KIND == kStInit)
-        k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)1, (const S *)d->p, nullptr,
-                                                     (S *)d->r, (S *)d->p, (const LS *)d->U, d->nbr, 1, d->rd, none);
     else
         k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)d->diag, (const S *)d->p,
                                                      (const S *)d->r, (S *)d->q, nullptr, (const LS *)d->U, d->nbr, 1,
@@ -2299,7 +2423,7 @@ __global__ __launch_bounds__(kBlock) void k_b_fold(BatchLaunch B, int phase) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, phase);
     if (!d) return;
-    k_fold_body<S>(bk, d->L, (double2 *)d->x64, (S *)d->xlo);
+    k_fold_body<S>(bk, d->L, (double2 *)d->x64, (S *)d->xlo, d->fold0);
 }
 
 template <typename S, int NC, bool LINKS, int MODE>
@@ -3058,8 +3182,7 @@ static void init_block(const Launch &L, int prec, const ProbeGen &g, const doubl
     DP_DISPATCH_PREC(prec, S,
                      k_init<S, SRC><<<L.nblk, kBlock, 0, L.stream>>>(L, g, (const double2 *)src, rhs0, nvalid,
                                                                      (double2 *)ia.b64, (S *)ia.r, (S *)ia.p,
-                                                                     (S *)ia.xlo, (double2 *)ia.x64, ia.mixed,
-                                                                     1.0 / ia.diag, ia.rd));
+                                                                     (S *)ia.xlo, 1.0 / ia.diag, ia.rd));
     if (!L.lat.eo) {
         k_finish<2, kEpiInit><<<L.W, kBlock, 0, L.stream>>>(ia.rd, ia.cs);
         return;
@@ -3080,8 +3203,24 @@ static void init_block(const Launch &L, int prec, const ProbeGen &g, const doubl
     launch_stencil(L, prec, a);
 }
 
+template <typename S, int NC, bool LINKS>
+static void init_probe_t(const Launch &L, const ProbeGen &g, const InitArgs &ia) {
+    k_init_probe<S, NC, LINKS><<<L.nblk, kBlock, 0, L.stream>>>(L, g, (S *)ia.r, (S *)ia.p, (S *)ia.xlo,
+                                                                1.0 / ia.diag, (const double2 *)ia.U64, ia.rd);
+}
+
 void launch_init_probe(const Launch &L, int prec, const ProbeGen &g, const InitArgs &ia) {
-    init_block<0>(L, prec, g, nullptr, 0, 0, ia);
+    if (!L.lat.eo) {
+        init_block<0>(L, prec, g, nullptr, 0, 0, ia);
+        return;
+    }
+    DP_DISPATCH_PREC(prec, S, {
+        if (L.nc == 3)
+            ia.links ? init_probe_t<S, 3, true>(L, g, ia) : init_probe_t<S, 3, false>(L, g, ia);
+        else
+            ia.links ? init_probe_t<S, 1, true>(L, g, ia) : init_probe_t<S, 1, false>(L, g, ia);
+    });
+    k_finish<4, kEpiInitEo><<<L.W, kBlock, 0, L.stream>>>(ia.rd, ia.cs);
 }
 
 void launch_init_abi(const Launch &L, int prec, const double *babi, long long rhs0, long long nvalid,
@@ -3216,8 +3355,8 @@ void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const v
                            : update_t<S, false>(L, x, r, p, q, rd, cs, xmode));
 }
 
-void launch_fold(const Launch &L, int prec, double *x64, void *xlo) {
-    DP_DISPATCH_PREC(prec, S, k_fold<S><<<L.nblk, kBlock, 0, L.stream>>>(L, (double2 *)x64, (S *)xlo));
+void launch_fold(const Launch &L, int prec, double *x64, void *xlo, int first) {
+    DP_DISPATCH_PREC(prec, S, k_fold<S><<<L.nblk, kBlock, 0, L.stream>>>(L, (double2 *)x64, (S *)xlo, first));
 }
 
 
@@ -3450,12 +3589,22 @@ static void b_stencil(const BatchLaunch &B, hipEvent_t ev0 = nullptr, hipEvent_t
     });
 }
 
-void launch_b_init(const BatchLaunch &B, int mixed) {
-    DP_DISPATCH_PREC(B.prec, S, k_b_init<S><<<B.nblocks, kBlock, 0, B.stream>>>(B, mixed));
+template <typename S, int NC, bool LINKS>
+static void b_init_probe_t(const BatchLaunch &B) {
+    k_b_init_probe<S, NC, LINKS><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+}
+
+void launch_b_init(const BatchLaunch &B) {
     if (B.eo) {
-        b_stencil<kStInit>(B);
+        DP_DISPATCH_PREC(B.prec, S, {
+            if (B.nc == 3)
+                B.links ? b_init_probe_t<S, 3, true>(B) : b_init_probe_t<S, 3, false>(B);
+            else
+                B.links ? b_init_probe_t<S, 1, true>(B) : b_init_probe_t<S, 1, false>(B);
+        });
         k_b_finish<4, kEpiInitEo><<<B.nslots * B.W, kBlock, 0, B.stream>>>(B, kSlotInit);
     } else {
+        DP_DISPATCH_PREC(B.prec, S, k_b_init<S><<<B.nblocks, kBlock, 0, B.stream>>>(B));
         k_b_finish<2, kEpiInit><<<B.nslots * B.W, kBlock, 0, B.stream>>>(B, kSlotInit);
     }
 }

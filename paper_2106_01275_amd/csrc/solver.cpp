@@ -451,7 +451,7 @@ static dp_status time_iterations(dp_ctx *ctx, const OpPrep &op, int inner, const
     g.ncolors = 1;
     g.noise = DP_NOISE_Z2_COMPLEX;
     g.nvalid = Lc.W;
-    launch_init_probe(Lc, inner, g, init_args(ctx, op, xlo, (double *)ctx->at(kSlotX64), rd, cs));
+    launch_init_probe(Lc, inner, g, init_args(ctx, op, xlo, rd, cs));
     StencilArgs a;
     a.links = op.links;
     a.diag = op.m2 + 8.0;
@@ -702,17 +702,16 @@ void launch_cg_step(const Launch &L, int prec, const StencilArgs &a, void *xlo, 
     launch_update(L, prec, xlo, (void *)a.rin, (void *)a.pin, a.q, a.rd, a.cs, xmode);
 }
 
-InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, double *x64, const Red &rd, const CgState &cs) {
+InitArgs init_args(dp_ctx *ctx, const OpPrep &op, void *xlo, const Red &rd, const CgState &cs) {
     InitArgs ia;
     ia.b64 = (double *)ctx->at(kSlotB64);
     ia.r = ctx->at(kSlotR);
     ia.p = ctx->at(kSlotP);
     ia.xlo = xlo;
-    ia.x64 = x64;
-    ia.mixed = op.inner != kF64;
     ia.links = op.links;
     ia.diag = op.m2 + 8.0;
     ia.U = op.U8;
+    ia.U64 = (const double *)op.U8x;
     ia.nbr = op.nbr;
     ia.rd = rd;
     ia.cs = cs;
@@ -963,7 +962,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             it_ru = it;
             // reliable update: x64 += xlo, r = b - A x64 in FP64 (p continued
             // from it), the residual norms restart from it
-            launch_fold(L, cfg.inner, x64, xlo);
+            launch_fold(L, cfg.inner, x64, xlo, bs.ru == 0);
             true_residual(ctx, op, cfg, L, rd, cs, b64, x64, 1, init.probe());
             DP_HIP(hipGetLastError());
             ++bs.ru;
@@ -977,10 +976,11 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     // Mixed precision: lanes stop only at a reliable update, which folded
     // x and left the FP64 true residual of the final x64 in true_rr, so
     // with no lane active there is nothing left to do.  Otherwise (FP64, or
-    // max_iter reached) fold what is left (mixed) and take the final true
+    // max_iter reached, or mixed with no lane active from the start, whose x64
+    // is still unwritten) fold what is left (mixed) and take the final true
     // residual (statistics).
-    if (!(mixed && nactive == 0)) {
-        if (mixed) launch_fold(L, cfg.inner, x64, xlo);
+    if (!(mixed && nactive == 0 && bs.ru > 0)) {
+        if (mixed) launch_fold(L, cfg.inner, x64, xlo, bs.ru == 0);
         true_residual(ctx, op, cfg, L, rd, cs, b64, x64, 0, init.probe());
         DP_HIP(hipGetLastError());
     }
@@ -1077,7 +1077,7 @@ static dp_status time_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, 
     g.nvalid = W;
     const bool mixed = cfg.inner != kF64;
     void *xlo = mixed ? ctx->at(kSlotXLo) : ctx->at(kSlotX64);
-    launch_init_probe(L, cfg.inner, g, init_args(ctx, op, xlo, (double *)ctx->at(kSlotX64), rd, cs));
+    launch_init_probe(L, cfg.inner, g, init_args(ctx, op, xlo, rd, cs));
     StencilArgs a;
     a.links = op.links;
     a.diag = op.m2 + 8.0;
