@@ -2080,6 +2080,14 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
     block_partials_to<2>(bk, acc, W, logW, rd.part2, rd.nblk, sm);
 }
 
+template <typename S, int NC, bool LINKS, int MODE>
+__global__ __launch_bounds__(kBlock) void k_true_resid(Launch L, double diag, const double2 *__restrict__ b64,
+                                                       const double2 *__restrict__ x64, const double2 *__restrict__ U,
+                                                       const int *__restrict__ nbr, S *__restrict__ rout,
+                                                       S *__restrict__ pio, const S *__restrict__ qin, int ru, Red rd,
+                                                       CgState cs, ProbeGen g, int gen) {
+    k_true_resid_body<S, NC, LINKS, MODE>(own_blk(), L, diag, b64, x64, U, nbr, rout, pio, qin, ru, rd, cs, g, gen);
+}
 
 // The true residual from q64 = A x64 (the FP64 stencil, run just before on
 // x64 with the FP64 hop links): r = b - q64 in FP64 element by element, with
@@ -3359,6 +3367,36 @@ void launch_fold(const Launch &L, int prec, double *x64, void *xlo, int first) {
     DP_DISPATCH_PREC(prec, S, k_fold<S><<<L.nblk, kBlock, 0, L.stream>>>(L, (double2 *)x64, (S *)xlo, first));
 }
 
+template <typename S, int NC, bool LINKS>
+static void true_resid_t(const Launch &L, const ResidArgs &a) {
+    const ProbeGen g = a.gen ? *a.gen : ProbeGen{};
+#define DP_TR(M)                                                                                                  \
+    k_true_resid<S, NC, LINKS, M><<<L.nblk, kBlock, 0, L.stream>>>(                                               \
+        L, a.diag, (const double2 *)a.b64, (const double2 *)a.x64, (const double2 *)a.U64, a.nbr, (S *)a.r, (S *)a.p, \
+        (const S *)a.q, a.ru, a.rd, a.cs, g, a.gen ? 1 : 0)
+    // (by width as the stencil's; at W = 64 the LDS tile took the fine trace of
+    // 16^4 x 3, FP32, from 167 to 171 ms)
+    if (L.W >= 64)
+        DP_TR(2);
+    else if (L.W >= 16)
+        DP_TR(1);
+    else
+        DP_TR(0);
+#undef DP_TR
+}
+
+void launch_true_resid(const Launch &L, int prec, const ResidArgs &a) {
+    DP_DISPATCH_PREC(prec, S, {
+        if (L.nc == 3)
+            a.links ? true_resid_t<S, 3, true>(L, a) : true_resid_t<S, 3, false>(L, a);
+        else
+            a.links ? true_resid_t<S, 1, true>(L, a) : true_resid_t<S, 1, false>(L, a);
+    });
+    if (a.ru)
+        k_finish<2, kEpiRU><<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
+    else
+        k_finish<2, kEpiStats><<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
+}
 
 void launch_resid_q(const Launch &L, int prec, const double *b64, const double *q64, void *r, void *p,
                     const void *q, int ru_mode, const Red &rd, const CgState &cs, const ProbeGen *gen) {

@@ -809,10 +809,14 @@ static std::string graph_key(int steps, int inner, const Launch &L, const Stenci
 }
 
 // The FP64 true residual r = b - A x64 of the block (ru: with the residual
-// replacement; else statistics only): the FP64 stencil on x64 into an FP64
-// q, then an element-wise pass that forms r,
-// continues p and sums |r|^2.  With FP64 storage q itself is the scratch
-// (its contents are dead whenever this runs).
+// replacement; else statistics only), in one launch.  (The FP64 stencil into a
+// vector q and an element-wise pass over it wrote and read q, 200 MB of the 920
+// that an update moves at 16^4 x 3, FP32, W = 64: fine trace 169.5 ms, 166 in one
+// launch; 16^4 multi-shift, BF16, 13.7 and 12.9; index order, 16 x 9 x 15 x 15,
+// FP32, W = 64, 4.57 and 4.44.)  One right-hand side still takes the two: its
+// stencil splits a site over 32 threads, which a launch over so few values needs.
+// With FP64 storage q itself is the scratch (its contents are dead whenever
+// this runs).
 static void true_residual(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const Launch &L, const Red &rd,
                           const CgState &cs, const double *b64, double *x64, int ru, const ProbeGen *gen) {
     const bool mixed = cfg.inner != kF64;
@@ -836,6 +840,24 @@ static void true_residual(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, co
         launch_stencil(L64, kF64, a);
         a = StencilArgs();
     }
+    if (L.W > 1) {
+        ResidArgs ra;
+        ra.links = op.links;
+        ra.diag = op.m2 + 8.0;
+        ra.b64 = b64;
+        ra.x64 = x64;
+        ra.U64 = op.U8x;
+        ra.nbr = op.nbr;
+        ra.r = ctx->at(kSlotR);
+        ra.p = ctx->at(kSlotP);
+        ra.q = ctx->at(kSlotQ);
+        ra.ru = ru;
+        ra.rd = rd;
+        ra.cs = cs;
+        ra.gen = gen;
+        launch_true_resid(L, cfg.inner, ra);
+        return;
+    }
     a.links = op.links;
     a.diag = op.m2 + 8.0;
     a.pin = x64;
@@ -843,10 +865,6 @@ static void true_residual(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, co
     a.U = op.U8x;
     a.nbr = op.nbr;
     a.cg = 0;
-    // the built-in choice, the fastest measured in index order: 16^4, W = 32:
-    // FP64 quads 100 us (although they hold 177 registers: two waves per
-    // SIMD), the LDS tile 105, x0 pairs 108, per-lane links 157; 32^4: x0
-    // lines 1504 us, pairs 1672, the LDS tile 1756, per-lane links 2417
     launch_stencil(L64, kF64, a);
     launch_resid_q(L, cfg.inner, b64, q64, ctx->at(kSlotR), ctx->at(kSlotP), ctx->at(kSlotQ), ru, rd, cs, gen);
 }
