@@ -395,15 +395,21 @@ __device__ void block_partials(const Blk &bk, const double (&val)[NV], int W, in
     block_partials_to<NV>(bk, val, W, logW, rd.part1, rd.nblk, sm);
 }
 
-// Total over the nblk partial sums of one lane, src = the lane's [nblk][NV]
-// block, in a fixed order (the same on every call): thread tid adds
-// partials tid, tid + kBlock, ... (four loads in flight), then a butterfly
-// in each wavefront and the wavefronts in order.  All threads call it; the
-// totals are valid in thread 0.  sm: NV * kBlock / 64 doubles.
-template <int NV>
-__device__ __forceinline__ void lane_total(const double *src, int nblk, double (&tot)[NV], double *sm) {
-    constexpr int kWaves = kBlock / 64;
+// Total over the nblk partial sums of one lane, srcA = the lane's [nblk][NA]
+// block (and srcB its [nblk][NB] one, both in one pass: the latencies of the
+// two loads and of the two reductions overlap), in a fixed order (the same on
+// every call): thread tid adds partials tid, tid + kBlock, ... (four loads in
+// flight), then a butterfly in each wavefront and the wavefronts in order.
+// All threads call it; the totals are valid in thread 0.  sm: (NA + NB) *
+// kBlock / 64 doubles.
+template <int NA, int NB>
+__device__ __forceinline__ void lane_totals(const double *srcA, const double *srcB, int nblk, double (&totA)[NA],
+                                            double (&totB)[NB > 0 ? NB : 1], double *sm) {
+    constexpr int kWaves = kBlock / 64, NV = NA + NB;
     const int tid = threadIdx.x;
+    auto at = [&](int b, int v) {
+        return v < NA ? srcA[(size_t)b * NA + v] : srcB[(size_t)b * NB + (v - NA)];
+    };
     double s[NV], s2[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) s[v] = s2[v] = 0.0;
@@ -411,15 +417,14 @@ __device__ __forceinline__ void lane_total(const double *src, int nblk, double (
     for (; b + 3 * kBlock < nblk; b += 4 * kBlock) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const double a0 = src[(size_t)b * NV + v], a1 = src[(size_t)(b + kBlock) * NV + v];
-            const double a2 = src[(size_t)(b + 2 * kBlock) * NV + v], a3 = src[(size_t)(b + 3 * kBlock) * NV + v];
+            const double a0 = at(b, v), a1 = at(b + kBlock, v), a2 = at(b + 2 * kBlock, v), a3 = at(b + 3 * kBlock, v);
             s[v] += a0 + a1;
             s2[v] += a2 + a3;
         }
     }
     for (; b < nblk; b += kBlock) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) s[v] += src[(size_t)b * NV + v];
+        for (int v = 0; v < NV; ++v) s[v] += at(b, v);
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -430,9 +435,19 @@ __device__ __forceinline__ void lane_total(const double *src, int nblk, double (
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        tot[v] = 0.0;
-        for (int w = 0; w < kWaves; ++w) tot[v] += sm[v * kWaves + w];
+        double t = 0.0;
+        for (int w = 0; w < kWaves; ++w) t += sm[v * kWaves + w];
+        if (v < NA)
+            totA[v] = t;
+        else
+            totB[v - NA] = t;
     }
+}
+
+template <int NV>
+__device__ __forceinline__ void lane_total(const double *src, int nblk, double (&tot)[NV], double *sm) {
+    double none[1];
+    lane_totals<NV, 0>(src, nullptr, nblk, tot, none, sm);
 }
 
 // The same total by one wavefront alone (any wavefront of the workgroup;
@@ -477,10 +492,10 @@ __device__ __forceinline__ void k_finish_body(int lane, const Red &rd, const CgS
     __shared__ double sm[NV * kBlock / 64];
     const int tid = threadIdx.x;
     if constexpr (EPI == kEpiInitEo) {
-        __shared__ double sm2[2 * kBlock / 64], rr_all;
+        __shared__ double sm6[6 * kBlock / 64], rr_all;
         double t4[4], t2[2];
-        lane_total<4>(rd.part1 + (size_t)lane * rd.nblk * 4, rd.nblk, t4, sm);
-        lane_total<2>(rd.part2 + (size_t)lane * rd.nblk * 2, rd.nblk, t2, sm2);
+        lane_totals<4, 2>(rd.part1 + (size_t)lane * rd.nblk * 4, rd.part2 + (size_t)lane * rd.nblk * 2, rd.nblk, t4, t2,
+                          sm6);
         if (tid == 0) {
             const double bb = t2[0], rr = t4[2];
             rr_all = rr;
@@ -620,8 +635,7 @@ __device__ __forceinline__ void k_finish_cg_body(int lane, const Red &rd, const 
     LaneState ls;
     if (tid == 0) ls = load_lane_state(lane, cs);
     double d3[4], d2[2];
-    lane_total<4>(rd.part1 + (size_t)lane * rd.nblk * 4, rd.nblk, d3, sm);
-    lane_total<2>(rd.part2 + (size_t)lane * rd.nblk * 2, rd.nblk, d2, sm + 4 * kBlock / 64);
+    lane_totals<4, 2>(rd.part1 + (size_t)lane * rd.nblk * 4, rd.part2 + (size_t)lane * rd.nblk * 2, rd.nblk, d3, d2, sm);
     if (tid == 0) finish_cg_epilogue(lane, cs, ls, d3, d2);
 }
 
@@ -701,44 +715,43 @@ __global__ __launch_bounds__(kBlock) void k_finish_cg(Red rd, CgState cs) { k_fi
 // ctrld[1] (mixed precision) the smallest |r|^2 / (delta^2 |r_ref|^2) of an
 // active lane not yet due a reliable update (how close the next one is;
 // 0 if there is none).
+// One wavefront; the counts and extremes of its threads meet by butterflies
+// (with one thread reading 64 of each from LDS the launch took 7.1 us, now 2.4).
 __device__ __forceinline__ void k_ctrl_body(const CgState &cs, int W) {
-    __shared__ int cnt[4][64];
-    __shared__ double worst[64], first[64];
     const int t = threadIdx.x;
     int na = 0, nk = 0, nru = 0, nb = 0;
-    double wr = 0.0, fr = 0.0;
+    double wr = 0.0, fr = HUGE_VAL;
     for (int k = t; k < W; k += 64) {
-        nb += (cs.flags[k] & kFlagBreakdown) ? 1 : 0;
+        const double rr = cs.rr[k], ref = cs.rr_ref[k], bb = cs.bb[k];
+        const int flags = cs.flags[k];
+        nb += (flags & kFlagBreakdown) ? 1 : 0;
         if (!cs.active[k]) continue;
         ++na;
-        const double goal = cs.tol2 * cs.bb[k];
-        if (cs.rr[k] <= goal) ++nk;
-        const bool due = !(cs.rr[k] >= cs.delta2 * cs.rr_ref[k]) || (cs.flags[k] & (kFlagRestart | kFlagHold));
-        if (due) {
+        const double goal = cs.tol2 * bb;
+        if (rr <= goal) ++nk;
+        const bool due = !(rr >= cs.delta2 * ref) || (flags & (kFlagRestart | kFlagHold));
+        if (due)
             ++nru;
-        } else if (!cs.exact) {
-            const double q = cs.rr[k] / (cs.delta2 * cs.rr_ref[k]);
-            fr = fr == 0.0 ? q : fmin(fr, q);
-        }
-        wr = fmax(wr, cs.rr[k] / goal);
+        else if (!cs.exact)
+            fr = fmin(fr, rr / (cs.delta2 * ref));
+        wr = fmax(wr, rr / goal);
     }
-    cnt[0][t] = na;
-    cnt[1][t] = nk;
-    cnt[2][t] = nru;
-    cnt[3][t] = nb;
-    worst[t] = wr;
-    first[t] = fr;
-    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+        na += __shfl_xor(na, off, 64);
+        nk += __shfl_xor(nk, off, 64);
+        nru += __shfl_xor(nru, off, 64);
+        nb += __shfl_xor(nb, off, 64);
+        wr = fmax(wr, __shfl_xor(wr, off, 64));
+        fr = fmin(fr, __shfl_xor(fr, off, 64));
+    }
     if (t != 0) return;
-    for (int i = 1; i < 64; ++i) {
-        for (int c = 0; c < 4; ++c) cnt[c][0] += cnt[c][i];
-        worst[0] = fmax(worst[0], worst[i]);
-        if (first[i] > 0.0) first[0] = first[0] == 0.0 ? first[i] : fmin(first[0], first[i]);
-    }
-    for (int c = 0; c < 4; ++c) cs.ctrl[c] = cnt[c][0];
-    cs.ctrld[0] = worst[0];
-    cs.ctrld[1] = first[0];
-    if (cs.live) *cs.live = cnt[0][0];
+    cs.ctrl[0] = na;
+    cs.ctrl[1] = nk;
+    cs.ctrl[2] = nru;
+    cs.ctrl[3] = nb;
+    cs.ctrld[0] = wr;
+    cs.ctrld[1] = isfinite(fr) ? fr : 0.0;
+    if (cs.live) *cs.live = na;
 }
 
 __global__ void k_ctrl(CgState cs, int W) { k_ctrl_body(cs, W); }
@@ -2490,6 +2503,14 @@ __global__ __launch_bounds__(kBlock) void k_b_finish_cg(BatchLaunch B) {
     k_finish_cg_wave_body(lane, d->rd, d->cs);
 }
 
+// One workgroup per (slot, lane).
+__global__ __launch_bounds__(kBlock) void k_b_finish_cg_wide(BatchLaunch B) {
+    const int s = blockIdx.x / B.W, lane = blockIdx.x % B.W;
+    const SlotDesc *d = B.sd + s;
+    if (!(d->flags & kSlotIter) || lane >= d->L.W || (d->cs.live && ldg(d->cs.live) == 0)) return;
+    k_finish_cg_body(lane, d->rd, d->cs);
+}
+
 __global__ void k_b_ctrl(BatchLaunch B) {
     const SlotDesc *d = B.sd + blockIdx.x;
     k_ctrl_body(d->cs, d->L.W);
@@ -3662,7 +3683,14 @@ static void b_update_t(const BatchLaunch &B, int xmode) {
 }
 
 void launch_b_update(const BatchLaunch &B, int xmode) {
-    k_b_finish_cg<<<(B.nslots * B.W + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, B.stream>>>(B);
+    // With few slots a slot has many workgroups, and a wavefront would add up
+    // its lane's partials in many rounds (9 instances, 9216 workgroups: 10.2 us,
+    // 5.7 with a workgroup per lane); with many slots there are few partials
+    // and many lanes (256 slots of 64 workgroups: 12.8 us, and 26).
+    if (B.nblocks / B.nslots > 128)
+        k_b_finish_cg_wide<<<B.nslots * B.W, kBlock, 0, B.stream>>>(B);
+    else
+        k_b_finish_cg<<<(B.nslots * B.W + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, B.stream>>>(B);
     if (B.prec == kF64) xmode = 0;  // the slots' state of mixed precision has xdef
     DP_DISPATCH_PREC(B.prec, S, B.xnt ? b_update_t<S, true>(B, xmode) : b_update_t<S, false>(B, xmode));
 }
