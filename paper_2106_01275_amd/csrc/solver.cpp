@@ -464,7 +464,7 @@ static dp_status time_iterations(dp_ctx *ctx, const OpPrep &op, int inner, const
     a.rd = rd;
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
-    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
+    const bool xdefer = xdefer_enabled();
     auto iter = [&](int xm) { launch_cg_step(Lc, inner, a, xlo, xm); };
     iter(0);
     DP_HIP(hipEventRecord(e0, Lc.stream));
@@ -574,7 +574,7 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     cs.beta = d + 5 * kMaxW;
     cs.true_rr = d + 6 * kMaxW;
     cs.tj = d + 7 * kMaxW;
-    cs.xdef = cfg.inner != kF64 ? d + 9 * kMaxW : nullptr;
+    cs.xdef = d + 9 * kMaxW;
     // the control word lives in pinned host memory: k_ctrl writes it there
     // and the host reads it after the synchronisation, no copy
     cs.ctrld = (double *)(ctx->ctrl_dev + 4);
@@ -925,9 +925,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     const double delta2 = cs.delta2, start = 1.0 / (cfg.tol * cfg.tol);
     double ratio_ref = start;
     int steps_next = ctx->pace > 0 ? plan_steps(ctx->pace, start, start, 1.0 / delta2, cfg.inner) : check_every;
-    // mixed precision takes the x updates of an iteration group in pairs
-    // (the update kernel's deferred mode)
-    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
+    // the x updates of an iteration group are taken in pairs (the update
+    // kernel's deferred mode)
+    const bool xdefer = xdefer_enabled();
     double ratio_prev = -1.0;
     int it_prev = 0, it_ru = 0;
     while (nactive > 0 && it < max_steps) {
@@ -1108,7 +1108,7 @@ static dp_status time_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, 
     a.rd = rd;
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
-    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
+    const bool xdefer = xdefer_enabled();
     auto iter = [&](int xm) { launch_cg_step(L, cfg.inner, a, xlo, xm); };
     iter(xmode_of(0, 2, xdefer));
     iter(xmode_of(1, 2, xdefer));
