@@ -1425,22 +1425,15 @@ __device__ __forceinline__ void ld_hop(const LS *__restrict__ U8, int site, int 
 // and q are one vector in a hop launch, which reads its even half and writes
 // its odd one; in kStInit each even site is read by the thread that
 // overwrites it.)
-struct HopB {  // kStHopB: where b comes from
-    const double2 *b64;
-    ProbeGen g;
-    int gen;
-};
-
 template <typename S, typename LS, int NC, bool LINKS, int MODE, int KIND>
 __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename St<S>::R diag, const S *pin,
                                                const S *__restrict__ rin, S *q, S *q2, const LS *__restrict__ U,
-                                               const int *__restrict__ nbr, int cg, Red rd, const HopB &hb) {
+                                               const int *__restrict__ nbr, int cg, Red rd) {
     if constexpr (std::is_same<S, bf16x2>::value) {
         k_stencil_bf16_body<NC, LINKS, MODE, KIND>(bk, L, diag, pin, rin, q, q2, U, nbr, cg, rd);
         return;
     }
-    constexpr bool HOP = KIND == kStHop || KIND == kStHopB;
-    constexpr bool HOPB = KIND == kStHopB;
+    constexpr bool HOP = KIND == kStHop;
     constexpr bool INIT = KIND == kStInit;
     using R = typename St<S>::R;
     constexpr bool STAGE = MODE == 1 && LINKS;
@@ -1460,8 +1453,6 @@ __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename
     const Rows<S, NC> Q(q, logW), Q2(INIT ? q2 : q, logW);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const SiteWalk wk = site_walk(L, bk, HOP ? 1 : 0);
-    const unsigned long long seedmix = HOPB && hb.gen ? mix64(hb.g.seed) : 0ull;
-    const ProbeLane pl = HOPB && hb.gen ? probe_lane(hb.g, NC, hb.g.rhs0 + j) : ProbeLane{};
     for (int t = wk.first; t * sites_per_tile < wk.items; t += wk.stride) {
         const int item0 = t * sites_per_tile;
         if (MODE == 1) stage_hops_wave<LS, R, NC, LINKS>(su, snb, wk, item0, wi, U, nbr);
@@ -1479,19 +1470,6 @@ __device__ __forceinline__ void k_stencil_body(const Blk &bk, Launch L, typename
         for (int a = 0; a < NC; ++a) {
             ar[a] = HOP ? (R)0 : diag * vr[0][a];
             ai[a] = HOP ? (R)0 : diag * vi[0][a];
-        }
-        if constexpr (HOPB) {
-            const int x = hb.gen ? lex_of(L.lat, site) : 0;
-#pragma unroll
-            for (int a = 0; a < NC; ++a) {
-                double br = 0.0, bi = 0.0;
-                if (!hb.gen)
-                    St<double2>::ld(hb.b64, vidx(site, NC, a, logW, j), br, bi);
-                else if (j < hb.g.nvalid)
-                    probe_at(hb.g, seedmix, L.lat, NC, pl, x, a, br, bi);
-                ar[a] = -br;
-                ai[a] = -bi;
-            }
         }
 #pragma unroll
         for (int dir = 0; dir < 8; ++dir) {
@@ -1672,6 +1650,12 @@ __device__ __forceinline__ void k_stencil_group_body(const Blk &bk, Launch L, ty
     block_partials<4>(bk, acc, W, logW, rd, sm);
 }
 
+struct HopB {  // kStHopB: where b comes from
+    const double2 *b64;
+    ProbeGen g;
+    int gen;
+};
+
 // MODE 5 (W = 1): one right-hand side leaves a launch with one thread per
 // site too few threads to fill the GPU (an 8^4 lattice: 16 workgroups), so
 // a site takes 32 threads: thread (h, a) = (lane / 4, lane % 4) forms row a
@@ -1763,7 +1747,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R 
         else if constexpr (MODE == 5)
             k_stencil_split_body<S, LS, NC, LINKS, KIND>(own_blk(), L, diag, pin, rin, q, q2, U, nbr, cg_, rd, hb);
         else
-            k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(own_blk(), L, diag, pin, rin, q, q2, U, nbr, cg_, rd, hb);
+            k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(own_blk(), L, diag, pin, rin, q, q2, U, nbr, cg_, rd);
     };
     if constexpr (KIND == kStHop || KIND == kStHopB) {
         body(0);
@@ -1959,12 +1943,17 @@ __global__ __launch_bounds__(kBlock) void k_fold(Launch L, double2 *__restrict__
 // storage keeps them (residual replacement; its finishing kernel takes the
 // exact line search along p) and writes the lane's total cs.qp back.
 // Otherwise (statistics) nothing is written but the norm.
-template <typename S, int NC, bool LINKS, int MODE>
+// ODD (even-odd order): the same walk over the odd sites, whose residual is made
+// zero instead: xo = (b + H x64) / c (diag: 1 / c).  The FP64 stencil body that
+// first did this holds all eight neighbours' values at once, 108 registers and
+// two waves per SIMD (64 uneven lattices, BF16, W = 32: 308 us, 235 here; 16^4,
+// FP32, W = 64: 107 and 104).
+template <typename S, int NC, bool LINKS, int MODE, bool ODD = false>
 __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, double diag, const double2 *__restrict__ b64,
                                                   const double2 *__restrict__ x64, const double2 *__restrict__ U,
                                                   const int *__restrict__ nbr, S *__restrict__ rout,
                                                   S *__restrict__ pio, const S *__restrict__ qin, int ru, Red rd,
-                                                  CgState cs, ProbeGen g, int gen) {
+                                                  CgState cs, ProbeGen g, int gen, double2 *xo = nullptr) {
     constexpr int kMaxSites = kBlock / 16;
     // STAGE: two tile buffers, each the tile's hop links then its neighbour
     // indices; the next tile is copied into one while the other is read
@@ -1980,10 +1969,10 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
     const int sl = MODE == 2 ? __builtin_amdgcn_readfirstlane(tid >> logW) : tid >> logW;
     const int sites_per_tile = kBlock >> logW;
     double acc[2] = {0.0, 0.0};
-    const SiteWalk wk = site_walk(L, bk);
+    const SiteWalk wk = site_walk(L, bk, ODD ? 1 : 0);
     const unsigned long long seedmix = gen ? mix64(g.seed) : 0ull;
     const ProbeLane pl = gen ? probe_lane(g, NC, g.rhs0 + j) : ProbeLane{};
-    const bool restart = ru && ((cs.flags[j] & kFlagRestart) || cs.ru_restart);
+    const bool restart = !ODD && ru && ((cs.flags[j] & kFlagRestart) || cs.ru_restart);
     if (STAGE && wk.first * sites_per_tile < wk.items)
         dma_tile<double2, NC>(sbuf, wk, wk.first * sites_per_tile, sites_per_tile, U, nbr);
     int cur = 0;
@@ -2011,7 +2000,7 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
         // SIMD instead of four)
         double vr[5][NC], vi[5][NC], br[NC], bi[NC];
 #pragma unroll
-        for (int k = 0; k < 5; ++k) ld_site<double2, NC>(x64, y[k], logW, j, vr[k], vi[k]);
+        for (int k = ODD ? 1 : 0; k < 5; ++k) ld_site<double2, NC>(x64, y[k], logW, j, vr[k], vi[k]);
         if (gen) {
             // probes are regenerated instead of read back (exact values)
             const int x = lex_of(L.lat, site);
@@ -2027,8 +2016,8 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
         double ar[NC], ai[NC];
 #pragma unroll
         for (int a = 0; a < NC; ++a) {
-            ar[a] = -fma(-diag, vr[0][a], br[a]);
-            ai[a] = -fma(-diag, vi[0][a], bi[a]);
+            ar[a] = ODD ? -br[a] : -fma(-diag, vr[0][a], br[a]);
+            ai[a] = ODD ? -bi[a] : -fma(-diag, vi[0][a], bi[a]);
         }
 #pragma unroll
         for (int dir = 0; dir < 8; ++dir) {
@@ -2058,6 +2047,13 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
                 mul_sub<double, NC, false>(u, vr[k], vi[k], ar, ai);
             else
                 mul_sub<double, NC, true>(u, vr[k], vi[k], ar, ai);
+        }
+        if constexpr (ODD) {
+            double2 *xrow = xo + ((size_t)(site * NC) << logW);
+#pragma unroll
+            for (int a = 0; a < NC; ++a)
+                St<double2>::st(xrow, ((size_t)a << logW) + j, -diag * ar[a], -diag * ai[a]);
+            continue;
         }
         if (ru) {
             using R = typename St<S>::R;
@@ -2090,6 +2086,7 @@ __device__ __forceinline__ void k_true_resid_body(const Blk &bk, Launch L, doubl
 #pragma unroll
         for (int a = 0; a < NC; ++a) acc[0] += ar[a] * ar[a] + ai[a] * ai[a];
     }
+    if constexpr (ODD) return;
     if (ru && cs.rq_direct) acc[1] = (bk.b == 0 && tid < W) ? cs.qp[j] : 0.0;
     if (STAGE) __syncthreads();  // every wavefront is done with the tile buffers
     block_partials_to<2>(bk, acc, W, logW, rd.part2, rd.nblk, sm);
@@ -2102,6 +2099,14 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Launch L, double diag, co
                                                        S *__restrict__ pio, const S *__restrict__ qin, int ru, Red rd,
                                                        CgState cs, ProbeGen g, int gen) {
     k_true_resid_body<S, NC, LINKS, MODE>(own_blk(), L, diag, b64, x64, U, nbr, rout, pio, qin, ru, rd, cs, g, gen);
+}
+
+template <int NC, bool LINKS, int MODE>
+__global__ __launch_bounds__(kBlock) void k_odd_x(Launch L, double hop_scale, const double2 *__restrict__ b64,
+                                                  double2 *x64, const double2 *__restrict__ U,
+                                                  const int *__restrict__ nbr, ProbeGen g, int gen) {
+    k_true_resid_body<double2, NC, LINKS, MODE, true>(own_blk(), L, hop_scale, b64, x64, U, nbr, nullptr, nullptr,
+                                                      nullptr, 0, Red{}, CgState{}, g, gen, x64);
 }
 
 // The true residual from q64 = A x64 (the FP64 stencil, run just before on
@@ -2408,15 +2413,13 @@ __global__ __launch_bounds__(kBlock) void k_b_stencil(BatchLaunch B) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, kSlotIter);
     if (!d) return;
-    const HopB none{};
     if constexpr (KIND == kStHop)
         k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)(1.0 / d->diag), (const S *)d->p,
-                                                     nullptr, (S *)d->p, nullptr, (const LS *)d->U, d->nbr, 0, d->rd,
-                                                     none);
+                                                     nullptr, (S *)d->p, nullptr, (const LS *)d->U, d->nbr, 0, d->rd);
     else
         k_stencil_body<S, LS, NC, LINKS, MODE, KIND>(bk, d->L, (typename St<S>::R)d->diag, (const S *)d->p,
                                                      (const S *)d->r, (S *)d->q, nullptr, (const LS *)d->U, d->nbr, 1,
-                                                     d->rd, none);
+                                                     d->rd);
 }
 
 // Even-odd order: the odd half of the FP64 solution, x_o = (b_o + H x_e) / c
@@ -2425,10 +2428,10 @@ __global__ __launch_bounds__(kBlock) void k_b_odd_x(BatchLaunch B, int phase) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, phase);
     if (!d) return;
-    const HopB hb{(const double2 *)d->b64, d->g, d->gen_b};
-    k_stencil_body<double2, double2, NC, LINKS, MODE, kStHopB>(bk, d->L, 1.0 / d->diag, (const double2 *)d->x64,
-                                                               nullptr, (double2 *)d->x64, nullptr,
-                                                               (const double2 *)d->U64, d->nbr, 0, d->rd, hb);
+    k_true_resid_body<double2, NC, LINKS, MODE, true>(bk, d->L, 1.0 / d->diag, (const double2 *)d->b64,
+                                                      (const double2 *)d->x64, (const double2 *)d->U64, d->nbr, nullptr,
+                                                      nullptr, nullptr, 0, d->rd, d->cs, d->g, d->gen_b,
+                                                      (double2 *)d->x64);
 }
 
 template <typename S, int XM, bool XNT>
@@ -3309,6 +3312,10 @@ static void stencil_nc(const Launch &L, const StencilArgs &a) {
         k_stencil<S, LS, NC, LINKS, M, KIND><<<grid, blk, 0, L.stream>>>(L, (R)a.diag, pin, rin, q, q2, U, a.nbr, \
                                                                          a.cg, a.rd, hb)
     constexpr int prec = std::is_same<S, double2>::value ? kF64 : (std::is_same<S, float2>::value ? kF32 : kBF16);
+    if constexpr (KIND == kStHopB) {  // (W = 1: see stencil_kind)
+        DP_ST(5);
+        return;
+    }
     const int mode = L.smode >= 0 && stencil_mode_valid(L, prec, L.smode) ? L.smode : stencil_mode_rule(L, prec);
     switch (mode) {
         case 5:
@@ -3350,12 +3357,35 @@ static void stencil_t(const Launch &L, const StencilArgs &a) {
     }
 }
 
+// The odd half of the solution (W > 1; the modes go by width as the stencil's)
+template <int NC, bool LINKS>
+static void odd_x_t(const Launch &L, const StencilArgs &a) {
+    const ProbeGen g = a.gen ? *a.gen : ProbeGen{};
+#define DP_OX(M)                                                                                                   \
+    k_odd_x<NC, LINKS, M><<<L.nblk, kBlock, 0, L.stream>>>(L, a.diag, (const double2 *)a.b64, (double2 *)a.q,      \
+                                                           (const double2 *)a.U, a.nbr, g, a.gen ? 1 : 0)
+    if (L.W >= 64)
+        DP_OX(2);
+    else if (L.W >= 16)
+        DP_OX(1);
+    else
+        DP_OX(0);
+#undef DP_OX
+}
+
+static void odd_x(const Launch &L, const StencilArgs &a) {
+    if (L.nc == 3)
+        a.links ? odd_x_t<3, true>(L, a) : odd_x_t<3, false>(L, a);
+    else
+        a.links ? odd_x_t<1, true>(L, a) : odd_x_t<1, false>(L, a);
+}
+
 template <typename S>
 static void stencil_kind(const Launch &L, const StencilArgs &a) {
     if (a.kind == kStHop) return stencil_t<S, S, kStHop>(L, a);
     if (a.kind == kStInit) return stencil_t<S, S, kStInit>(L, a);
     if constexpr (std::is_same<S, double2>::value)
-        if (a.kind == kStHopB) return stencil_t<S, S, kStHopB>(L, a);
+        if (a.kind == kStHopB) return L.W == 1 ? stencil_t<S, S, kStHopB>(L, a) : odd_x(L, a);
     stencil_t<S, S, kStFull>(L, a);
 }
 
