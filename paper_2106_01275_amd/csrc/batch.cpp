@@ -234,7 +234,11 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     for (int k = 0; k < nslots; ++k)
         it_bytes += iteration_bytes(in[jobs[k].inst].lat, nc, W, links, (double)prec_bytes(cfg.inner));
     B.xnt = update_streams_x(it_bytes);
-    B.mode = W >= 64 ? 2 : (W >= 16 ? 1 : 0);
+    // (also from W = 64 up, where a single instance's launches have a wavefront
+    // per site read its links through scalar loads: here the links' addresses
+    // come from the slot table, and those loads were per-lane ones; 64 uneven
+    // lattices, BF16: W = 64 81 -> 64 ms, 128 86 -> 68; FP32, W = 64 98 -> 73)
+    B.mode = W >= 16 ? 1 : 0;
     B.stream = s;
 
     std::vector<int> slot_job(nslots, -1), slot_it(nslots, 0), slot_ru(nslots, 0);

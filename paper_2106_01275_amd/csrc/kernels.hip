@@ -3661,9 +3661,7 @@ static void b_stencil_m(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) {
 
 template <typename S, int NC, bool LINKS, int KIND>
 static void b_stencil_t(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) {
-    if (B.mode == 2)
-        b_stencil_m<S, NC, LINKS, 2, KIND>(B, ev0, ev1);
-    else if (B.mode == 1)
+    if (B.mode == 1)
         b_stencil_m<S, NC, LINKS, 1, KIND>(B, ev0, ev1);
     else
         b_stencil_m<S, NC, LINKS, 0, KIND>(B, ev0, ev1);
@@ -3735,9 +3733,7 @@ void launch_b_iteration(const BatchLaunch &B, int xmode) {
 
 template <typename S, int NC, bool LINKS>
 static void b_tr_t(const BatchLaunch &B, int phase, int ru) {
-    if (B.mode == 2)
-        k_b_true_resid<S, NC, LINKS, 2><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase, ru);
-    else if (B.mode == 1)
+    if (B.mode == 1)
         k_b_true_resid<S, NC, LINKS, 1><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase, ru);
     else
         k_b_true_resid<S, NC, LINKS, 0><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase, ru);
@@ -3745,9 +3741,7 @@ static void b_tr_t(const BatchLaunch &B, int phase, int ru) {
 
 template <int NC, bool LINKS>
 static void b_odd_x_t(const BatchLaunch &B, int phase) {
-    if (B.mode == 2)
-        k_b_odd_x<NC, LINKS, 2><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
-    else if (B.mode == 1)
+    if (B.mode == 1)
         k_b_odd_x<NC, LINKS, 1><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
     else
         k_b_odd_x<NC, LINKS, 0><<<B.nblocks, kBlock, 0, B.stream>>>(B, phase);
