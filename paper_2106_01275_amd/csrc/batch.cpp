@@ -233,7 +233,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     double it_bytes = 0;  // of the jobs resident first (the longest)
     for (int k = 0; k < nslots; ++k)
         it_bytes += iteration_bytes(in[jobs[k].inst].lat, nc, W, links, (double)prec_bytes(cfg.inner));
-    B.xnt = update_streams_x(it_bytes);
+    B.xnt = update_streams(it_bytes);
     // (also from W = 64 up, where a single instance's launches have a wavefront
     // per site read its links through scalar loads: here the links' addresses
     // come from the slot table, and those loads were per-lane ones; 64 uneven

@@ -118,18 +118,18 @@ struct Launch {
     int ns;             // sites the CG vectors cover: N, or the even half of an even-odd order
     hipStream_t stream;
     int smode = -1;     // stencil mode (kernels.hip); -1: the built-in choice for the shape
-    int xnt = 0;        // the vector update passes x by the caches (update_streams_x)
+    int xnt = 0;        // what the vector update passes by the caches (update_streams)
 };
 
-// Whether the vector update should pass x by the caches: when the vectors
-// of an iteration (p on every site of the lattice; r, q and x) and the hop
-// links, in the storage precision, outgrow the Infinity Cache.  bytes: of one
-// complex number; several instances add up theirs.
+// What the vector update should pass by the caches: x when the vectors of an
+// iteration (p on every site of the lattice; r, q and x) and the hop links, in
+// the storage precision, outgrow the Infinity Cache, r and q too (2) from twice
+// its size.  bytes: of one complex number; several instances add up theirs.
 inline double iteration_bytes(const Lat &lat, int nc, int W, bool links, double bytes) {
     const double vec = (double)lat.N * nc * W * bytes;
     return vec * (lat.eo ? 2.5 : 4.0) + (links ? (double)lat.N * 8 * nc * nc * bytes : 0.0);
 }
-inline bool update_streams_x(double bytes) { return bytes > 256e6; }
+inline int update_streams(double bytes) { return bytes > 512e6 ? 2 : bytes > 256e6 ? 1 : 0; }
 
 // geometry fields of a launch of W right-hand sides (grid, stream and mode
 // are the caller's)

@@ -1790,11 +1790,15 @@ constexpr double kDeferBetaMin = std::is_same<S, bf16x2>::value ? 1.0 / 16 : 1.0
 
 // XNT: x passes by the caches.  Of the vectors of an iteration x alone has no
 // reader before the next update; where they are together larger than the
-// 256 MB Infinity Cache (update_streams_x), keeping x out of it leaves the
+// 256 MB Infinity Cache (update_streams), keeping x out of it leaves the
 // others more room.  16^4 x 3, FP32, W = 64 (290 MB): the fine trace 182 ms
 // with x cached, 173 past the caches; where everything fits it only costs
 // (8^4 x 3, FP64, W = 256, 140 MB: 2.44 ms and 2.54).
-template <typename S, int XM, bool XNT>
+// XNT = 2: r and q too, from twice that size on, where little of them would
+// last until its next reader (32^4 x 3, FP32, W = 32, 2.3 GB: 216.2 ms -> 214.2;
+// 64 uneven lattices, BF16, over 1 GB: 57.0 -> 56.1; at 290 MB it costs, 16^4
+// multi-shift, BF16, W = 128: 15.6 -> 16.0).
+template <typename S, int XM, int XNT>
 __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__restrict__ x, S *__restrict__ r,
                                               S *__restrict__ p, const S *__restrict__ q, Red rd, CgState cs) {
     using R = typename St<S>::R;
@@ -1831,9 +1835,9 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             St<S>::ld(p, e + u * kBlock, pr[u], pi[u]);
-            St<S>::ld(q, e + u * kBlock, qr[u], qi[u]);
-            St<S>::ld(r, e + u * kBlock, rr_[u], ri[u]);
-            if (xio) St<S>::template ld<XNT>(x, e + u * kBlock, xr[u], xi[u]);
+            St<S>::template ld<(XNT > 1)>(q, e + u * kBlock, qr[u], qi[u]);
+            St<S>::template ld<(XNT > 1)>(r, e + u * kBlock, rr_[u], ri[u]);
+            if (xio) St<S>::template ld<(XNT > 0)>(x, e + u * kBlock, xr[u], xi[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1842,10 +1846,10 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
                 xi[u] = fmaR(cdef, pi[u] - ri[u], xi[u]);
             }
             if (xio)
-                St<S>::template st<XNT>(x, e + u * kBlock, fmaR(alpha, pr[u], xr[u]), fmaR(alpha, pi[u], xi[u]));
+                St<S>::template st<(XNT > 0)>(x, e + u * kBlock, fmaR(alpha, pr[u], xr[u]), fmaR(alpha, pi[u], xi[u]));
             rr_[u] = fmaR(-alpha, qr[u], rr_[u]);
             ri[u] = fmaR(-alpha, qi[u], ri[u]);
-            St<S>::st(r, e + u * kBlock, rr_[u], ri[u]);
+            St<S>::template st<(XNT > 1)>(r, e + u * kBlock, rr_[u], ri[u]);
             // the next iteration uses the stored (rounded) residual
             St<S>::round(rr_[u], ri[u]);
             R npr = keep ? pr[u] : fmaR(beta, pr[u], rr_[u]), npi = keep ? pi[u] : fmaR(beta, pi[u], ri[u]);
@@ -1864,17 +1868,17 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
     for (; e < e1; e += kBlock) {
         R xr, xi, rr_, ri, pr, pi, qr, qi;
         St<S>::ld(p, e, pr, pi);
-        St<S>::ld(q, e, qr, qi);
-        St<S>::ld(r, e, rr_, ri);
-        if (xio) St<S>::template ld<XNT>(x, e, xr, xi);
+        St<S>::template ld<(XNT > 1)>(q, e, qr, qi);
+        St<S>::template ld<(XNT > 1)>(r, e, rr_, ri);
+        if (xio) St<S>::template ld<(XNT > 0)>(x, e, xr, xi);
         if (XM == 2) {
             xr = fmaR(cdef, pr - rr_, xr);
             xi = fmaR(cdef, pi - ri, xi);
         }
-        if (xio) St<S>::template st<XNT>(x, e, fmaR(alpha, pr, xr), fmaR(alpha, pi, xi));
+        if (xio) St<S>::template st<(XNT > 0)>(x, e, fmaR(alpha, pr, xr), fmaR(alpha, pi, xi));
         rr_ = fmaR(-alpha, qr, rr_);
         ri = fmaR(-alpha, qi, ri);
-        St<S>::st(r, e, rr_, ri);
+        St<S>::template st<(XNT > 1)>(r, e, rr_, ri);
         St<S>::round(rr_, ri);
         R npr = keep ? pr : fmaR(beta, pr, rr_), npi = keep ? pi : fmaR(beta, pi, ri);
         St<S>::st(p, e, npr, npi);
@@ -1897,7 +1901,7 @@ __device__ __forceinline__ void k_update_body(const Blk &bk, Launch L, S *__rest
     block_partials_to<2>(bk, acc, W, logW, rd.part2, rd.nblk, sm);
 }
 
-template <typename S, int XM, bool XNT>
+template <typename S, int XM, int XNT>
 __global__ __launch_bounds__(kBlock) void k_update(Launch L, S *__restrict__ x, S *__restrict__ r,
                                                    S *__restrict__ p, const S *__restrict__ q, Red rd, CgState cs) {
     k_update_body<S, XM, XNT>(own_blk(), L, x, r, p, q, rd, cs);
@@ -2434,7 +2438,7 @@ __global__ __launch_bounds__(kBlock) void k_b_odd_x(BatchLaunch B, int phase) {
                                                       (double2 *)d->x64);
 }
 
-template <typename S, int XM, bool XNT>
+template <typename S, int XM, int XNT>
 __global__ __launch_bounds__(kBlock) void k_b_update(BatchLaunch B) {
     Blk bk;
     const SlotDesc *d = slot_of_block(B, bk, kSlotIter);
@@ -3397,7 +3401,7 @@ void launch_stencil(const Launch &L, int prec, const StencilArgs &a) {
         k_finish_cg<<<L.W, kBlock, 0, L.stream>>>(a.rd, a.cs);
 }
 
-template <typename S, bool XNT>
+template <typename S, int XNT>
 static void update_t(const Launch &L, void *x, void *r, void *p, const void *q, const Red &rd, const CgState &cs,
                      int xmode) {
     if (xmode == 1)
@@ -3411,8 +3415,9 @@ static void update_t(const Launch &L, void *x, void *r, void *p, const void *q, 
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
                    const CgState &cs, int xmode) {
     DP_DISPATCH_PREC(prec, S,
-                     L.xnt ? update_t<S, true>(L, x, r, p, q, rd, cs, xmode)
-                           : update_t<S, false>(L, x, r, p, q, rd, cs, xmode));
+                     L.xnt == 0   ? update_t<S, 0>(L, x, r, p, q, rd, cs, xmode)
+                     : L.xnt == 1 ? update_t<S, 1>(L, x, r, p, q, rd, cs, xmode)
+                                  : update_t<S, 2>(L, x, r, p, q, rd, cs, xmode));
 }
 
 void launch_fold(const Launch &L, int prec, double *x64, void *xlo, int first) {
@@ -3701,7 +3706,7 @@ void launch_b_hop(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_sten
 
 void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_stencil<kStFull>(B, ev0, ev1); }
 
-template <typename S, bool XNT>
+template <typename S, int XNT>
 static void b_update_t(const BatchLaunch &B, int xmode) {
     if (xmode == 1)
         k_b_update<S, 1, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
@@ -3720,7 +3725,10 @@ void launch_b_update(const BatchLaunch &B, int xmode) {
         k_b_finish_cg_wide<<<B.nslots * B.W, kBlock, 0, B.stream>>>(B);
     else
         k_b_finish_cg<<<(B.nslots * B.W + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, B.stream>>>(B);
-    DP_DISPATCH_PREC(B.prec, S, B.xnt ? b_update_t<S, true>(B, xmode) : b_update_t<S, false>(B, xmode));
+    DP_DISPATCH_PREC(B.prec, S,
+                     B.xnt == 0   ? b_update_t<S, 0>(B, xmode)
+                     : B.xnt == 1 ? b_update_t<S, 1>(B, xmode)
+                                  : b_update_t<S, 2>(B, xmode));
 }
 
 void launch_b_reseed(const BatchLaunch &B) { k_b_reseed<<<B.nslots * B.W, kBlock, 0, B.stream>>>(B); }

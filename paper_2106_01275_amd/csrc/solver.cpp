@@ -555,7 +555,7 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     L.nblk = launch_blocks(op.lat, W);
     L.stream = s;
     L.smode = -1;
-    L.xnt = update_streams_x(iteration_bytes(op.lat, op.nc, W, op.links, prec_bytes(cfg.inner)));
+    L.xnt = update_streams(iteration_bytes(op.lat, op.nc, W, op.links, prec_bytes(cfg.inner)));
     for (int slot : {kSlotB64, kSlotX64, kSlotR, kSlotP, kSlotQ, kSlotQ64, kSlotXLo, kSlotPart1, kSlotState}) {
         const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W)
                                    : slot_size(slot, op.lat, op.nc, op.links, cfg.inner, W);
