@@ -121,8 +121,8 @@ Launch block_launch(const Lat &lat, int nc, int W, hipStream_t s) {
 }
 
 size_t gram_part_bytes(long long n, int WX, int WY) {
-    const size_t tiles = (size_t)((WX + 63) / 64) * ((WY + 63) / 64);
-    return (size_t)gram_row_blocks(n) * tiles * 64 * 64 * 16;
+    const size_t tiles = (size_t)((WX + 31) / 32) * ((WY + 31) / 32);
+    return (size_t)gram_row_blocks(n) * tiles * 32 * 32 * 16;
 }
 
 }  // namespace

@@ -354,7 +354,7 @@ void launch_axpby(long long n, double a, const double *q, double b, const double
 void launch_rand_fill(long long n, unsigned long long seed, double *v, hipStream_t s);
 void launch_scale_lanes(long long n, int W, const double *sc, const double *v, double *out, hipStream_t s);
 // H [WX][WY] = scale * X^H Y over n rows; part: workspace of gram_row_blocks(n)
-// * ceil(WX / 64) * ceil(WY / 64) * 64 * 64 complex numbers
+// * ceil(WX / 32) * ceil(WY / 32) * 32 * 32 complex numbers
 int gram_row_blocks(long long n);
 void launch_gram(long long n, int WX, int WY, const double *X, const double *Y, double *part, double scale, double *H,
                  hipStream_t s);

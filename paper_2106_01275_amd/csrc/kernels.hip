@@ -793,9 +793,10 @@ __global__ void k_prepare(Lat L, int nc, const double2 *__restrict__ abi, int *_
 }
 
 // Initialise one block of W right-hand sides: r = p = b (storage precision),
-// x = 0, and |b|^2 per lane; the finishing workgroup sets up the CG scalars.
+// xlo = 0 (x64 is the first fold's to write), and |b|^2 per lane; the finishing
+// workgroup sets up the CG scalars.
 // SRC 0: probes generated from ProbeGen (whoever needs b again regenerates
-// it); 1: from ABI b; 2: from an FP64 block src in index order; these two
+// it; index order, k_init_probe below in even-odd order); 1: from ABI b; 2: from an FP64 block src in index order; these two
 // also write b (FP64).  In even-odd order the odd half of p is -b / c, from
 // which the stencil that follows (kStInit) forms r = p = b_e + H b_o / c.
 template <typename S, int SRC>
@@ -3075,60 +3076,101 @@ __global__ void k_scale_lanes(long long n, int W, const double *__restrict__ s, 
 }
 
 // Partial products H = X^H Y over one range of rows per workgroup (blockIdx.x)
-// for one 64 x 64 output tile (blockIdx.y): part[blockIdx.x][blockIdx.y][64 * 64].
-// Rows are staged through LDS 8 at a time; thread t owns the entries
-// (t / 64 + 4 k, t % 64), k < 16, of the tile.
-constexpr int kGramTile = 64;
+// for one 32 x 32 output tile (blockIdx.y): part[blockIdx.x][blockIdx.y][32 * 32].
+// A contraction over the rows, on the FP64 matrix instruction (16 x 16 outputs,
+// four rows): lane l of a wavefront supplies column l % 16 of row l / 16 of either
+// operand, which is how it loads them (whole 256-byte rows of 16 columns), so
+// there is no LDS tile and no barrier per stage, and X and Y are all that is
+// moved.  The wavefronts take 16 rows each in turn; their sums meet in order.
+// (64 x 64 tiles staged through LDS, 16 outputs per thread, padded 16 x 32
+// outputs to 64 x 64: n = 196608, 16 x 32: 374 us, 24 now (the vectors partly in the
+// Infinity Cache).)
+constexpr int kGramTile = 32;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(kBlock) void k_gram(long long n, int WX, int WY, const double2 *__restrict__ X,
                                                  const double2 *__restrict__ Y, double2 *__restrict__ part) {
-    __shared__ double2 sx[8][kGramTile], sy[8][kGramTile];
+    __shared__ double2 sum[kGramTile * kGramTile];
     const int tilesY = (WY + kGramTile - 1) / kGramTile;
     const int i0 = (blockIdx.y / tilesY) * kGramTile, j0 = (blockIdx.y % tilesY) * kGramTile;
-    const int t = threadIdx.x, jl = t & (kGramTile - 1), il = t / kGramTile;
-    double ar[16], ai[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) ar[k] = ai[k] = 0.0;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, c = lane & 15, k = lane >> 4;
+    const int ni = i0 + 16 < WX ? 2 : 1, nj = j0 + 16 < WY ? 2 : 1;  // 16-wide halves in use
+    f64x4 re[2][2] = {}, im[2][2] = {};
     const long long r0 = n * blockIdx.x / gridDim.x, r1 = n * (blockIdx.x + 1) / gridDim.x;
-    for (long long rb = r0; rb < r1; rb += 8) {
-        __syncthreads();
-        for (int e = t; e < 8 * kGramTile; e += kBlock) {
-            const int rr = e / kGramTile, c = e % kGramTile;
-            const long long r = rb + rr;
-            sx[rr][c] = (r < r1 && i0 + c < WX) ? X[r * WX + i0 + c] : make_double2(0.0, 0.0);
-            sy[rr][c] = (r < r1 && j0 + c < WY) ? Y[r * WY + j0 + c] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
+    for (long long rb = r0 + 16 * wave; rb < r1; rb += 16 * (kBlock / 64)) {
+        double2 x[4][2], y[4][2];
 #pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-            const double2 y = sy[rr][jl];
+        for (int q = 0; q < 4; ++q) {
+            const long long r = rb + 4 * q + k;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const double2 x = sx[rr][il + 4 * k];
-                ar[k] = fma(x.x, y.x, fma(x.y, y.y, ar[k]));   // conj(x) y
-                ai[k] = fma(x.x, y.y, fma(-x.y, y.x, ai[k]));
+            for (int h = 0; h < 2; ++h) {
+                const int ci = i0 + 16 * h + c, cj = j0 + 16 * h + c;
+                x[q][h] = y[q][h] = make_double2(0.0, 0.0);
+                if (r < r1 && ci < WX) x[q][h] = ldg(X + r * WX + ci);
+                if (r < r1 && cj < WY) y[q][h] = ldg(Y + r * WY + cj);
             }
         }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    if (h >= ni || g >= nj) continue;
+                    // conj(x) y
+                    re[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][h].x, y[q][g].x, re[h][g], 0, 0, 0);
+                    re[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][h].y, y[q][g].y, re[h][g], 0, 0, 0);
+                    im[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][h].x, y[q][g].y, im[h][g], 0, 0, 0);
+                    im[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[q][h].y, y[q][g].x, im[h][g], 0, 0, 0);
+                }
+    }
+    // entry v of a lane's result: row 4 v + l / 16, column l % 16
+    for (int w = 0; w < kBlock / 64; ++w) {
+        if (wave == w)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double2 &o = sum[(16 * h + 4 * v + k) * kGramTile + 16 * g + c];
+                        const double2 a = w ? o : make_double2(0.0, 0.0);
+                        o = make_double2(a.x + re[h][g][v], a.y + im[h][g][v]);
+                    }
+        __syncthreads();
     }
     double2 *o = part + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kGramTile * kGramTile;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) o[k * kBlock + t] = make_double2(ar[k], ai[k]);
+    for (int e = t; e < kGramTile * kGramTile; e += kBlock) o[e] = sum[e];
 }
 
-// H[i][j] = scale * sum over the row ranges (in order) of the partials
-__global__ void k_gram_reduce(int nrb, int WX, int WY, const double2 *__restrict__ part, double scale,
-                              double2 *__restrict__ H) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= WX * WY) return;
-    const int i = e / WY, j = e % WY;
-    const int tilesY = (WY + kGramTile - 1) / kGramTile;
-    const int tiles = ((WX + kGramTile - 1) / kGramTile) * tilesY;
-    const int tile = (i / kGramTile) * tilesY + j / kGramTile;
-    const int off = (i % kGramTile) * kGramTile + j % kGramTile;
+// H[i][j] = scale * the sum of the partials over the row ranges: 16 entries per
+// workgroup, 16 threads to an entry (thread g adds ranges g, g + 16, ...), then
+// those in order.  (One thread per entry: 74 us for 256 ranges of 16 x 32, now
+// below 9.)
+__global__ __launch_bounds__(kBlock) void k_gram_reduce(int nrb, int WX, int WY, const double2 *__restrict__ part,
+                                                        double scale, double2 *__restrict__ H) {
+    __shared__ double2 sums[16][16];
+    const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int e = blockIdx.x * 16 + c;
     double sr = 0.0, si = 0.0;
-    for (int b = 0; b < nrb; ++b) {
-        const double2 v = part[((size_t)b * tiles + tile) * kGramTile * kGramTile + off];
-        sr += v.x;
-        si += v.y;
+    if (e < WX * WY) {
+        const int i = e / WY, j = e % WY;
+        const int tilesY = (WY + kGramTile - 1) / kGramTile;
+        const int tiles = ((WX + kGramTile - 1) / kGramTile) * tilesY;
+        const int tile = (i / kGramTile) * tilesY + j / kGramTile;
+        const int off = (i % kGramTile) * kGramTile + j % kGramTile;
+        for (int b = g; b < nrb; b += 16) {
+            const double2 v = part[((size_t)b * tiles + tile) * kGramTile * kGramTile + off];
+            sr += v.x;
+            si += v.y;
+        }
+    }
+    sums[g][c] = make_double2(sr, si);
+    __syncthreads();
+    if (g != 0 || e >= WX * WY) return;
+    for (int q = 1; q < 16; ++q) {
+        sr += sums[q][c].x;
+        si += sums[q][c].y;
     }
     H[e] = make_double2(scale * sr, scale * si);
 }
@@ -3864,7 +3906,7 @@ void launch_gram(long long n, int WX, int WY, const double *X, const double *Y, 
     const int nrb = gram_row_blocks(n);
     const int tiles = ((WX + kGramTile - 1) / kGramTile) * ((WY + kGramTile - 1) / kGramTile);
     k_gram<<<dim3(nrb, tiles), kBlock, 0, s>>>(n, WX, WY, (const double2 *)X, (const double2 *)Y, (double2 *)part);
-    k_gram_reduce<<<blocks_for((long long)WX * WY), kBlock, 0, s>>>(nrb, WX, WY, (const double2 *)part, scale,
+    k_gram_reduce<<<(WX * WY + 15) / 16, kBlock, 0, s>>>(nrb, WX, WY, (const double2 *)part, scale,
                                                                    (double2 *)H);
 }
 
