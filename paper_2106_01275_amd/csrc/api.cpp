@@ -313,11 +313,11 @@ dp_status dp_make_probes(dp_ctx *ctx, const dp_probe_spec *ps, int64_t rhs0, int
     return DP_OK;
 }
 
-// nrhs right-hand sides of one operator; s: their statistics
+// nrhs right-hand sides of one operator from `done` on; s: their statistics.
+// (A repeat without small solves goes on from the block that gave up: the x of
+// the blocks before it is written, and x may be b's own memory.)
 static dp_status solve_one(dp_ctx *ctx, const dp_operator &opd, const double *b, double *x, int64_t nrhs,
-                           int32_t rhs_block, SolveCfg cfg, hipStream_t stream, dp_solve_stats &s) {
-    const double t0 = now_s();
-    s = dp_solve_stats{};
+                           int32_t rhs_block, SolveCfg cfg, hipStream_t stream, dp_solve_stats &s, long long &done) {
     OpPrep op;
     int W = 1;
     DP_TRY(plan_solve(ctx, opd, nrhs, rhs_block, stream, cfg, op, W));
@@ -326,8 +326,8 @@ static dp_status solve_one(dp_ctx *ctx, const dp_operator &opd, const double *b,
     Red rd{};
     CgState cs{};
     DP_TRY(make_launch(ctx, op, W, stream, L, rd, cs, cfg));
-    for (long long r0 = 0; r0 < nrhs; r0 += W) {
-        const long long nv = std::min<long long>(W, nrhs - r0);
+    while (done < nrhs) {
+        const long long r0 = done, nv = std::min<long long>(W, nrhs - r0);
         BlockStats bs;
         bs.nvalid = (int)nv;
         InitAbi init{&L, cfg.inner, b, r0, nv, &rd, &cs, ctx};
@@ -335,9 +335,9 @@ static dp_status solve_one(dp_ctx *ctx, const dp_operator &opd, const double *b,
         DP_TRY(solve_block(ctx, op, cfg, L, rd, cs, x64, init, bs, &s));
         launch_to_abi(L, x64, x, r0, nv);
         DP_HIP(hipGetLastError());
+        done += nv;
     }
     DP_HIP(hipStreamSynchronize(stream));
-    s.seconds = now_s() - t0;
     return DP_OK;
 }
 
@@ -411,9 +411,13 @@ dp_status dp_solve_batch(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, con
             ctx->err = "solve_batch: bad right-hand sides";
             return DP_EINVAL;
         }
+        const double t0 = now_s();
+        long long done = 0;
         DP_TRY(with_small(ctx, [&] {
-            return solve_one(ctx, ops[i], (const double *)b[i], (double *)x[i], nrhs[i], o->rhs_block, cfg, stream, s);
+            return solve_one(ctx, ops[i], (const double *)b[i], (double *)x[i], nrhs[i], o->rhs_block, cfg, stream, s,
+                             done);
         }));
+        s.seconds = now_s() - t0;
         if (st) st[i] = s;
         dp_status fs = final_status(s);
         if (fs != DP_OK && worst == DP_OK) worst = fs;

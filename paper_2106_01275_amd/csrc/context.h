@@ -99,6 +99,7 @@ struct dp_ctx {
     unsigned long long *small_part = nullptr;
     unsigned small_tag = 0;
     bool small_off = false, small_failed = false;
+    int small_launches = 0;  // of the present call
 
     // set while a call runs on the static scratch array (dp_solve_noalloc):
     // ensure() and pool_get() then fail instead of allocating or freeing
@@ -181,6 +182,7 @@ dp_status small_check(dp_ctx *ctx);
 template <typename F>
 dp_status with_small(dp_ctx *ctx, F f) {
     ctx->small_failed = false;
+    ctx->small_launches = 0;
     dp_status st = f();
     if (!ctx->small_failed) return st;
     ctx->small_failed = false;

@@ -183,6 +183,7 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
     std::memcpy(plain_bytes, bytes, sizeof bytes);
     const double t0 = std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
     dp_solve_stats s{};
+    long long done = 0;  // right-hand sides whose x is written (it may be b's own memory)
     DP_TRY(with_small(ctx, [&]() -> dp_status {
         SolveCfg cfg = cfg0;
         std::memcpy(bytes, plain_bytes, sizeof bytes);
@@ -197,7 +198,6 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
                 std::memcpy(bytes, plain_bytes, sizeof bytes);
             }
         }
-        s = dp_solve_stats{};
         s.rhs_block = W;
         ScratchSlots scope(ctx, (char *)base, bytes);
         OpPrep opp;
@@ -211,8 +211,8 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
         // lane, the finishing kernels the whole per-lane state, and each
         // reduction all of its partial sums, so nothing left by an earlier
         // call on this GPU needs clearing
-        for (long long r0 = 0; r0 < nrhs; r0 += W) {
-            const long long nv = std::min<long long>(W, nrhs - r0);
+        while (done < nrhs) {
+            const long long r0 = done, nv = std::min<long long>(W, nrhs - r0);
             BlockStats bs;
             bs.nvalid = (int)nv;
             InitAbi init{&L, cfg.inner, (const double *)b, r0, nv, &rd, &cs, ctx};
@@ -220,6 +220,7 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
             DP_TRY(solve_block(ctx, opp, cfg, L, rd, cs, x64, init, bs, &s));
             launch_to_abi(L, x64, (double *)x, r0, nv);
             DP_HIP(hipGetLastError());
+            done += nv;
         }
         DP_HIP(hipStreamSynchronize(stream));
         return DP_OK;

@@ -349,9 +349,14 @@ static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg,
     ctx->small_tag += (unsigned)std::min<unsigned long long>(sums, 0x40000000ull);
     a.max_steps = max_steps;
     a.refine = cfg.refine;
-    // a wait gives up after some 0.2 s (DP_SMALL_POLLS: tests)
-    const char *polls = std::getenv("DP_SMALL_POLLS");
-    a.polls = polls ? std::atoi(polls) : 400000;
+    // a wait gives up after some 0.2 s (DP_SMALL_POLLS=n or n:k, tests: after n
+    // polls, from the k-th launch of a call on)
+    a.polls = 400000;
+    if (const char *e = std::getenv("DP_SMALL_POLLS")) {
+        int n = 0, k = 0;
+        if (std::sscanf(e, "%d:%d", &n, &k) >= 1 && ctx->small_launches >= k) a.polls = n;
+    }
+    ++ctx->small_launches;
     a.err = ctx->ctrl_dev + 12;
     a.cs = cs;
     a.nref = cs.flags + kMaxW;  // the first spare int of the state block
