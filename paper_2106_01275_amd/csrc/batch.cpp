@@ -74,7 +74,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     const int eo = in[0].lat.eo;  // (the same for every instance of a run)
     // even-odd order: a step counts as two iterations (solve_block)
     const int mult = eo ? 2 : 1;
-    const int max_steps = (cfg.max_iter + mult - 1) / mult, ru_gap = std::max(1, cfg.ru_gap / mult);
+    const int max_steps = step_limit(cfg.max_iter, mult), ru_gap = std::max(1, cfg.ru_gap / mult);
     const int check_every = std::max(1, ctx->check_every / mult);
     for (auto &I : in)
         if (!block_fits(I.lat, nc, W, cfg.inner)) {

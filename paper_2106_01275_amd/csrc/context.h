@@ -156,6 +156,9 @@ bool xdefer_enabled();
 // iterations without one.
 double default_reliable_delta(int inner, int eo);
 int default_ru_gap(int inner);
+// CG steps that the limit max_iter allows, a step counting as mult iterations
+// (max_iter may be the largest int)
+inline int step_limit(int max_iter, int mult) { return max_iter / mult + (max_iter % mult != 0); }
 int max_launch_blocks(const Lat &lat, int W);
 // bytes of workspace slot `slot` that prepare_operator and make_launch need
 // for this operator, inner precision and width (0: the slot is not used)

@@ -887,7 +887,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
         bs.small = 1;
         bs.it_mult = op.lat.eo ? 2 : 1;
         bs.it_cap = op.lat.eo ? cfg.max_iter : 0;
-        DP_TRY(small_block(ctx, op, cfg, L, cs, x64, init, (cfg.max_iter + bs.it_mult - 1) / bs.it_mult));
+        DP_TRY(small_block(ctx, op, cfg, L, cs, x64, init, step_limit(cfg.max_iter, bs.it_mult)));
         if (defer) {
             DP_HIP(hipMemcpyAsync(defer, cs.rr, state_bytes(), hipMemcpyDeviceToHost, L.stream));
             return DP_OK;
@@ -923,7 +923,7 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     const int mult = op.lat.eo ? 2 : 1;
     bs.it_mult = mult;
     bs.it_cap = op.lat.eo ? cfg.max_iter : 0;
-    const int max_steps = (cfg.max_iter + mult - 1) / mult, ru_gap = std::max(1, cfg.ru_gap / mult);
+    const int max_steps = step_limit(cfg.max_iter, mult), ru_gap = std::max(1, cfg.ru_gap / mult);
     const int check_every = std::max(1, ctx->check_every / mult);
     // Iterations between host checks: start with check_every, then predict
     // from the decay of the slowest lane's residual since the last check.
