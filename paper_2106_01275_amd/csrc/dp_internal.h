@@ -338,6 +338,8 @@ constexpr int kSmallThreads = 512;
 constexpr int kSmallMaxGrid = 256;       // one workgroup per CU
 constexpr size_t kSmallPartBytes = (size_t)2 * kSmallMaxGrid * 8 * 2 * 8;
 void launch_small(const SmallArgs &a, hipStream_t s);
+// zeroes the partial sums' words
+void launch_small_clear(unsigned long long *part, hipStream_t s);
 
 // Deflation (dense pieces over FP64 blocks [n rows][width], index order)
 // the probes of g, FP64, index order

@@ -2681,6 +2681,10 @@ __device__ __forceinline__ bool small_sum(const SmallArgs &A, SmallShared &sh, u
     return true;
 }
 
+__global__ __launch_bounds__(kBlock) void k_small_clear(unsigned long long *part) {
+    stg(part + (size_t)blockIdx.x * kBlock + threadIdx.x, 0ull);
+}
+
 template <int NC, bool LINKS, bool EO, int WG>
 __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
     static_assert(2 * WG <= 8, "two sums per lane");
@@ -3667,6 +3671,11 @@ void launch_small(const SmallArgs &a, hipStream_t s) {
         else
             a.lat.eo ? small_t<1, false, true>(a, s) : small_t<1, false, false>(a, s);
     }
+}
+
+void launch_small_clear(unsigned long long *part, hipStream_t s) {
+    static_assert(kSmallPartBytes % (8 * kBlock) == 0, "whole workgroups of words");
+    k_small_clear<<<kSmallPartBytes / (8 * kBlock), kBlock, 0, s>>>(part);
 }
 
 void launch_to_abi(const Launch &L, const double *x64, double *xabi, long long rhs0, long long nvalid) {

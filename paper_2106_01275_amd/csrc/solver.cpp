@@ -341,12 +341,12 @@ static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg,
     const unsigned long long rounds = (L.W + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
     const unsigned long long sums = rounds * (6ull * (unsigned)max_steps + 8);
     if (ctx->small_tag + sums >= 0xffffffffull) {
-        DP_HIP(hipStreamSynchronize(L.stream));
-        DP_HIP(hipMemset(ctx->small_part, 0, kSmallPartBytes));
+        // in the stream's order: after the launches queued there, before this one
+        launch_small_clear(ctx->small_part, L.stream);
         ctx->small_tag = 0;
     }
     a.tag = ctx->small_tag;
-    ctx->small_tag += (unsigned)std::min<unsigned long long>(sums, 0x40000000ull);
+    ctx->small_tag = (unsigned)std::min<unsigned long long>(a.tag + sums, 0xffffffffull);
     a.max_steps = max_steps;
     a.refine = cfg.refine;
     // a wait gives up after some 0.2 s (DP_SMALL_POLLS=n or n:k, tests: after n
