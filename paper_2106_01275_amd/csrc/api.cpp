@@ -190,8 +190,8 @@ dp_status dp_create(dp_ctx **out, int32_t hip_device) {
         return DP_ENOMEM;
     }
     std::memset(ctx->ctrl_host, 0, 64);
-    if (hipMalloc((void **)&ctx->small_part, kSmallPartBytes) != hipSuccess ||
-        hipMemset(ctx->small_part, 0, kSmallPartBytes) != hipSuccess) {
+    if (hipMalloc((void **)&ctx->small_part, kSmallBytes) != hipSuccess ||
+        hipMemset(ctx->small_part, 0, kSmallBytes) != hipSuccess) {
         g_err = "dp_create: device allocation failed";
         dp_destroy(ctx);
         return DP_ENOMEM;
@@ -413,7 +413,7 @@ dp_status dp_solve_batch(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, con
         }
         const double t0 = now_s();
         long long done = 0;
-        DP_TRY(with_small(ctx, [&] {
+        DP_TRY(with_small(ctx, stream, [&] {
             return solve_one(ctx, ops[i], (const double *)b[i], (double *)x[i], nrhs[i], o->rhs_block, cfg, stream, s,
                              done);
         }));
@@ -561,7 +561,7 @@ static dp_status trace_one(dp_ctx *ctx, const dp_operator &opd, int32_t p, const
         ctx->err = "trace_estimate: p must be >= 0";
         return DP_EINVAL;
     }
-    return with_small(ctx, [&] { return trace_displacements(ctx, opd, &p, 1, ps, o, cfg, &out, stream); });
+    return with_small(ctx, stream, [&] { return trace_displacements(ctx, opd, &p, 1, ps, o, cfg, &out, stream); });
 }
 
 dp_status dp_trace_estimate(dp_ctx *ctx, int32_t ninst, const dp_operator *ops, const int32_t *p,
@@ -659,7 +659,7 @@ dp_status dp_trace_multi(dp_ctx *ctx, const dp_operator *op, const int32_t *disp
         ~Leave() { (void)w.leave(); }
     } leave_{ws_};
     dp_status st =
-        with_small(ctx, [&] { return trace_displacements(ctx, *op, disp, ndisp, *ps, o, cfg, out, ws_.s); });
+        with_small(ctx, ws_.s, [&] { return trace_displacements(ctx, *op, disp, ndisp, *ps, o, cfg, out, ws_.s); });
     if (st == DP_ENOCONV) ctx->err = "trace_multi: some right-hand sides did not converge";
     if (st == DP_EBREAKDOWN) ctx->err = "trace_multi: CG breakdown";
     return st;
@@ -713,7 +713,7 @@ dp_status dp_trace_levels(dp_ctx *ctx, const dp_operator *op, int32_t p, const d
         }
     }
     std::vector<int32_t> disp(ncoarse + 1, p);
-    dp_status st = with_small(ctx, [&] {
+    dp_status st = with_small(ctx, ws_.s, [&] {
         return trace_displacements(ctx, *op, disp.data(), ncoarse + 1, *ps, o, cfg, out, ws_.s, cols.data(),
                                    maps.data());
     });
@@ -742,7 +742,7 @@ dp_status dp_trace_grad(dp_ctx *ctx, const dp_operator *opd, int32_t p, const dp
     } leave_{ws_};
     stream = ws_.s;
     dp_solve_stats s{};
-    DP_TRY(with_small(ctx, [&]() -> dp_status {
+    DP_TRY(with_small(ctx, stream, [&]() -> dp_status {
         SolveCfg cfg = cfg0;
         OpPrep op;
         const int ndil = ps->dilute ? ps->nc : 1;
@@ -943,7 +943,7 @@ dp_status dp_trace_deflated(dp_ctx *ctx, const dp_operator *opd, const dp_deflat
     DP_TRY(deflation_trace_part(ctx, *d, p, stream, td));
     dp_solve_stats s{};
     std::vector<double> tj;
-    DP_TRY(with_small(ctx, [&]() -> dp_status {
+    DP_TRY(with_small(ctx, stream, [&]() -> dp_status {
         SolveCfg cfg = cfg0;
         OpPrep op;
         const int ndil = ps->dilute ? ps->nc : 1;

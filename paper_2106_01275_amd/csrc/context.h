@@ -99,7 +99,9 @@ struct dp_ctx {
     unsigned long long *small_part = nullptr;
     unsigned small_tag = 0;
     bool small_off = false, small_failed = false;
-    int small_launches = 0;  // of the present call
+    int small_launches = 0;      // of the present call
+    bool small_pending = false;  // launches that no small_check has followed
+    bool small_stopped = false;  // the stop word is set
 
     // set while a call runs on the static scratch array (dp_solve_noalloc):
     // ensure() and pool_get() then fail instead of allocating or freeing
@@ -181,12 +183,20 @@ dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int re
 // after a synchronisation: DP_EHIP, with ctx->small_failed set, when a small
 // solve gave up
 dp_status small_check(dp_ctx *ctx);
-// Runs f; when a small solve of it gave up, once more without them.
+// Runs f, whose work is on s; when a small solve of it gave up, once more
+// without them.
 template <typename F>
-dp_status with_small(dp_ctx *ctx, F f) {
+dp_status with_small(dp_ctx *ctx, hipStream_t s, F f) {
     ctx->small_failed = false;
     ctx->small_launches = 0;
     dp_status st = f();
+    if (ctx->small_pending) {  // f ended early, for a reason of its own
+        const std::string err = ctx->err;
+        (void)hipStreamSynchronize(s);
+        (void)small_check(ctx);
+        ctx->err = err;
+        return st;
+    }
     if (!ctx->small_failed) return st;
     ctx->small_failed = false;
     ctx->small_off = true;

@@ -330,16 +330,19 @@ struct SmallArgs {
     unsigned tag;            // of the launch's sums: the numbers from tag + 1 up
     int max_steps, refine;   // refine: converged means the true residual meets tol
     int polls;               // after which a wait gives up
-    int *err;                // set when a wait ran out
+    int *err;                // set when a wait ran out (host memory)
+    unsigned *stop;          // the same in device memory: later launches end at once
     CgState cs;
     int *nref;               // true-residual checks made (refine)
 };
 constexpr int kSmallThreads = 512;
 constexpr int kSmallMaxGrid = 256;       // one workgroup per CU
 constexpr size_t kSmallPartBytes = (size_t)2 * kSmallMaxGrid * 8 * 2 * 8;
+constexpr size_t kSmallBytes = kSmallPartBytes + 256;  // and the stop word
 void launch_small(const SmallArgs &a, hipStream_t s);
 // zeroes the partial sums' words
 void launch_small_clear(unsigned long long *part, hipStream_t s);
+void launch_small_go(unsigned *stop, hipStream_t s);  // zeroes the stop word
 
 // Deflation (dense pieces over FP64 blocks [n rows][width], index order)
 // the probes of g, FP64, index order

@@ -2568,7 +2568,8 @@ __global__ void k_b_ctrl(BatchLaunch B) {
 // 9 us with 64 workgroups and 32 with 256: they queue at the XCD's L2.)
 // Every wait is bounded: should some workgroup not become resident (other
 // work holding the CUs), all give up, set *err and the host solves the block
-// with the launched kernels instead.
+// with the launched kernels instead; *stop keeps the launches already queued
+// behind from waiting in their turn.
 
 __device__ __forceinline__ double ldc(const double *p) {
     return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
@@ -2621,8 +2622,9 @@ struct SmallShared {
 // every thread gets in out[l]; any: whether some lane's `active` is set after
 // it.  False when a wait ran out.
 template <int WG, typename F>
-__device__ __forceinline__ bool small_sum(const SmallArgs &A, SmallShared &sh, unsigned &tag, const double (&v)[8],
-                                          const int &active, F step, double (&out)[WG], int &any) {
+__device__ __forceinline__ bool small_sum(const SmallArgs &A, SmallShared &sh, int polls, unsigned &tag,
+                                          const double (&v)[8], const int &active, F step, double (&out)[WG],
+                                          int &any) {
     const int tid = threadIdx.x, n = A.nwg, lane = tid & 63, wave = tid >> 6;
     const int group = blockIdx.x % A.ngroups, wb = blockIdx.x / A.ngroups;
     auto wave_sum = [&](double a) {  // a: value tid % 8
@@ -2652,16 +2654,15 @@ __device__ __forceinline__ bool small_sum(const SmallArgs &A, SmallShared &sh, u
     }
     int good = 1;
     double a = 0.0;
-    for (int w = tid >> 3; w < n; w += kSmallThreads >> 3) {
+    for (int w = tid >> 3; w < n; w += kSmallThreads >> 3) {  // (polls: of all its words together)
         const unsigned long long *e = part + ((size_t)w * 8 + (tid & 7)) * 2;
         unsigned long long lo = 0, hi = 0;
-        int k = 0;
-        for (; k < A.polls; ++k) {
+        for (; polls > 0; --polls) {
             lo = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             hi = __hip_atomic_load(e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((lo >> 32) == tag && (hi >> 32) == tag) break;
         }
-        good &= k < A.polls;
+        good &= polls > 0;
         a += __builtin_bit_cast(double, (hi << 32) | (lo & 0xffffffffull));
     }
     if (!__syncthreads_and(good)) return false;
@@ -2685,6 +2686,8 @@ __global__ __launch_bounds__(kBlock) void k_small_clear(unsigned long long *part
     stg(part + (size_t)blockIdx.x * kBlock + threadIdx.x, 0ull);
 }
 
+__global__ void k_small_go(unsigned *stop) { stg(stop, 0u); }
+
 template <int NC, bool LINKS, bool EO, int WG>
 __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
     static_assert(2 * WG <= 8, "two sums per lane");
@@ -2701,6 +2704,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
     // this thread's component of its sites: colour ca, real or imaginary part
     const bool own = live && h < 2 * NC;
     const int ca = own ? h >> 1 : 0, im = h & 1;
+    // the launches queued behind one that gave up end at their first sum
+    // (loaded here, waited for there)
+    const int polls = __hip_atomic_load(A.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0 : A.polls;
     const double c = A.c, ic = 1.0 / A.c;
     const unsigned long long seedmix = A.src == 0 ? mix64(A.g.seed) : 0ull;
     const CgState &cs = A.cs;
@@ -2768,7 +2774,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
     int cur = 0;
     double v[8], out[WG];
     auto give_up = [&]() {
-        if (tid == 0) *A.err = 1;
+        if (tid != 0) return;
+        __hip_atomic_store(A.stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *A.err = 1;
     };
     auto advance = [&]() {
         cur = cur + 1 < A.nring ? cur + 1 : 0;
@@ -2842,7 +2850,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
             publish(Rk(cur), l, r[l]);
         }
         double beta[WG];
-        if (!small_sum<WG>(A, sh, tag, v, active,
+        if (!small_sum<WG>(A, sh, polls, tag, v, active,
                            [&](double t0, double t1) {
                                rr = rr_first = t0;
                                bb = t1;
@@ -2880,7 +2888,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
                     }
                 }
                 double alpha[WG];
-                if (!small_sum<WG>(A, sh, tag, v, active,
+                if (!small_sum<WG>(A, sh, polls, tag, v, active,
                                    [&](double t0, double t1) {
                                        const double pq = EO ? c * (t0 - t1) : t0;
                                        if (!active) return 0.0;
@@ -2911,7 +2919,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
                     publish(Rk(next), l, r[l]);
                     v[2 * l] = r[l] * r[l];
                 }
-                if (!small_sum<WG>(A, sh, tag, v, active,
+                if (!small_sum<WG>(A, sh, polls, tag, v, active,
                                    [&](double t0, double) {
                                        if (!active) return 0.0;
                                        const double f = t0 / rr;
@@ -2928,7 +2936,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
 #pragma unroll
             for (int l = 0; l < WG; ++l) publish(Rk(cur), l, x[l]);
             clear();
-            if (!small_sum<WG>(A, sh, tag, v, active, none, out, any)) return give_up();
+            if (!small_sum<WG>(A, sh, polls, tag, v, active, none, out, any)) return give_up();
             if (EO) {
 #pragma unroll
                 for (int l = 0; l < WG; ++l) {
@@ -2939,7 +2947,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
                     publish(Wk(cur), l, xo);
                     if (own && l0 + l < A.W) A.x[2 * ((size_t)((ns + s) * NC + ca) * A.W + l0 + l) + im] = xo;
                 }
-                if (!small_sum<WG>(A, sh, tag, v, active, none, out, any)) return give_up();
+                if (!small_sum<WG>(A, sh, polls, tag, v, active, none, out, any)) return give_up();
             }
             const int next = cur + 1 < A.nring ? cur + 1 : 0;
 #pragma unroll
@@ -2955,7 +2963,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
                 }
             }
             ++nref;
-            if (!small_sum<WG>(A, sh, tag, v, active,
+            if (!small_sum<WG>(A, sh, polls, tag, v, active,
                                [&](double t0, double) {
                                    true_rr = t0;
                                    if (!A.refine) {
@@ -3677,6 +3685,8 @@ void launch_small_clear(unsigned long long *part, hipStream_t s) {
     static_assert(kSmallPartBytes % (8 * kBlock) == 0, "whole workgroups of words");
     k_small_clear<<<kSmallPartBytes / (8 * kBlock), kBlock, 0, s>>>(part);
 }
+
+void launch_small_go(unsigned *stop, hipStream_t s) { k_small_go<<<1, 1, 0, s>>>(stop); }
 
 void launch_to_abi(const Launch &L, const double *x64, double *xabi, long long rhs0, long long nvalid) {
     const long long n = (long long)L.lat.N * L.nc * L.W;

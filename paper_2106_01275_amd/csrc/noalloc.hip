@@ -184,7 +184,7 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
     const double t0 = std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
     dp_solve_stats s{};
     long long done = 0;  // right-hand sides whose x is written (it may be b's own memory)
-    DP_TRY(with_small(ctx, [&]() -> dp_status {
+    DP_TRY(with_small(ctx, stream, [&]() -> dp_status {
         SolveCfg cfg = cfg0;
         std::memcpy(bytes, plain_bytes, sizeof bytes);
         if (small_problem(ctx, red, op->nc, nrhs, cfg)) {

@@ -306,8 +306,10 @@ dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int re
 }
 
 dp_status small_check(dp_ctx *ctx) {
+    ctx->small_pending = false;
     if (!ctx->ctrl_host[12]) return DP_OK;
     ctx->ctrl_host[12] = 0;
+    ctx->small_stopped = true;
     ctx->small_failed = true;
     ctx->err = "internal: a persistent solve did not become resident";
     return DP_EHIP;
@@ -358,6 +360,10 @@ static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg,
     }
     ++ctx->small_launches;
     a.err = ctx->ctrl_dev + 12;
+    a.stop = (unsigned *)((char *)ctx->small_part + kSmallPartBytes);
+    if (ctx->small_stopped) launch_small_go(a.stop, L.stream);
+    ctx->small_stopped = false;
+    ctx->small_pending = true;
     a.cs = cs;
     a.nref = cs.flags + kMaxW;  // the first spare int of the state block
     launch_small(a, L.stream);

@@ -64,3 +64,36 @@ def test_in_place_solve_goes_on(ctx, problem, monkeypatch, inner, first):
         assert st["nrhs"] == st["nconverged"] == len(B)
         err = np.abs(X.cpu().numpy() - Xo).max() / np.abs(Xo).max()
         assert err < (1e-10 if inner == "f64" else 1e-8), (call, err)
+
+
+@pytest.mark.parametrize("first", [0, 7])
+def test_queued_launches_give_way(ctx, monkeypatch, first):
+    """Estimates whose blocks are queued one behind the other (a trace, every
+    level's adjoint, deflated probes): the first or the eighth launch gives up,
+    those behind it end at once, and the call's results are the launched
+    kernels' own, as are the next calls' to the bars of the tolerance (1e-10 of
+    the largest)."""
+    _say("queue", first)
+    dims = (4, 4, 6, 4)
+    U = workloads.random_links(dims, 0.4, 3)
+    col, m, _ = oracle.coloring(dims, 1, 2, oracle.NATURAL)
+    op = ctx.operator(dims, 3, 0.3, cuda(U))
+    ps = ctx.probe_spec(dims, 3, cuda(col), m, 5, 0, 2, "z2_complex", True)
+    o = ctx.opts(tol=1e-12, rhs_block=2)
+    d = ctx.deflation(op, 6, tol=1e-8, seed=2)
+    calls = (lambda: ctx.trace_estimate([op], [ps], [1], o)[0]["tj"],
+             lambda: np.concatenate([np.ravel(v.cpu().numpy() if torch.is_tensor(v) else v)
+                                     for v in ctx.trace_grad(op, ps, 1, o)[:4]]),
+             lambda: ctx.trace_deflated(op, d, 1, ps, o)["tj"])
+    for k, call in enumerate(calls):
+        monkeypatch.setenv("DP_SMALL", "0")
+        ref = call()
+        monkeypatch.setenv("DP_SMALL", "1")
+        before = call()
+        monkeypatch.setenv("DP_SMALL_POLLS", f"0:{first}")
+        got = call()
+        monkeypatch.delenv("DP_SMALL_POLLS")
+        assert np.array_equal(got, ref), k
+        for after in (before, call(), call(), call()):
+            assert np.abs(after - ref).max() < 1e-10 * np.abs(ref).max(), k
+    d.close()
