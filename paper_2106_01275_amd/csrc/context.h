@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <map>
 #include <string>
@@ -102,6 +103,9 @@ struct dp_ctx {
     int small_launches = 0;      // of the present call
     bool small_pending = false;  // launches that no small_check has followed
     bool small_stopped = false;  // the stop word is set
+    // calls that would take small solves but do not try for now, and how many
+    // did not after the last failure
+    int small_skip = 0, small_backoff = 0;
 
     // set while a call runs on the static scratch array (dp_solve_noalloc):
     // ensure() and pool_get() then fail instead of allocating or freeing
@@ -170,7 +174,7 @@ size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W)
 constexpr int kSmallRing = 8;
 size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int nring = kSmallRing);
 // Whether nrhs right-hand sides take the small solves (whatever the width).
-bool small_problem(const dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg);
+bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg);
 inline int pow2_above(long long n) {
     int w = 1;
     while (w < n) w *= 2;
@@ -184,7 +188,11 @@ dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int re
 // solve gave up
 dp_status small_check(dp_ctx *ctx);
 // Runs f, whose work is on s; when a small solve of it gave up, once more
-// without them.
+// without them.  Other work that holds the CUs may last: after a failure the
+// next call that could take small solves does not try, after another failure
+// the next two, four, .. kSmallBackoff (a failure costs a wait of about 0.2 s;
+// a solve that succeeds ends the count).
+constexpr int kSmallBackoff = 256;
 template <typename F>
 dp_status with_small(dp_ctx *ctx, hipStream_t s, F f) {
     ctx->small_failed = false;
@@ -197,7 +205,12 @@ dp_status with_small(dp_ctx *ctx, hipStream_t s, F f) {
         ctx->err = err;
         return st;
     }
-    if (!ctx->small_failed) return st;
+    if (!ctx->small_failed) {
+        if (ctx->small_launches > 0) ctx->small_backoff = 0;
+        return st;
+    }
+    ctx->small_skip = ctx->small_backoff =
+        ctx->small_backoff == 0 ? 1 : std::min(kSmallBackoff, 2 * ctx->small_backoff);
     ctx->small_failed = false;
     ctx->small_off = true;
     st = f();

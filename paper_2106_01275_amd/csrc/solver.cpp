@@ -240,7 +240,7 @@ static SmallShape small_shape(const Lat &lat, long long n) {
     return z;
 }
 
-bool small_problem(const dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg) {
+bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg) {
     const long long ns = lat.eo ? lat.N / 2 : lat.N;
     if (ctx->small_off || cfg.profile || nrhs < 1 || ns > kSmallMaxGrid * (kSmallThreads / 8) || !small_enabled())
         return false;
@@ -255,7 +255,12 @@ bool small_problem(const dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, co
     const double base = lat.eo ? (z.wg == 1 ? 8.5 : (z.wg == 2 ? 12.0 : 19.0))
                                : (z.wg == 1 ? 8.0 : (z.wg == 2 ? 10.0 : 13.0));
     const double bytes = (double)ns * nrhs * nc * prec_bytes(cfg.inner) * (lat.eo ? 12.0 : 9.0);
-    return rounds * (base + 0.015 * z.nwg) < 21.0 + bytes / 4.5e6;
+    if (!(rounds * (base + 0.015 * z.nwg) < 21.0 + bytes / 4.5e6)) return false;
+    if (ctx->small_skip > 0) {  // (asked once for each attempt at a call)
+        --ctx->small_skip;
+        return false;
+    }
+    return true;
 }
 
 // one slot of the groups' rings (r and p_o of a step), whose vectors start on

@@ -97,3 +97,32 @@ def test_queued_launches_give_way(ctx, monkeypatch, first):
         for after in (before, call(), call(), call()):
             assert np.abs(after - ref).max() < 1e-10 * np.abs(ref).max(), k
     d.close()
+
+
+def test_failures_are_remembered(ctx, problem, monkeypatch):
+    """Under lasting contention a context does not wait in every call: after a
+    failure the next call that could take a persistent launch does not try, after
+    a second one in a row the next two, and so on; a success ends that.  (The two
+    paths round differently, so bits tell which one a call took.)"""
+    _say("remembered")
+    dims, U, B, _ = problem
+    op, b = ctx.operator(dims, 3, 0.2, cuda(U)), cuda(B)
+    o = ctx.opts(tol=1e-11, rhs_block=16)
+    solve = lambda: ctx.solve_batch([op], [b], o)[0][0]  # noqa: E731
+    monkeypatch.setenv("DP_SMALL", "0")
+    launched = solve()
+    monkeypatch.setenv("DP_SMALL", "1")
+    for _ in range(256):  # (whatever calls before this test left)
+        small = solve()
+        if not torch.equal(small, launched):
+            break
+    took = lambda: "launched" if torch.equal(solve(), launched) else "small"  # noqa: E731
+    assert took() == took() == "small" and torch.equal(solve(), small)
+    for turn in range(2):  # (the second time as the first: the success between them ended the count)
+        for skipped in (1, 2, 4):
+            monkeypatch.setenv("DP_SMALL_POLLS", "0")
+            assert took() == "launched"
+            monkeypatch.delenv("DP_SMALL_POLLS")
+            for _ in range(skipped):
+                assert took() == "launched"
+        assert took() == took() == "small"
