@@ -190,6 +190,13 @@ dp_status dp_create(dp_ctx **out, int32_t hip_device) {
         return DP_ENOMEM;
     }
     std::memset(ctx->ctrl_host, 0, 64);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) != hipSuccess || cus < 1) {
+        g_err = "dp_create: hipDeviceGetAttribute failed";
+        dp_destroy(ctx);
+        return DP_EHIP;
+    }
+    ctx->small_grid = std::min(kSmallMaxGrid, cus);
     if (hipMalloc((void **)&ctx->small_part, kSmallBytes) != hipSuccess ||
         hipMemset(ctx->small_part, 0, kSmallBytes) != hipSuccess) {
         g_err = "dp_create: device allocation failed";

@@ -99,6 +99,9 @@ struct dp_ctx {
     // out, after which it is repeated with small_off
     unsigned long long *small_part = nullptr;
     unsigned small_tag = 0;
+    // workgroups that can be resident together: the device's compute units (at
+    // least one fits each, by the kernel's launch bounds and LDS)
+    int small_grid = dp::kSmallMaxGrid;
     bool small_off = false, small_failed = false;
     int small_launches = 0;      // of the present call
     bool small_pending = false;  // launches that no small_check has followed
@@ -172,7 +175,13 @@ size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W)
 // the same for small solves; nring (>= 2) slots of the steps' vectors, between
 // whose uses the caches are dropped: few make that more frequent
 constexpr int kSmallRing = 8;
-size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int nring = kSmallRing);
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int grid, int nring = kSmallRing);
+// Workgroups of a group (nwg), lanes of a group (wg) and groups side by side for
+// n lanes, at most `grid` workgroups (if one group fits).
+struct SmallShape {
+    int nwg, wg, ngroups;
+};
+SmallShape small_shape(const Lat &lat, long long n, int grid);
 // Whether nrhs right-hand sides take the small solves (whatever the width).
 bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg);
 inline int pow2_above(long long n) {

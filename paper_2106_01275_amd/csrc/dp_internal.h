@@ -336,7 +336,7 @@ struct SmallArgs {
     int *nref;               // true-residual checks made (refine)
 };
 constexpr int kSmallThreads = 512;
-constexpr int kSmallMaxGrid = 256;       // one workgroup per CU
+constexpr int kSmallMaxGrid = 256;       // at most; one workgroup per CU of the device
 constexpr size_t kSmallPartBytes = (size_t)2 * kSmallMaxGrid * 8 * 2 * 8;
 constexpr size_t kSmallBytes = kSmallPartBytes + 256;  // and the stop word
 void launch_small(const SmallArgs &a, hipStream_t s);

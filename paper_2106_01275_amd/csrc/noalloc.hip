@@ -60,10 +60,11 @@ struct ScratchSlots {
 
 // Scratch bytes of a solve at width W (the slots that prepare_operator and
 // make_launch take; the colour slot of the autotuner is never used here).
-size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots], int nring = 0) {
+size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots], int grid = 0,
+              int nring = 0) {
     size_t tot = 0;
     for (int s = 0; s < kNumSlots; ++s) {
-        bytes[s] = nring ? small_slot_size(s, lat, nc, links, W, nring) : slot_size(s, lat, nc, links, inner, W);
+        bytes[s] = nring ? small_slot_size(s, lat, nc, links, W, grid, nring) : slot_size(s, lat, nc, links, inner, W);
         tot += align256(bytes[s]);
     }
     return tot;
@@ -189,8 +190,9 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
         std::memcpy(bytes, plain_bytes, sizeof bytes);
         if (small_problem(ctx, red, op->nc, nrhs, cfg)) {
             int nring = kSmallRing;
-            while (nring > 2 && layout(red, op->nc, links, kF64, W, bytes, nring) > kScratchBytes) --nring;
-            if (layout(red, op->nc, links, kF64, W, bytes, nring) <= kScratchBytes) {
+            const int grid = ctx->small_grid;
+            while (nring > 2 && layout(red, op->nc, links, kF64, W, bytes, grid, nring) > kScratchBytes) --nring;
+            if (layout(red, op->nc, links, kF64, W, bytes, grid, nring) <= kScratchBytes) {
                 cfg.small = 1;
                 cfg.refine = cfg.inner != kF64;
                 cfg.inner = kF64;

@@ -226,15 +226,11 @@ static bool small_enabled() {
     return !(e && std::strcmp(e, "0") == 0);
 }
 
-// Workgroups of a group, lanes of a group and groups for n lanes side by side
-struct SmallShape {
-    int nwg, wg, ngroups;
-};
-static SmallShape small_shape(const Lat &lat, long long n) {
+SmallShape small_shape(const Lat &lat, long long n, int grid) {
     SmallShape z;
     const long long ns = lat.eo ? lat.N / 2 : lat.N;
     z.nwg = (int)((ns + kSmallThreads / 8 - 1) / (kSmallThreads / 8));
-    const int fit = std::max(1, kSmallMaxGrid / z.nwg);  // groups that are resident together
+    const int fit = std::max(1, grid / z.nwg);  // groups that are resident together
     z.wg = n <= fit ? 1 : (n <= 2 * fit ? 2 : 4);
     z.ngroups = (int)std::min<long long>(fit, (n + z.wg - 1) / z.wg);
     return z;
@@ -242,7 +238,8 @@ static SmallShape small_shape(const Lat &lat, long long n) {
 
 bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg) {
     const long long ns = lat.eo ? lat.N / 2 : lat.N;
-    if (ctx->small_off || cfg.profile || nrhs < 1 || ns > kSmallMaxGrid * (kSmallThreads / 8) || !small_enabled())
+    if (ctx->small_off || cfg.profile || nrhs < 1 || ns > (long long)ctx->small_grid * (kSmallThreads / 8) ||
+        !small_enabled())
         return false;
     // microseconds per CG step of all right-hand sides: a small solve's rounds
     // one after another, against the launched kernels' latency and traffic.
@@ -250,7 +247,7 @@ bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const So
     // 23), 8 (one a group) 10 (29), 16 (two) 12 (30), 32 (four) 19 (33), 64
     // (two rounds of four) 39 (37); odd extents 9 x 10 x 7 x 12: one 7.7 (19),
     // 8 (four) 14 (23), 20 (three rounds) 30 (30)
-    const SmallShape z = small_shape(lat, nrhs);
+    const SmallShape z = small_shape(lat, nrhs, ctx->small_grid);
     const long long rounds = (nrhs + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
     const double base = lat.eo ? (z.wg == 1 ? 8.5 : (z.wg == 2 ? 12.0 : 19.0))
                                : (z.wg == 1 ? 8.0 : (z.wg == 2 ? 10.0 : 13.0));
@@ -272,7 +269,7 @@ static size_t small_ring_bytes(const Lat &lat, int nc, const SmallShape &z) {
     return (size_t)z.ngroups * 2 * 16 * small_vec(lat, nc, z);
 }
 
-size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int nring) {
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int grid, int nring) {
     switch (slot) {
         case kSlotR:
         case kSlotQ:
@@ -281,7 +278,7 @@ size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int 
         case kSlotQ64:
         case kSlotXLo:
         case kSlotU8x: return 0;
-        case kSlotSmall: return nring * small_ring_bytes(lat, nc, small_shape(lat, W));
+        case kSlotSmall: return nring * small_ring_bytes(lat, nc, small_shape(lat, W, grid));
         default: return slot_size(slot, lat, nc, links, kF64, W);
     }
 }
@@ -325,7 +322,7 @@ template <typename Init>
 static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const Launch &L, const CgState &cs,
                              double *x64, const Init &init, int max_steps) {
     SmallArgs a{};
-    const SmallShape z = small_shape(op.lat, L.W);
+    const SmallShape z = small_shape(op.lat, L.W, ctx->small_grid);
     a.lat = op.lat;
     a.nc = op.nc;
     a.W = L.W;
@@ -573,13 +570,13 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     L.smode = -1;
     L.xnt = update_streams(iteration_bytes(op.lat, op.nc, W, op.links, prec_bytes(cfg.inner)));
     for (int slot : {kSlotB64, kSlotX64, kSlotR, kSlotP, kSlotQ, kSlotQ64, kSlotXLo, kSlotPart1, kSlotState}) {
-        const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W)
+        const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W, ctx->small_grid)
                                    : slot_size(slot, op.lat, op.nc, op.links, cfg.inner, W);
         if (b) DP_TRY(ctx->ensure(slot, b));
     }
     // (the scratch of a call that may not allocate holds as many ring slots as fit)
     if (cfg.small && !ctx->no_alloc)
-        DP_TRY(ctx->ensure(kSlotSmall, small_slot_size(kSlotSmall, op.lat, op.nc, op.links, W)));
+        DP_TRY(ctx->ensure(kSlotSmall, small_slot_size(kSlotSmall, op.lat, op.nc, op.links, W, ctx->small_grid)));
     const size_t nd = kStateDoubles;
     double *d = (double *)ctx->at(kSlotState);
     cs.rr = d;
