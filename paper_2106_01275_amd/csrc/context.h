@@ -134,7 +134,8 @@ struct SolveCfg {
     int ru_gap = 100;     // a reliable update at least every ru_gap iterations (mixed)
     int profile = 0;
     int W = 0, logW = 0;
-    int small = 0;        // each block is one persistent launch (inner is then kF64)
+    int small = 0;        // each block, of at most so many right-hand sides, is one persistent launch
+                          // (inner is then kF64); 0: launched kernels
     int refine = 0;       // small, for a mixed-precision request: the true residual decides
 };
 
@@ -175,15 +176,16 @@ size_t slot_size(int slot, const Lat &lat, int nc, bool links, int inner, int W)
 // the same for small solves; nring (>= 2) slots of the steps' vectors, between
 // whose uses the caches are dropped: few make that more frequent
 constexpr int kSmallRing = 8;
-size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int grid, int nring = kSmallRing);
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int lanes, int grid,
+                       int nring = kSmallRing);
 // Workgroups of a group (nwg), lanes of a group (wg) and groups side by side for
 // n lanes, at most `grid` workgroups (if one group fits).
 struct SmallShape {
     int nwg, wg, ngroups;
 };
 SmallShape small_shape(const Lat &lat, long long n, int grid);
-// Whether nrhs right-hand sides take the small solves (whatever the width).
-bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg);
+// Whether blocks of `lanes` right-hand sides take the small solves.
+bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, int lanes, const SolveCfg &cfg);
 inline int pow2_above(long long n) {
     int w = 1;
     while (w < n) w *= 2;
@@ -405,7 +407,7 @@ struct InitDeflated {
         const dp_status e = deflate_rhs(ctx, *d, *L, z);
         a.src = 2;
         a.b = z;
-        a.nvalid = L->W;
+        a.nvalid = g.nvalid;
         return e;
     }
     const ProbeGen *probe() const { return nullptr; }

@@ -2785,6 +2785,19 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs A) {
     };
     // blocks of WG lanes, the group's share of the W lanes in turn
     for (int l0 = group * WG; l0 < A.W; l0 += A.ngroups * WG) {
+        if (l0 >= A.nvalid) {  // lanes without a right-hand side: x = 0
+            for (int j = l0; j < min(l0 + WG, A.W); ++j) {
+                if (own) {
+                    A.x[2 * ((size_t)(s * NC + ca) * A.W + j) + im] = 0.0;
+                    if (EO) A.x[2 * ((size_t)((ns + s) * NC + ca) * A.W + j) + im] = 0.0;
+                }
+                if (wb != 0 || tid != 0) continue;
+                cs.rr[j] = cs.qp[j] = cs.rr_ref[j] = cs.bb[j] = cs.alpha[j] = cs.beta[j] = cs.true_rr[j] = 0.0;
+                cs.active[j] = cs.iters[j] = 0;
+                cs.flags[j] = kFlagConverged;
+            }
+            continue;
+        }
         // b at a site (of the internal order), colour a, lane l of this block
         auto b_at = [&](int site, int a, int l) {
             double re = 0.0, bi = 0.0;

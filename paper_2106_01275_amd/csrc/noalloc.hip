@@ -60,11 +60,11 @@ struct ScratchSlots {
 
 // Scratch bytes of a solve at width W (the slots that prepare_operator and
 // make_launch take; the colour slot of the autotuner is never used here).
-size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots], int grid = 0,
-              int nring = 0) {
+size_t layout(const Lat &lat, int nc, bool links, int inner, int W, size_t (&bytes)[kNumSlots], int lanes = 0,
+              int grid = 0, int nring = 0) {
     size_t tot = 0;
     for (int s = 0; s < kNumSlots; ++s) {
-        bytes[s] = nring ? small_slot_size(s, lat, nc, links, W, grid, nring) : slot_size(s, lat, nc, links, inner, W);
+        bytes[s] = nring ? small_slot_size(s, lat, nc, links, W, lanes, grid, nring) : slot_size(s, lat, nc, links, inner, W);
         tot += align256(bytes[s]);
     }
     return tot;
@@ -188,12 +188,14 @@ extern "C" dp_status dp_solve_noalloc(dp_ctx *ctx, const dp_operator *op, const 
     DP_TRY(with_small(ctx, stream, [&]() -> dp_status {
         SolveCfg cfg = cfg0;
         std::memcpy(bytes, plain_bytes, sizeof bytes);
-        if (small_problem(ctx, red, op->nc, nrhs, cfg)) {
+        const int lanes = (int)std::min<long long>(nrhs, W);
+        if (small_problem(ctx, red, op->nc, lanes, cfg)) {
             int nring = kSmallRing;
             const int grid = ctx->small_grid;
-            while (nring > 2 && layout(red, op->nc, links, kF64, W, bytes, grid, nring) > kScratchBytes) --nring;
-            if (layout(red, op->nc, links, kF64, W, bytes, grid, nring) <= kScratchBytes) {
-                cfg.small = 1;
+            auto need = [&] { return layout(red, op->nc, links, kF64, W, bytes, lanes, grid, nring); };
+            while (nring > 2 && need() > kScratchBytes) --nring;
+            if (need() <= kScratchBytes) {
+                cfg.small = lanes;
                 cfg.refine = cfg.inner != kF64;
                 cfg.inner = kF64;
             } else {

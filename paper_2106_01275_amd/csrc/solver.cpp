@@ -236,23 +236,26 @@ SmallShape small_shape(const Lat &lat, long long n, int grid) {
     return z;
 }
 
-bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, long long nrhs, const SolveCfg &cfg) {
+bool small_problem(dp_ctx *ctx, const Lat &lat, int nc, int lanes, const SolveCfg &cfg) {
     const long long ns = lat.eo ? lat.N / 2 : lat.N;
-    if (ctx->small_off || cfg.profile || nrhs < 1 || ns > (long long)ctx->small_grid * (kSmallThreads / 8) ||
+    if (ctx->small_off || cfg.profile || lanes < 1 || ns > (long long)ctx->small_grid * (kSmallThreads / 8) ||
         !small_enabled())
         return false;
-    // microseconds per CG step of all right-hand sides: a small solve's rounds
-    // one after another, against the launched kernels' latency and traffic.
+    // microseconds per CG step of a block: a small solve's rounds of lanes one
+    // after another, against the launched kernels' latency and traffic.
     // Measured (FP64, 8^4 x 3, per step): one right-hand side 7.6 us (launched
     // 23), 8 (one a group) 10 (29), 16 (two) 12 (30), 32 (four) 19 (33), 64
-    // (two rounds of four) 39 (37); odd extents 9 x 10 x 7 x 12: one 7.7 (19),
-    // 8 (four) 14 (23), 20 (three rounds) 30 (30)
-    const SmallShape z = small_shape(lat, nrhs, ctx->small_grid);
-    const long long rounds = (nrhs + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
+    // (two rounds of four) 39 (37).  Index order, a round of four lanes by the
+    // workgroups of a group: 10 (5^4) 10.7, 72 (8 x 8 x 8 x 9) 13.2, 119 (9 x 10
+    // x 7 x 12) 15.5; one round of 9 x 10 x 7 x 12, 8 right-hand sides, 16.5
+    // (launched 26), two rounds, 16 right-hand sides, 31 (29)
+    const SmallShape z = small_shape(lat, lanes, ctx->small_grid);
+    const long long rounds = (lanes + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
     const double base = lat.eo ? (z.wg == 1 ? 8.5 : (z.wg == 2 ? 12.0 : 19.0))
-                               : (z.wg == 1 ? 8.0 : (z.wg == 2 ? 10.0 : 13.0));
-    const double bytes = (double)ns * nrhs * nc * prec_bytes(cfg.inner) * (lat.eo ? 12.0 : 9.0);
-    if (!(rounds * (base + 0.015 * z.nwg) < 21.0 + bytes / 4.5e6)) return false;
+                               : (z.wg == 1 ? 8.0 : (z.wg == 2 ? 10.0 : 10.5));
+    const double each = !lat.eo && z.wg == 4 ? 0.04 : 0.015;  // per workgroup of a group
+    const double bytes = (double)ns * lanes * nc * prec_bytes(cfg.inner) * (lat.eo ? 12.0 : 9.0);
+    if (!(rounds * (base + each * z.nwg) < 21.0 + bytes / 5.8e6)) return false;
     if (ctx->small_skip > 0) {  // (asked once for each attempt at a call)
         --ctx->small_skip;
         return false;
@@ -269,7 +272,7 @@ static size_t small_ring_bytes(const Lat &lat, int nc, const SmallShape &z) {
     return (size_t)z.ngroups * 2 * 16 * small_vec(lat, nc, z);
 }
 
-size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int grid, int nring) {
+size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int lanes, int grid, int nring) {
     switch (slot) {
         case kSlotR:
         case kSlotQ:
@@ -278,7 +281,7 @@ size_t small_slot_size(int slot, const Lat &lat, int nc, bool links, int W, int 
         case kSlotQ64:
         case kSlotXLo:
         case kSlotU8x: return 0;
-        case kSlotSmall: return nring * small_ring_bytes(lat, nc, small_shape(lat, W, grid));
+        case kSlotSmall: return nring * small_ring_bytes(lat, nc, small_shape(lat, lanes, grid));
         default: return slot_size(slot, lat, nc, links, kF64, W);
     }
 }
@@ -295,8 +298,9 @@ dp_status plan_solve(dp_ctx *ctx, const dp_operator &opd, long long nrhs, int re
         lat.N = (int)N;
         lat.eo = eo_reducible(lat.D, opd.m2);
         const int w = requested != 0 ? requested : pow2_above(std::min<long long>(nrhs, kMaxW));
-        if (w > 0 && w <= kMaxW && (w & (w - 1)) == 0 && small_problem(ctx, lat, opd.nc, nrhs, cfg)) {
-            cfg.small = 1;
+        const int lanes = (int)std::min<long long>(nrhs, w);
+        if (w > 0 && w <= kMaxW && (w & (w - 1)) == 0 && small_problem(ctx, lat, opd.nc, lanes, cfg)) {
+            cfg.small = lanes;
             cfg.refine = cfg.inner != kF64;
             cfg.inner = kF64;
             W = w;
@@ -322,7 +326,7 @@ template <typename Init>
 static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const Launch &L, const CgState &cs,
                              double *x64, const Init &init, int max_steps) {
     SmallArgs a{};
-    const SmallShape z = small_shape(op.lat, L.W, ctx->small_grid);
+    const SmallShape z = small_shape(op.lat, cfg.small, ctx->small_grid);
     a.lat = op.lat;
     a.nc = op.nc;
     a.W = L.W;
@@ -342,7 +346,7 @@ static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg,
     a.nring = (int)std::min<size_t>(kSmallRing, ctx->slot_bytes[kSlotSmall] / small_ring_bytes(op.lat, op.nc, z));
     // the sums of this launch: two a step and a few for each closing residual,
     // for every round of lanes (numbers that start over only over cleared words)
-    const unsigned long long rounds = (L.W + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
+    const unsigned long long rounds = (cfg.small + z.wg * z.ngroups - 1) / (z.wg * z.ngroups);
     const unsigned long long sums = rounds * (6ull * (unsigned)max_steps + 8);
     if (ctx->small_tag + sums >= 0xffffffffull) {
         // in the stream's order: after the launches queued there, before this one
@@ -570,13 +574,14 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     L.smode = -1;
     L.xnt = update_streams(iteration_bytes(op.lat, op.nc, W, op.links, prec_bytes(cfg.inner)));
     for (int slot : {kSlotB64, kSlotX64, kSlotR, kSlotP, kSlotQ, kSlotQ64, kSlotXLo, kSlotPart1, kSlotState}) {
-        const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W, ctx->small_grid)
+        const size_t b = cfg.small ? small_slot_size(slot, op.lat, op.nc, op.links, W, cfg.small, ctx->small_grid)
                                    : slot_size(slot, op.lat, op.nc, op.links, cfg.inner, W);
         if (b) DP_TRY(ctx->ensure(slot, b));
     }
     // (the scratch of a call that may not allocate holds as many ring slots as fit)
     if (cfg.small && !ctx->no_alloc)
-        DP_TRY(ctx->ensure(kSlotSmall, small_slot_size(kSlotSmall, op.lat, op.nc, op.links, W, ctx->small_grid)));
+        DP_TRY(ctx->ensure(kSlotSmall, small_slot_size(kSlotSmall, op.lat, op.nc, op.links, W, cfg.small,
+                                                       ctx->small_grid)));
     const size_t nd = kStateDoubles;
     double *d = (double *)ctx->at(kSlotState);
     cs.rr = d;
