@@ -622,13 +622,13 @@ static dp_status read_ctrl(dp_ctx *ctx, const Red &rd, const CgState &cs, int W,
 }
 
 int next_check(int dflt, double ratio, double ratio_prev, int dit, double ru_ratio) {
-    int next = dflt;
+    double next = dflt;
     if (ratio_prev > 0 && ratio > 1.0 && ratio < ratio_prev && dit > 0) {
         const double per_it = std::log(ratio_prev / ratio) / dit;
-        next = (int)std::ceil(std::log(ratio) / per_it);
-        if (ru_ratio > 1.0) next = std::min(next, (int)std::ceil(std::log(ru_ratio) / per_it));
+        next = std::ceil(std::log(ratio) / per_it);
+        if (ru_ratio > 1.0) next = std::min(next, std::ceil(std::log(ru_ratio) / per_it));
     }
-    return std::min(16, std::max(2, next));
+    return (int)std::min(16.0, std::max(2.0, next));  // (next may exceed every int)
 }
 
 // Steps until the next check, from the pace: what the slowest lane needs to
@@ -650,7 +650,8 @@ int plan_steps(double pace, double ratio, double ratio_ref, double ru_ratio, int
         const double n = std::max(1.0, std::ceil(whole / cycle - 0.05));
         left = std::min(left, whole / n - std::log(std::max(ratio_ref / ratio, 1.0)));
     }
-    return std::min(32, std::max(1, (int)std::ceil(left / pace - 1e-6)));
+    // (a pace near nothing: left / pace may exceed every int)
+    return (int)std::min(32.0, std::max(1.0, std::ceil(left / pace - 1e-6)));
 }
 
 // Update mode of iteration c of a group of n: pairs (1, 2) of a deferred

@@ -50,3 +50,28 @@ int main() {
 }""" % (cus, cus))
     taken, bad = (int(v) for v in out.split())
     assert taken > 20 and bad == 0
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_steps_to_the_next_check_are_bounded(tmp_path, prec):
+    """A lane that hardly decays asks for the most steps, not for one: whatever
+    the pace (down to the smallest number) the answer lies in 1 .. 32, and never
+    grows with it."""
+    out = run(tmp_path, """
+int main() {
+    long bad = 0;
+    for (double ratio : {1e24, 1e12, 1e3, 1.5, 1.0, 0.0}) {
+        int last = 32;
+        for (double pace = 5e-324; pace < 100; pace = pace < 1e-300 ? pace * 1e8 + 1e-308 : pace * 1.7) {
+            const int n = plan_steps(pace, ratio, std::max(ratio, 1.0), 10.0, %d);
+            bad += n < 1 || n > last;
+            bad += ratio >= 1e3 && pace < 1e-6 && n != 32;
+            last = n;
+        }
+    }
+    // (the multi-instance engine's: 2 .. 16)
+    for (double near = 1e-16; near < 0.5; near *= 3) bad += next_check(8, 1e20 * (1 - near), 1e20, 4, 0.0) != 16;
+    bad += next_check(8, 10.0, 1e9, 4, 0.0) != 2;
+    std::printf("%%ld", bad);
+}""" % prec)
+    assert int(out) == 0
