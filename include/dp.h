@@ -198,11 +198,14 @@ typedef struct {
                                vectors (N * nc * W elements of the inner precision)
                                stay under 4 GiB (DP_EINVAL otherwise) */
     double reliable_delta;  /* mixed precision: replace the residual by the FP64
-                               true residual once it dropped by this factor; a lane
-                               that reaches it waits for that update before it moves
-                               on (0: 1e-3 for F32; for BF16 0.002, and 0.01 on the
-                               even-odd reduced system).  BF16 storage resolves about 3 digits: smaller values cost extra
-                               iterations, larger ones extra FP64 updates */
+                               true residual once it dropped by this factor; with
+                               BF16 storage a lane that reaches it waits for that
+                               update before it moves on.  0: for BF16 0.002, and
+                               0.01 on the even-odd reduced system; for F32 from
+                               the measured decay, up to six digits where it is
+                               fast, else 1e-3 (several instances: 1e-3).  BF16
+                               storage resolves about 3 digits: smaller values cost
+                               extra iterations, larger ones extra FP64 updates */
     int32_t use_graph;      /* 1: replay the iteration loop from a captured hipGraph */
     int32_t profile;        /* 1: time stencil kernel launches with HIP events (single
                                instance: every 8th when a launch moves less than 256 MB of

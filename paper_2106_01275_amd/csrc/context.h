@@ -55,6 +55,17 @@ struct BlockStats {
 
 }  // namespace dp
 
+namespace dp {
+// Decay of ln |r|^2 per CG step of a block's slowest lane, measured between host
+// checks; 0: none yet.
+struct Pace {
+    double last = 0;  // between the last two checks
+    double mean = 0;  // since the start of the block
+    // a well conditioned operator (plan_steps); mult: iterations a step counts as
+    bool fast(int mult) const { return mean * 2 >= 1.7 * mult; }
+};
+}  // namespace dp
+
 struct dp_ctx {
     int device = 0;
     std::string err;
@@ -80,9 +91,7 @@ struct dp_ctx {
     std::array<int, 2> stencil_forced{{-1, 0}};
     bool tune_loaded = false;
     int check_every = 8;
-    // decay of ln |r|^2 per CG step of the prepared operator (single instance),
-    // measured between host checks; 0: none yet
-    double pace = 0;
+    dp::Pace pace;  // of the prepared operator (single instance)
     hipStream_t gstream = nullptr;            // library stream for graph capture
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     std::map<std::string, hipGraphExec_t> graphs;  // iteration groups by length and kernel arguments
@@ -292,8 +301,9 @@ double stencil_alg_bytes(const Launch &L, int prec, bool links, int kind);
 // needs to be due a reliable update, both from the slowest lane's decay of
 // |r|^2 over the last dit iterations (ratio_prev -> ratio); dflt without one.
 int next_check(int dflt, double ratio, double ratio_prev, int dit, double ru_ratio);
-// The same for a single instance whose pace is known: 1..32 steps.
-int plan_steps(double pace, double ratio, double ratio_ref, double ru_ratio, int inner);
+// The same for a single instance whose pace is known, mult iterations a step:
+// 1..32 steps.
+int plan_steps(const Pace &pc, double ratio, double ratio_ref, double ru_ratio, int inner, int mult);
 
 // Work stream of a call: the caller's stream, or (graph replay requested)
 // the library's own stream, ordered after the caller's stream on entry and

@@ -407,7 +407,7 @@ dp_status prepare_operator(dp_ctx *ctx, const dp_operator &op, int inner, OpPrep
     out.m2 = op.m2;
     out.links = op.links != nullptr;
     out.inner = inner;
-    ctx->pace = 0;
+    ctx->pace = Pace();
     auto sz = [&](int slot) { return slot_size(slot, out.lat, op.nc, out.links, inner, 1); };
     DP_TRY(ctx->ensure(kSlotNbr, sz(kSlotNbr)));
     out.nbr = (const int *)ctx->at(kSlotNbr);
@@ -632,26 +632,40 @@ int next_check(int dflt, double ratio, double ratio_prev, int dit, double ru_rat
 }
 
 // Steps until the next check, from the pace: what the slowest lane needs to
-// reach tol (ratio = |r|^2 / (tol^2 |b|^2) of it), with BF16 storage at most
-// what the first lane needs to be due its reliable update, and with FP32
-// storage at most what the present cycle should gain.  FP32 follows the true
-// residual over about six digits (then the recursive residual runs on alone,
-// and its steps are lost), and a reliable update costs about two steps: the
-// way to tol since the last update (ratio_ref) is taken in the fewest equal
-// cycles of at most six digits.  (16^4, 1e-11: 27 steps and three updates a
-// block became 23 and two.)  The last step of a mixed-precision cycle aims a
-// little below tol: a lane that misses it costs another update.
-int plan_steps(double pace, double ratio, double ratio_ref, double ru_ratio, int inner) {
+// reach tol (ratio = |r|^2 / (tol^2 |b|^2) of it), and at most what the first
+// lane needs to be due its reliable update where the caller or the storage sets
+// the drop between them (BF16; FP32 with a reliable_delta: ru_ratio > 1).
+// Otherwise FP32 storage follows the true residual over about six digits of a
+// well conditioned operator (then the recursive residual runs on alone, and its
+// steps are lost), and a reliable update costs about two steps: the way to tol
+// since the last update (ratio_ref) is taken in the fewest equal cycles of at
+// most six digits.  (16^4, 1e-11: 27 steps and three updates a block became 23
+// and two.)  The last step of a mixed-precision cycle aims a little below tol: a
+// lane that misses it costs another update.
+// A light or smooth operator decays slowly and unevenly, FP32 follows its true
+// residual over four digits or three, and steps predicted from the first few run
+// far past: there a check comes after at most 8 steps (16 iterations) and FP32
+// takes its update at the first one past the default drop.  (BF16 storage has
+// its checks set by its drop already, and its updates restart the directions:
+// more of them cost.)  The line lies at a
+// decay of 1.7 in ln |r|^2 per step, a condition number of about 5.5 (emulated
+// FP32, steps and updates to 1e-11: 16^4 free field, m2 = 0.05 (1.0 a step), 50
+// and 3, in cycles 75 and 2; m2 = 0.001 81 and 3, 158 and 4; 8^4 x 3, eps = 0.1
+// (1.1) 45 and 3, 43 and 3; eps = 0.2 (1.6) 31 and 3, 31 and 2; eps = 0.4 (2.1)
+// 24 and 3, 21 and 2).
+int plan_steps(const Pace &pc, double ratio, double ratio_ref, double ru_ratio, int inner, int mult) {
     const double margin = inner == kF64 ? 0.0 : 2.0 * std::log(1.25), cycle = 2.0 * std::log(1e6);
+    const bool fast = pc.fast(mult);
     double left = std::log(std::max(ratio, 1.0)) + margin;
-    if (inner == kBF16 && ru_ratio > 1.0) left = std::min(left, std::log(ru_ratio));
-    if (inner == kF32) {
+    if (inner != kF64 && ru_ratio > 1.0) {
+        left = std::min(left, std::log(ru_ratio));
+    } else if (inner == kF32 && fast) {
         const double whole = std::log(std::max(ratio_ref, 1.0)) + margin;
         const double n = std::max(1.0, std::ceil(whole / cycle - 0.05));
         left = std::min(left, whole / n - std::log(std::max(ratio_ref / ratio, 1.0)));
     }
     // (a pace near nothing: left / pace may exceed every int)
-    return (int)std::min(32.0, std::max(1.0, std::ceil(left / pace - 1e-6)));
+    return (int)std::min(fast || inner == kBF16 ? 32.0 : 16.0 / mult, std::max(1.0, std::ceil(left / pc.last - 1e-6)));
 }
 
 // Update mode of iteration c of a group of n: pairs (1, 2) of a deferred
@@ -941,9 +955,19 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     const int check_every = std::max(1, ctx->check_every / mult);
     // Iterations between host checks: start with check_every, then predict
     // from the decay of the slowest lane's residual since the last check.
-    const double delta2 = cs.delta2, start = 1.0 / (cfg.tol * cfg.tol);
+    // The drop between reliable updates sets the checks where the caller gave it,
+    // and for BF16 storage.
+    const bool by_drop = cfg.inner == kBF16 || (mixed && cfg.delta > 0);
+    const double start = 1.0 / (cfg.tol * cfg.tol), whole_drop = by_drop ? 1.0 / cs.delta2 : 0.0;
     double ratio_ref = start;
-    int steps_next = ctx->pace > 0 ? plan_steps(ctx->pace, start, start, 1.0 / delta2, cfg.inner) : check_every;
+    Pace &pace = ctx->pace;
+    auto plan = [&](double ratio, double ru_ratio) {
+        return pace.last > 0 ? plan_steps(pace, ratio, ratio_ref, ru_ratio, cfg.inner, mult) : check_every;
+    };
+    // (a light operator's decay is uneven: its blocks, and what follows an update,
+    // start with the default)
+    auto uneven = [&] { return cfg.inner != kBF16 && !pace.fast(mult); };
+    int steps_next = uneven() ? check_every : plan(start, whole_drop);
     // the x updates of an iteration group are taken in pairs (the update
     // kernel's deferred mode)
     const bool xdefer = xdefer_enabled();
@@ -988,8 +1012,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             std::memcpy(&ratio, ctx->ctrl_host + 4, sizeof(double));
             std::memcpy(&ru_ratio, ctx->ctrl_host + 6, sizeof(double));
             const double from = ratio_prev > 0 ? ratio_prev : ratio_ref;
-            if (ratio > 0 && ratio < from) ctx->pace = std::log(from / ratio) / (it - it_prev);
-            steps_next = ctx->pace > 0 ? plan_steps(ctx->pace, ratio, ratio_ref, ru_ratio, cfg.inner) : check_every;
+            if (ratio > 0 && ratio < from) pace.last = std::log(from / ratio) / (it - it_prev);
+            if (ratio > 0) pace.mean = std::log(start / ratio) / it;
+            steps_next = plan(ratio, by_drop ? ru_ratio : 0.0);
             ratio_prev = ratio;
             it_prev = it;
         }
@@ -1007,7 +1032,10 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
             nactive = ctx->ctrl_host[0];
             std::memcpy(&ratio_ref, ctx->ctrl_host + 4, sizeof(double));
             ratio_prev = ratio_ref;
-            if (ctx->pace > 0) steps_next = plan_steps(ctx->pace, ratio_ref, ratio_ref, 1.0 / delta2, cfg.inner);
+            // (on from the true residual, which may lie above the recursive one)
+            if (ratio_ref > 0) pace.mean = std::log(start / ratio_ref) / it;
+            steps_next = plan(ratio_ref, whole_drop);
+            if (uneven()) steps_next = std::min(steps_next, check_every);
         }
     }
     // Mixed precision: lanes stop only at a reliable update, which folded

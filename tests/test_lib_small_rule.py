@@ -59,14 +59,25 @@ def test_steps_to_the_next_check_are_bounded(tmp_path, prec):
     grows with it."""
     out = run(tmp_path, """
 int main() {
+    const int prec = %d;
     long bad = 0;
     for (double ratio : {1e24, 1e12, 1e3, 1.5, 1.0, 0.0}) {
         int last = 32;
         for (double pace = 5e-324; pace < 100; pace = pace < 1e-300 ? pace * 1e8 + 1e-308 : pace * 1.7) {
-            const int n = plan_steps(pace, ratio, std::max(ratio, 1.0), 10.0, %d);
-            bad += n < 1 || n > last;
-            bad += ratio >= 1e3 && pace < 1e-6 && n != 32;
-            last = n;
+            for (int mult : {1, 2})
+                for (double mean : {0.1, 4.0}) {
+                    Pace pc;
+                    pc.last = pace;
+                    pc.mean = mean;
+                    const int n = plan_steps(pc, ratio, std::max(ratio, 1.0), 0.0, prec, mult);
+                    const int most = mean > 1.7 || prec == kBF16 ? 32 : 16 / mult;
+                    bad += n < 1 || n > most;
+                    bad += ratio >= 1e3 && pace < 1e-6 && n != most;
+                    if (mult == 1 && mean > 1.7) {
+                        bad += n > last;
+                        last = n;
+                    }
+                }
         }
     }
     // (the multi-instance engine's: 2 .. 16)
