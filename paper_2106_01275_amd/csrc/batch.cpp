@@ -198,7 +198,7 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
         cs.beta = st + 5 * kMaxW;
         cs.true_rr = st + 6 * kMaxW;
         cs.tj = st + 7 * kMaxW;
-        cs.xdef = st + 9 * kMaxW;
+        cs.xdef = mixed ? st + 9 * kMaxW : nullptr;
         int *iv = (int *)(st + st_doubles);
         cs.active = iv;
         cs.iters = iv + kMaxW;
@@ -431,8 +431,9 @@ static dp_status run_engine(dp_ctx *ctx, std::vector<BatchInst> &in, const Solve
     DP_TRY(init_slots());
 
     int steps_next = check_every;
-    // the x updates of an iteration group in pairs (as in the single-instance solve)
-    const bool xdefer = xdefer_enabled();
+    // mixed precision: the x updates of an iteration group in pairs (as in
+    // the single-instance solve)
+    const bool xdefer = mixed && xdefer_enabled();
     std::vector<double> ratio_prev(nslots, -1.0);
     std::vector<int> it_prev(nslots, 0);
     ctx->drop_graphs();

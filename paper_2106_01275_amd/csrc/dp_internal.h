@@ -47,7 +47,7 @@ struct Red {
 // Per-right-hand-side CG state of one block of W right-hand sides (device).
 struct CgState {
     double *rr, *qp, *rr_ref, *bb, *alpha, *beta, *true_rr;  // qp: Re q^H p total of part2
-    double *xdef;        // alpha / beta of an x update deferred by one iteration
+    double *xdef;        // alpha / beta of an x update deferred by one iteration (null: none)
     double *tj;          // [W][2] contraction results / dot products
     int *active, *iters, *flags;
     int *ctrl;           // [0] active, [1] candidates, [2] need reliable update, [3] breakdowns
@@ -181,7 +181,7 @@ struct BatchLaunch {
     hipStream_t stream;
 };
 void launch_b_init(const BatchLaunch &B);
-// xmode: as launch_update's
+// xmode: as launch_update's (the slots of mixed precision have cs.xdef)
 void launch_b_iteration(const BatchLaunch &B, int xmode = 0);
 // even-odd order: the odd half of p, H p_e / c, before the stencil
 void launch_b_hop(const BatchLaunch &B, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -260,9 +260,10 @@ void launch_stencil(const Launch &L, int prec, const StencilArgs &a);
 bool stencil_mode_valid(const Launch &L, int prec, int mode);
 int stencil_mode_rule(const Launch &L, int prec);
 // The vector update of a CG iteration: x += alpha p, r -= alpha q,
-// p = r + beta p, and |r|^2 per lane into rd.part2.  xmode 1 defers this
-// iteration's x update to the next update, which must be launched with xmode 2;
-// 0 the plain update.
+// p = r + beta p, and |r|^2 per lane into rd.part2.  xmode (FP32 or BF16
+// storage with cs.xdef set, else taken as 0): 1 defers this iteration's x
+// update to the next update, which must be launched with xmode 2; 0 the
+// plain update.
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
                    const CgState &cs, int xmode = 0);
 // x64 += xlo, xlo = 0 (mixed precision); first: x64 = xlo (no fold yet in this block)

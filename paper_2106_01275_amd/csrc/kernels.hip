@@ -1768,7 +1768,7 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R 
 // finishing kernel adds the partials up).  A held or stopped lane keeps its
 // direction (alpha = 0: x and r are unchanged too).
 // The solution's update x += alpha p can be taken two iterations at a time
-// (XM): an update with XM = 1 leaves x and records
+// (XM; FP32 or BF16 storage): an update with XM = 1 leaves x and records
 // c = alpha_k / beta_k per lane; the next one (XM = 2) recovers the direction
 // p_k it skipped from the two vectors it reads anyway, p_k = (p_{k+1} -
 // r_{k+1}) / beta_k (the relation by which the skipped update formed p_{k+1}),
@@ -1782,8 +1782,11 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Launch L, typename St<S>::R 
 // sqrt(beta_k)) of the step, against 2^-9 of the whole accumulated x that
 // every BF16 write of x costs (and the pairs halve those writes); there the
 // floor is 1/16 (at most 5 x 2^-9 of a step).  XM = 0 is the plain update.
-// FP64 takes the pairs too, its recovery rounding by at most 8 units of 2^-53:
-// 8^4 x 3, W = 256, 2.40 -> 2.31 ms a trace.
+// FP64 storage, whose result is x as it stands, takes the plain update alone:
+// in pairs a step is rounded by up to 8 units of 2^-53 where it was by one
+// (8^4 x 3 trace, W = 256, 2.31 ms for 2.40, but errors at 1e-15 of 1.05 times
+// the plain ones' rms on the average of seven lattices and of 1.3 times on a
+// 6^4 free field).
 // An XM = 1 update is always followed by an XM = 2 one before anything
 // reads x.
 template <typename S>
@@ -3471,16 +3474,20 @@ void launch_stencil(const Launch &L, int prec, const StencilArgs &a) {
 template <typename S, int XNT>
 static void update_t(const Launch &L, void *x, void *r, void *p, const void *q, const Red &rd, const CgState &cs,
                      int xmode) {
-    if (xmode == 1)
-        k_update<S, 1, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
-    else if (xmode == 2)
-        k_update<S, 2, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
-    else
-        k_update<S, 0, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
+    if constexpr (!std::is_same<S, double2>::value) {
+        if (xmode == 1)
+            return k_update<S, 1, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd,
+                                                                        cs);
+        if (xmode == 2)
+            return k_update<S, 2, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd,
+                                                                        cs);
+    }
+    k_update<S, 0, XNT><<<L.nblk, kBlock, 0, L.stream>>>(L, (S *)x, (S *)r, (S *)p, (const S *)q, rd, cs);
 }
 
 void launch_update(const Launch &L, int prec, void *x, void *r, void *p, const void *q, const Red &rd,
                    const CgState &cs, int xmode) {
+    if (!cs.xdef) xmode = 0;  // (deferral: FP32 and BF16 storage)
     DP_DISPATCH_PREC(prec, S,
                      L.xnt == 0   ? update_t<S, 0>(L, x, r, p, q, rd, cs, xmode)
                      : L.xnt == 1 ? update_t<S, 1>(L, x, r, p, q, rd, cs, xmode)
@@ -3782,12 +3789,11 @@ void launch_b_stencil(const BatchLaunch &B, hipEvent_t ev0, hipEvent_t ev1) { b_
 
 template <typename S, int XNT>
 static void b_update_t(const BatchLaunch &B, int xmode) {
-    if (xmode == 1)
-        k_b_update<S, 1, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
-    else if (xmode == 2)
-        k_b_update<S, 2, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
-    else
-        k_b_update<S, 0, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+    if constexpr (!std::is_same<S, double2>::value) {
+        if (xmode == 1) return k_b_update<S, 1, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+        if (xmode == 2) return k_b_update<S, 2, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
+    }
+    k_b_update<S, 0, XNT><<<B.nblocks, kBlock, 0, B.stream>>>(B);
 }
 
 void launch_b_update(const BatchLaunch &B, int xmode) {

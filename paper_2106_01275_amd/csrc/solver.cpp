@@ -481,7 +481,7 @@ static dp_status time_iterations(dp_ctx *ctx, const OpPrep &op, int inner, const
     a.rd = rd;
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
-    const bool xdefer = xdefer_enabled();
+    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
     auto iter = [&](int xm) { launch_cg_step(Lc, inner, a, xlo, xm); };
     iter(0);
     DP_HIP(hipEventRecord(e0, Lc.stream));
@@ -592,7 +592,7 @@ dp_status make_launch(dp_ctx *ctx, const OpPrep &op, int W, hipStream_t s, Launc
     cs.beta = d + 5 * kMaxW;
     cs.true_rr = d + 6 * kMaxW;
     cs.tj = d + 7 * kMaxW;
-    cs.xdef = d + 9 * kMaxW;
+    cs.xdef = cfg.inner != kF64 ? d + 9 * kMaxW : nullptr;
     // the control word lives in pinned host memory: k_ctrl writes it there
     // and the host reads it after the synchronisation, no copy
     cs.ctrld = (double *)(ctx->ctrl_dev + 4);
@@ -968,9 +968,9 @@ dp_status solve_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, const 
     // start with the default)
     auto uneven = [&] { return cfg.inner != kBF16 && !pace.fast(mult); };
     int steps_next = uneven() ? check_every : plan(start, whole_drop);
-    // the x updates of an iteration group are taken in pairs (the update
-    // kernel's deferred mode)
-    const bool xdefer = xdefer_enabled();
+    // mixed precision takes the x updates of an iteration group in pairs
+    // (the update kernel's deferred mode)
+    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
     double ratio_prev = -1.0;
     int it_prev = 0, it_ru = 0;
     while (nactive > 0 && it < max_steps) {
@@ -1155,7 +1155,7 @@ static dp_status time_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, 
     a.rd = rd;
     a.cs = cs;
     // the solve's paired x updates (xmode 1 then 2) where it takes them
-    const bool xdefer = xdefer_enabled();
+    const bool xdefer = cs.xdef != nullptr && xdefer_enabled();
     auto iter = [&](int xm) { launch_cg_step(L, cfg.inner, a, xlo, xm); };
     iter(xmode_of(0, 2, xdefer));
     iter(xmode_of(1, 2, xdefer));
