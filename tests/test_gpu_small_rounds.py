@@ -90,3 +90,24 @@ def test_probes_and_gradients(ctx, monkeypatch, dims, ns, block):
     assert not np.array_equal(got["0"][0], got["1"][0])
     for a, b in zip(got["1"], got["0"]):
         assert np.abs(a - b).max() < 1e-10 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("dims,n,block", [((18, 12, 12, 12), 4, 4), ((16, 16, 16, 8), 2, 2), ((18, 12, 12, 12), 11, 4)])
+def test_short_ring(ctx, monkeypatch, dims, n, block):
+    """Without allocations the ring of the steps' vectors has as many slots as the
+    fixed workspace leaves (four and seven here; four is the fewest that a solve that fits
+    can get), so that it wraps more often: bit for bit the solve with eight."""
+    _say("short ring", dims, n, block)
+    _settle(ctx, monkeypatch)
+    rng = np.random.default_rng(2)
+    N = int(np.prod(dims))
+    B = cuda(rng.standard_normal((n, N, 3)) + 1j * rng.standard_normal((n, N, 3)))
+    op = ctx.operator(dims, 3, 0.1, cuda(workloads.random_links(dims, 0.4, 6)))
+    o = ctx.opts(tol=1e-11, rhs_block=block)
+    (X,), (st,) = ctx.solve_batch([op], [B], o)
+    for _ in range(3):
+        Y, sy = ctx.solve_noalloc(op, B, o)
+        assert torch.equal(X, Y) and sy["rhs_iters"] == st["rhs_iters"] and sy["nconverged"] == n
+    monkeypatch.setenv("DP_SMALL", "0")
+    Z, _ = ctx.solve_noalloc(op, B, o)
+    assert not torch.equal(X, Z) and (X - Z).abs().max() < 1e-9 * Z.abs().max()

@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def run(tmp_path, body):
     """Output of a program of the library's internals."""
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text('#include <cmath>\n#include <cstdio>\n#include <cstring>\n#include "context.h"\nusing namespace dp;\n' + body)
+    src.write_text('#include <array>\n#include <cmath>\n#include <cstdio>\n#include <cstring>\n#include "context.h"\nusing namespace dp;\n' + body)
     lib = os.path.dirname(dp.LIB_PATH)
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(lib, "csrc"), "-I", "/opt/rocm/include", str(src), "-o", str(exe), dp.LIB_PATH,
