@@ -3844,8 +3844,9 @@ static void b_odd_x(const BatchLaunch &B, int phase) {
 
 // Reliable update (final_stats = 0: slots flagged kSlotRU; mixed precision:
 // fold, then the true residual replaces r and continues p) or the final
-// statistics (final_stats = 1: slots flagged kSlotFinal; FP64, whose iterate
-// is already the solution: the true residual's norm only).
+// statistics (final_stats = 1: slots flagged kSlotFinal; the true residual's norm
+// only: FP64, whose iterate is already the solution, and mixed slots that no
+// update has folded yet, having had no active lane).
 void launch_b_ru(const BatchLaunch &B, int final_stats) {
     const int phase = final_stats ? kSlotFinal : kSlotRU;
     const int ru = final_stats ? 0 : 1;

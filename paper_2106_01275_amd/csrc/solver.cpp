@@ -1202,8 +1202,11 @@ dp_status choose_width(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg, long 
         // p, q read, x, r, p written), times the padding of every instance's last
         // block (its lanes and blocks over the useful lane-sites sum n_i N_i).  Timing one instance
         // alone instead rewards wide blocks that fill the GPU by themselves
-        // (64 uneven lattices: this ranks W = 16/32/64/128 as the measured
-        // 133/123/141/159 ms per step; the timed single instance picked 128).
+        // (64 uneven lattices, BF16: 132 bytes at W = 32, 141 to 143 at 16, 64 and
+        // 128; measured 62.9 / 56.0 / 63.5 / 66.4 ms at W = 16 / 32 / 64 / 128; the
+        // timed single instance picked 128).  The passes are those of the whole
+        // operator; with the even-odd halves' 12 half-lattice ones W = 32 is first
+        // as well (83 against 86 to 92).
         // Widths below 16 (per-lane link loads) only when no instance has
         // more right-hand sides.
         const double c = (double)prec_bytes(cfg.inner);
