@@ -210,8 +210,8 @@ dp_status small_check(dp_ctx *ctx);
 // Runs f, whose work is on s; when a small solve of it gave up, once more
 // without them.  Other work that holds the CUs may last: after a failure the
 // next call that could take small solves does not try, after another failure
-// the next two, four, .. kSmallBackoff (a failure costs a wait of about 0.2 s;
-// a solve that succeeds ends the count).
+// the next two, four, .. kSmallBackoff (a failure costs a wait; a solve that
+// succeeds ends the count).
 constexpr int kSmallBackoff = 256;
 template <typename F>
 dp_status with_small(dp_ctx *ctx, hipStream_t s, F f) {

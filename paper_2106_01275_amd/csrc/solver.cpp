@@ -357,9 +357,15 @@ static dp_status small_block(dp_ctx *ctx, const OpPrep &op, const SolveCfg &cfg,
     ctx->small_tag = (unsigned)std::min<unsigned long long>(a.tag + sums, 0xffffffffull);
     a.max_steps = max_steps;
     a.refine = cfg.refine;
-    // a wait gives up after some 0.2 s (DP_SMALL_POLLS=n or n:k, tests: after n
-    // polls, from the k-th launch of a call on)
-    a.polls = 400000;
+    // A wait gives up after about 1.5 ms (DP_SMALL_POLLS=n or n:k, tests: after n
+    // polls, from the k-th launch of a call on).  Calls from several threads, each
+    // with its own context, can leave two launches half resident each, which only
+    // giving up ends: it has to cost little more than the launched kernels do.
+    // Eight right-hand sides of 8^4 x 3, FP64, per call: four threads 0.9 ms at
+    // 1000 and at 4000 polls, 1.1 at 16000, 10 at 400000 (launched 1.5); eight
+    // threads 2.0, 2.1, 2.7 and 44 (1.9).  A wait of a launch that is resident is
+    // a few microseconds, of its first sum some tens.
+    a.polls = 2000;
     if (const char *e = std::getenv("DP_SMALL_POLLS")) {
         int n = 0, k = 0;
         if (std::sscanf(e, "%d:%d", &n, &k) >= 1 && ctx->small_launches >= k) a.polls = n;

@@ -126,3 +126,50 @@ def test_failures_are_remembered(ctx, problem, monkeypatch):
             for _ in range(skipped):
                 assert took() == "launched"
         assert took() == took() == "small"
+
+
+@pytest.mark.parametrize("dims,n", [((8, 8, 8, 8), 8), ((9, 8, 7, 8), 7)])
+def test_several_threads(ctx, monkeypatch, dims, n):
+    """Four host threads, each with its own context and stream, solve at once.
+    Persistent launches of two contexts can keep each other from becoming
+    resident; the waits then run out and the launched kernels take the call.  The
+    right solutions (1e-10 at 1e-12), and on the average of all calls at most 20
+    ms: a wait that runs out is below 2 ms, the launched solves of four threads
+    sharing the GPU below 2 ms each, and a call has at most one of each."""
+    import threading
+    import time
+
+    _say("threads", dims, n)
+    monkeypatch.setenv("DP_SMALL", "1")
+    N = int(np.prod(dims))
+    rng = np.random.default_rng(2)
+    U = workloads.random_links(dims, 0.4, 3)
+    B = rng.standard_normal((n, N, 3)) + 1j * rng.standard_normal((n, N, 3))
+    Xo, _, _ = oracle.cg_many(dims, 3, 0.2, U, B, tol=1e-14)
+    Ug, b = cuda(U), cuda(B)
+    torch.cuda.synchronize()
+    threads, calls = 4, 40
+    start, errs, secs = threading.Barrier(threads), [], []
+
+    def work():
+        c = dp.Context(0)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            op, o, x = c.operator(dims, 3, 0.2, Ug), c.opts(tol=1e-12), torch.empty_like(b)
+            c.solve_batch([op], [b], o, xs=[x])
+            start.wait()
+            t = time.perf_counter()
+            for _ in range(calls):
+                x.zero_()
+                _, (st,) = c.solve_batch([op], [b], o, xs=[x])
+                errs.append(np.abs(x.cpu().numpy() - Xo).max() if st["nconverged"] == n else np.inf)
+            secs.append(time.perf_counter() - t)
+        c.close()
+
+    pool = [threading.Thread(target=work) for _ in range(threads)]
+    for p in pool:
+        p.start()
+    for p in pool:
+        p.join()
+    assert len(errs) == threads * calls and max(errs) < 1e-10 * np.abs(Xo).max()
+    _say("   ms a call", 1e3 * sum(secs) / (threads * calls))
+    assert sum(secs) / (threads * calls) < 20e-3
