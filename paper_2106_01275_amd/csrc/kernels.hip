@@ -650,6 +650,13 @@ __device__ __forceinline__ void k_finish_cg_wave_body(int lane, const Red &rd, c
     if ((threadIdx.x & 63) == 0) finish_cg_epilogue(lane, cs, ls, d3, d2);
 }
 
+// An FP32 lane whose |r|^2 has grown this far above its last true residual's (CG's
+// own residual may rise by the root of the condition number in norm), or is not
+// finite, has lost its directions: where a Krylov space is exhausted (a small
+// lattice, a few plane waves) the recursion falls far below what FP32 resolves
+// and what follows is noise that grows.  It restarts at the next reliable update.
+constexpr double kDiverged = 1e6;
+
 // alpha, beta, flags and counts of lane j from its totals (thread-local)
 __device__ __forceinline__ void finish_cg_epilogue(int j, const CgState &cs, const LaneState &ls, const double (&d3)[4],
                                                    const double (&d2)[2]) {
@@ -678,6 +685,8 @@ __device__ __forceinline__ void finish_cg_epilogue(int j, const CgState &cs, con
             flags |= kFlagConverged;
         } else if (cs.hold && !(rr >= cs.delta2 * st_ref)) {
             flags |= kFlagHold;  // due a reliable update (or not finite)
+        } else if (!cs.exact && !cs.hold && !(rr <= kDiverged * st_ref)) {
+            flags |= kFlagRestart;
         }
     }
     if (!active) beta = 0.0;

@@ -83,3 +83,35 @@ def test_fp32_drop_is_the_callers(ctx, monkeypatch, dims):
         assert st["nconverged"] == 8
         digits = -math.log10(delta)
         assert math.ceil(11 / (digits + 2)) <= st["reliable_updates"] <= math.ceil(11 / digits) + 1, delta
+
+
+@pytest.mark.parametrize("dims,eps", [((16, 8, 8, 8), 0), ((4, 4, 4, 4), 0), ((5, 4, 3, 4), 0), ((4, 3, 2, 4), 0.3)])
+def test_exhausted_krylov_space(ctx, monkeypatch, dims, eps):
+    """FP32 where a handful of steps solves a system exactly (a few plane waves of
+    the free field, lattices of few sites): the recursive residual falls below
+    what FP32 resolves, and a lane whose residual then grows starts again from the
+    true one.  Every right-hand side converges, well before the limit (the true
+    residual is the library's own, in FP64)."""
+    _say("exhausted", dims)
+    monkeypatch.setenv("DP_SMALL", "0")
+    N, n = int(np.prod(dims)), 6
+    ix = np.indices(dims)
+    for seed in range(12):
+        U = workloads.random_links(dims, eps, seed, 1) if eps else None
+        for m2 in (0.02, 0.3):
+            op = ctx.operator(dims, 1, m2, None if U is None else cuda(U))
+            rng = np.random.default_rng(seed)
+            B = rng.choice([-1.0, 1.0], (n, N, 1)) + 1j * rng.choice([-1.0, 1.0], (n, N, 1))
+            for j in range(3):
+                B[j] = 0
+                for _ in range(j + 1 + seed % 4):
+                    k = [rng.integers(d) for d in dims]
+                    B[j] += (rng.standard_normal() * np.exp(2j * np.pi * sum(a * x / d for a, x, d in zip(k, ix, dims)))
+                             ).reshape(N, 1)
+            B[4] *= rng.random((N, 1)) < 0.15
+            if not np.abs(B[4]).any():
+                B[4][0] = 1
+            for block in (1, 8):
+                _, (st,) = ctx.solve_batch([op], [cuda(B)], ctx.opts(tol=1e-10, inner="f32", rhs_block=block, max_iter=1500),
+                                           check=False)
+                assert st["nconverged"] == n and st["max_true_resid"] <= 1e-10, (seed, m2, block)
